@@ -21,8 +21,6 @@
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kCoarseThreads = 1024;
-constexpr int kCoarseMax = 8000;
 constexpr int kPersistCap = 4096;  // workgroups of a persistent launch (>> 256 CUs)
 constexpr int kGraphSteps = 1024;  // step-table entries reserved when a step is captured
 
@@ -553,17 +551,15 @@ __global__ __launch_bounds__(kThreads) void kb_prolong_add(Arenas A, const int2 
 }
 
 // Coarsest level of every box, one workgroup per box, in LDS (coarse_solve.h).
-__global__ __launch_bounds__(kCoarseThreads) void kb_coarse_solve(Arenas A,
-                                                                  const BoxDev *__restrict__ boxes) {
-  __shared__ float re[kCoarseMax];
-  __shared__ float im[kCoarseMax];
-  __shared__ float tc[pm_coarse::kMaxN], ts[pm_coarse::kMaxN];
+__global__ __launch_bounds__(pm_coarse::kThreads) void kb_coarse_solve(
+    Arenas A, const BoxDev *__restrict__ boxes) {
+  __shared__ float2 spec[pm_coarse::kSpec];
   const int b = blockIdx.x;
   const BoxDev &bx = boxes[b];
   const float coef = A.steps[*A.ctr].coef;
   const LevelView v = level_view(bx, bx.nlev - 1, A.phi, A.rho, A.lu, A.lf, coef, A.rmean, b);
   const float h = 1.0f / (float)v.n;
-  pm_coarse::solve_any(v.u, v.f, v.scale, v.mean, v.n, h * h, re, im, tc, ts);
+  pm_coarse::solve_any(v.u, v.f, v.scale, v.mean, v.n, h * h, spec);
 }
 
 // Per-item partial sums of |f - L u|^2 and |f|^2 on level 0 (convergence records).
@@ -805,7 +801,7 @@ int enqueue_accel(pm_batch *B, const float *pos, float *acc, float *vel, float *
         kb_restrict<PM_RESTRICT_FW><<<persist_grid(R.count), kThreads, 0, s>>>(
             A, B->items + R.off, R.count, B->boxes, l, B->g);
     }
-    kb_coarse_solve<<<B->nboxes, kCoarseThreads, 0, s>>>(A, B->boxes);
+    kb_coarse_solve<<<B->nboxes, pm_coarse::kThreads, 0, s>>>(A, B->boxes);
     for (int l = B->maxlev - 2; l >= 0; --l) {
       const pm_batch::List &F = B->finer[l];
       if (F.count == 0) continue;
@@ -947,7 +943,7 @@ int pm_batch_create(pm_batch **out, int nboxes, const int *n, const int64_t *np,
     if (n[b] < 8 || n[b] > 1024 || (n[b] & 1)) return PM_ERR_SHAPE;
     int m = n[b];
     while (m > 16 && m % 4 == 0) m /= 2;
-    if ((int64_t)m * m * m > kCoarseMax) return PM_ERR_SHAPE;
+    if (m > pm_coarse::kMaxN) return PM_ERR_SHAPE;
     if (np[b] < 1 || np[b] > INT32_MAX / 2) return PM_ERR_SHAPE;
   }
   pm_batch *B = new pm_batch();

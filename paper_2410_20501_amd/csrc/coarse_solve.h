@@ -1,196 +1,262 @@
-// Coarsest multigrid level (at most 20^3 cells), solved exactly by one 1024-thread
-// workgroup in LDS (the recursion's last level, paper Sect. 3.7.1). On a periodic
-// grid the seven-point operator is diagonal in the discrete Fourier basis:
+// Coarsest multigrid level (8 to 18 cells a side, an even number), solved exactly by one
+// workgroup (the recursion's last level, paper Sect. 3.7.1). On a periodic grid the
+// seven-point operator is diagonal in the discrete Fourier basis:
 //   L e^{i 2 pi (a i + b j + c k)/n} = lambda e^{...},
-//   lambda = (2 cos(2 pi a/n) + 2 cos(2 pi b/n) + 2 cos(2 pi c/n) - 6) / h^2,
+//   lambda = (s_a + s_b + s_c) / h^2,  s_m = 2 cos(2 pi m/n) - 2,
 // so u = DFT^-1[ DFT[f] / lambda ] with the zero mode set to zero (the periodic
 // problem's mean: the right-hand side's mean is dropped, the solution has mean zero).
-// The transforms are direct DFTs along each axis (n <= 20, any n), in FP32.
+//
+// What bounds it is the chain of passes on one compute unit. A thread transforms whole
+// lines in registers, with the length and every twiddle known at compile time; the k
+// transform is real to half complex straight from global memory, the i transform is
+// followed by its own inverse without leaving the registers, and the last k transform
+// goes straight back, so the grid crosses LDS four times, as the n^2 (n/2 + 1) half
+// spectrum.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace pm_coarse {
 
-constexpr int kThreads = 1024;
-constexpr int kMaxCells = 8000;
-constexpr int kMaxN = 20;
-constexpr int kItems = (kMaxCells + kThreads - 1) / kThreads;  // outputs per thread and pass
+constexpr int kThreads = 384;  // lines of the largest size: 18^2, whole waves
+constexpr int kMaxN = 18;
+constexpr int kSpec = kMaxN * kMaxN * (kMaxN / 2 + 1);  // complex values in LDS
 
-// One DFT pass along `axis` (0: i, stride n^2; 1: j, stride n; 2: k, stride 1) over the
-// planar complex grid (re, im), in place: every thread forms its outputs from the
-// line in LDS, then all write after a barrier. sgn = -1 forward, +1 inverse.
-__device__ __forceinline__ void dft_pass(float *re, float *im, const float *tc, const float *ts,
-                                         int n, int axis, float sgn) {
-  const int count = n * n * n;
-  const int st = axis == 0 ? n * n : (axis == 1 ? n : 1);
-  float orr[kItems], oii[kItems];
-#pragma unroll
-  for (int it = 0; it < kItems; ++it) {
-    const int c = threadIdx.x + it * kThreads;
-    orr[it] = oii[it] = 0.f;
-    if (c < count) {
-      const int i = c / (n * n), j = (c / n) % n, k = c % n;
-      const int p = axis == 0 ? i : (axis == 1 ? j : k);
-      const int base = c - p * st;
-      float sr = 0.f, si = 0.f;
-      int idx = 0;  // (m p) mod n
-      for (int m = 0; m < n; ++m) {
-        const float wr = tc[idx], wi = sgn * ts[idx];
-        const float xr = re[base + m * st], xi = im[base + m * st];
-        sr = fmaf(xr, wr, fmaf(-xi, wi, sr));
-        si = fmaf(xr, wi, fmaf(xi, wr, si));
-        idx += p;
-        if (idx >= n) idx -= n;
-      }
-      orr[it] = sr;
-      oii[it] = si;
-    }
+// cos and sin of 2 pi m / n at compile time, from the Taylor series about the nearest
+// multiple of pi / 2 (angle at most pi / 4: 14 terms reach the last bit of a double)
+constexpr double kPi = 3.14159265358979323846;
+constexpr double taylor(double x, bool sine) {
+  double term = sine ? x : 1.0, sum = term;
+  for (int k = 1; k <= 14; ++k) {
+    const int d = sine ? 2 * k * (2 * k + 1) : (2 * k - 1) * 2 * k;
+    term *= -x * x / d;
+    sum += term;
   }
-  __syncthreads();
-#pragma unroll
-  for (int it = 0; it < kItems; ++it) {
-    const int c = threadIdx.x + it * kThreads;
-    if (c < count) {
-      re[c] = orr[it];
-      im[c] = oii[it];
-    }
-  }
-  __syncthreads();
+  return sum;
 }
-
-// 16^3 (the coarsest level of every power-of-two grid): each of 256 threads transforms
-// one whole line in registers with a radix-2 FFT, so a pass reads and writes every value
-// of the grid once (the direct DFT reads each line n times). LDS index c + c / 16 (one
-// padding word per line along k) keeps the stride-1 lines of the k pass off a single
-// bank.
-constexpr int kFftN = 16;
-__device__ __forceinline__ int pad16(int c) { return c + (c >> 4); }
-
-// cos and sin of 2 pi k / 16, k = 0 .. 7
-__device__ constexpr float kC16[8] = {1.0f, 0.92387953251128674f, 0.70710678118654752f,
-                                      0.38268343236508977f, 0.0f, -0.38268343236508977f,
-                                      -0.70710678118654752f, -0.92387953251128674f};
-__device__ constexpr float kS16[8] = {0.0f, 0.38268343236508977f, 0.70710678118654752f,
-                                      0.92387953251128674f, 1.0f, 0.92387953251128674f,
-                                      0.70710678118654752f, 0.38268343236508977f};
-
-// in-place 16-point FFT of (xr, xi): bit-reversed order, then four radix-2 stages with
-// twiddles e^{sgn 2 pi i j / len}; sgn = -1 forward, +1 inverse (unnormalised)
-__device__ __forceinline__ void fft16(float (&xr)[kFftN], float (&xi)[kFftN], float sgn) {
-#pragma unroll
-  for (int i = 0; i < kFftN; ++i) {
-    const int r = ((i & 1) << 3) | ((i & 2) << 1) | ((i & 4) >> 1) | ((i & 8) >> 3);
-    if (r > i) {
-      const float tr = xr[i], ti = xi[i];
-      xr[i] = xr[r];
-      xi[i] = xi[r];
-      xr[r] = tr;
-      xi[r] = ti;
-    }
-  }
-#pragma unroll
-  for (int len = 2; len <= kFftN; len <<= 1) {
-#pragma unroll
-    for (int i = 0; i < kFftN; i += len) {
-#pragma unroll
-      for (int j = 0; j < len / 2; ++j) {
-        const int t = j * (kFftN / len);  // twiddle index in sixteenths
-        const float wr = kC16[t], wi = sgn * kS16[t];
-        const int a = i + j, b = a + len / 2;
-        const float vr = xr[b] * wr - xi[b] * wi, vi = xr[b] * wi + xi[b] * wr;
-        xr[b] = xr[a] - vr;
-        xi[b] = xi[a] - vi;
-        xr[a] += vr;
-        xi[a] += vi;
-      }
-    }
+constexpr double turn(int m, int n, bool sine) {
+  m = ((m % n) + n) % n;
+  const int q = (8 * m + n) / (2 * n);  // nearest quarter turn, 0 .. 4
+  const double x = 2.0 * kPi * (4.0 * m - (double)q * n) / (4.0 * n);
+  const double c = taylor(x, false), s = taylor(x, true);
+  switch (q & 3) {
+    case 0: return sine ? s : c;
+    case 1: return sine ? c : -s;
+    case 2: return sine ? -s : -c;
+    default: return sine ? -c : s;
   }
 }
 
-__device__ void fft16_pass(float *re, float *im, int axis, float sgn) {
+// In-place DFT of N values (natural order in and out), e^{-2 pi i/N} forward, its
+// conjugate inverse (INV), unnormalised: even lengths split into the even and odd
+// elements, odd lengths summed directly.
+template <int N, bool INV>
+struct Dft {
+  static __device__ __forceinline__ void run(float2 (&x)[N]) {
+    if constexpr (N == 2) {
+      const float2 a = x[0], b = x[1];
+      x[0] = make_float2(a.x + b.x, a.y + b.y);
+      x[1] = make_float2(a.x - b.x, a.y - b.y);
+    } else if constexpr (N % 2 == 0) {
+      float2 e[N / 2], o[N / 2];
+#pragma unroll
+      for (int m = 0; m < N / 2; ++m) {
+        e[m] = x[2 * m];
+        o[m] = x[2 * m + 1];
+      }
+      Dft<N / 2, INV>::run(e);
+      Dft<N / 2, INV>::run(o);
+      combine<0>(x, e, o);
+    } else {
+      direct(x);
+    }
+  }
+  template <int K>
+  static __device__ __forceinline__ void combine(float2 (&x)[N], const float2 (&e)[N / 2],
+                                                 const float2 (&o)[N / 2]) {
+    if constexpr (K < N / 2) {
+      float2 t = o[K];
+      if constexpr (4 * K == N) {
+        t = INV ? make_float2(-t.y, t.x) : make_float2(t.y, -t.x);
+      } else if constexpr (K > 0) {
+        constexpr float c = (float)turn(K, N, false), s = (float)(INV ? 1.0 : -1.0) * (float)turn(K, N, true);
+        t = make_float2(t.x * c - t.y * s, t.x * s + t.y * c);
+      }
+      x[K] = make_float2(e[K].x + t.x, e[K].y + t.y);
+      x[K + N / 2] = make_float2(e[K].x - t.x, e[K].y - t.y);
+      combine<K + 1>(x, e, o);
+    }
+  }
+  // odd N: the pairs x_m +- x_{N-m} halve the products
+  static __device__ __forceinline__ void direct(float2 (&x)[N]) {
+    float2 p[N / 2 + 1], q[N / 2 + 1], y[N];
+    float2 all = x[0];
+#pragma unroll
+    for (int m = 1; m <= N / 2; ++m) {
+      p[m] = make_float2(x[m].x + x[N - m].x, x[m].y + x[N - m].y);
+      q[m] = make_float2(x[m].x - x[N - m].x, x[m].y - x[N - m].y);
+      all = make_float2(all.x + p[m].x, all.y + p[m].y);
+    }
+    y[0] = all;
+    rows<1>(x, p, q, y);
+#pragma unroll
+    for (int m = 0; m < N; ++m) x[m] = y[m];
+  }
+  template <int K>
+  static __device__ __forceinline__ void rows(const float2 (&x)[N], const float2 (&p)[N / 2 + 1],
+                                              const float2 (&q)[N / 2 + 1], float2 (&y)[N]) {
+    if constexpr (K <= N / 2) {
+      float2 a = x[0], b = make_float2(0.f, 0.f);
+      terms<K, 1>(p, q, a, b);
+      // y_K = a -+ i b, y_{N-K} = a +- i b
+      const float2 ib = INV ? make_float2(-b.y, b.x) : make_float2(b.y, -b.x);
+      y[K] = make_float2(a.x + ib.x, a.y + ib.y);
+      y[N - K] = make_float2(a.x - ib.x, a.y - ib.y);
+      rows<K + 1>(x, p, q, y);
+    }
+  }
+  template <int K, int M>
+  static __device__ __forceinline__ void terms(const float2 (&p)[N / 2 + 1],
+                                               const float2 (&q)[N / 2 + 1], float2 &a, float2 &b) {
+    if constexpr (M <= N / 2) {
+      constexpr float c = (float)turn(K * M, N, false), s = (float)turn(K * M, N, true);
+      a = make_float2(fmaf(c, p[M].x, a.x), fmaf(c, p[M].y, a.y));
+      b = make_float2(fmaf(s, q[M].x, b.x), fmaf(s, q[M].y, b.y));
+      terms<K, M + 1>(p, q, a, b);
+    }
+  }
+};
+
+// Real line x[0 .. N) <-> half spectrum X[0 .. N/2] by a complex transform of half the
+// length: z_m = x_{2m} + i x_{2m+1}, X_k = E_k + w^k O_k with E, O the even and odd parts
+// of Z; the inverse forms (X_k + conj X_{N/2-k}) + i conj(w^k)(X_k - conj X_{N/2-k}) and
+// gives N times the line.
+template <int N, int K>
+__device__ __forceinline__ void split(const float2 (&z)[N / 2], float2 (&X)[N / 2 + 1]) {
+  if constexpr (K <= N / 2) {
+    constexpr int a = K == N / 2 ? 0 : K, b = K == 0 ? 0 : N / 2 - K;
+    constexpr float c = (float)turn(K, N, false), s = -(float)turn(K, N, true);
+    const float2 E = make_float2(0.5f * (z[a].x + z[b].x), 0.5f * (z[a].y - z[b].y));
+    const float2 O = make_float2(0.5f * (z[a].y + z[b].y), -0.5f * (z[a].x - z[b].x));
+    X[K] = make_float2(E.x + (c * O.x - s * O.y), E.y + (c * O.y + s * O.x));
+    split<N, K + 1>(z, X);
+  }
+}
+template <int N, int K>
+__device__ __forceinline__ void join(const float2 (&X)[N / 2 + 1], float2 (&z)[N / 2]) {
+  if constexpr (K < N / 2) {
+    constexpr float c = (float)turn(K, N, false), s = (float)turn(K, N, true);
+    const float2 p = X[K], q = make_float2(X[N / 2 - K].x, -X[N / 2 - K].y);
+    const float2 e = make_float2(p.x + q.x, p.y + q.y), d = make_float2(p.x - q.x, p.y - q.y);
+    const float2 o = make_float2(c * d.x - s * d.y, c * d.y + s * d.x);
+    z[K] = make_float2(e.x - o.y, e.y + o.x);
+    join<N, K + 1>(X, z);
+  }
+}
+
+// One pass over the half spectrum in LDS: the N-point transforms of lines of stride
+// `stride` that start at `base`.
+template <int N, bool INV>
+__device__ __forceinline__ void line_pass(float2 *spec, int base, int stride) {
+  float2 x[N];
+#pragma unroll
+  for (int m = 0; m < N; ++m) x[m] = spec[base + m * stride];
+  Dft<N, INV>::run(x);
+#pragma unroll
+  for (int m = 0; m < N; ++m) spec[base + m * stride] = x[m];
+}
+
+// 1 / (s_a + rest), a = 0 .. N - 1 in registers of the i pass; the zero mode gives 0
+template <int N, int A>
+__device__ __forceinline__ void divide(float2 (&x)[N], float rest, float unit, bool zero) {
+  if constexpr (A < N) {
+    constexpr float sa = (float)(2.0 * turn(A, N, false) - 2.0);
+    const float r = A == 0 && zero ? 0.0f : unit / (sa + rest);
+    x[A] = make_float2(x[A].x * r, x[A].y * r);
+    divide<N, A + 1>(x, rest, unit, zero);
+  }
+}
+
+// s_m for a run-time m
+template <int N>
+__device__ __forceinline__ float symbol(int m) {
+  float s = 0.0f;
+  auto pick = [&](auto self, auto I) {
+    constexpr int i = decltype(I)::value;
+    if constexpr (i < N) {
+      constexpr float v = (float)(2.0 * turn(i, N, false) - 2.0);
+      s = m == i ? v : s;
+      self(self, std::integral_constant<int, i + 1>{});
+    }
+  };
+  pick(pick, std::integral_constant<int, 0>{});
+  return s;
+}
+
+// ug = L^-1 (scale (fg - mean)) with zero mean on N^3 cells. spec: LDS, kSpec values.
+template <int N>
+__device__ __forceinline__ void solve(float *__restrict__ ug, const float *__restrict__ fg, float scale,
+                                      float mean, float h2, float2 *spec) {
+  constexpr int NH = N / 2 + 1;
   const int t = threadIdx.x;
-  if (t < kFftN * kFftN) {
-    const int st = axis == 0 ? kFftN * kFftN : (axis == 1 ? kFftN : 1);
-    const int u = t / kFftN, v = t % kFftN;  // the line's two other coordinates
-    const int base = axis == 0 ? u * kFftN + v : (axis == 1 ? u * kFftN * kFftN + v
-                                                            : (u * kFftN + v) * kFftN);
-    float xr[kFftN], xi[kFftN];
+  const bool row = t < N * N, line = t < N * NH;
+  const int lo = t / NH, kz = t - lo * NH;  // a line of the j and i passes
+  if (row) {
+    const float2 *src = reinterpret_cast<const float2 *>(fg + (size_t)t * N);
+    float2 z[N / 2], X[NH];
 #pragma unroll
-    for (int m = 0; m < kFftN; ++m) {
-      const int c = pad16(base + m * st);
-      xr[m] = re[c];
-      xi[m] = im[c];
-    }
-    fft16(xr, xi, sgn);
+    for (int m = 0; m < N / 2; ++m) z[m] = src[m];
 #pragma unroll
-    for (int m = 0; m < kFftN; ++m) {
-      const int c = pad16(base + m * st);
-      re[c] = xr[m];
-      im[c] = xi[m];
-    }
+    for (int m = 0; m < N / 2; ++m)
+      z[m] = make_float2(scale * (z[m].x - mean), scale * (z[m].y - mean));
+    Dft<N / 2, false>::run(z);
+    split<N, 0>(z, X);
+#pragma unroll
+    for (int k = 0; k < NH; ++k) spec[t * NH + k] = X[k];
   }
   __syncthreads();
+  if (line) line_pass<N, false>(spec, lo * N * NH + kz, NH);
+  __syncthreads();
+  if (line) {
+    // i transform, division by lambda (and by the transforms' N^3), inverse i transform
+    float2 x[N];
+    const int base = lo * NH + kz;
+#pragma unroll
+    for (int m = 0; m < N; ++m) x[m] = spec[base + m * N * NH];
+    Dft<N, false>::run(x);
+    divide<N, 0>(x, symbol<N>(lo) + symbol<N>(kz), h2 / (float)(N * N * N), lo == 0 && kz == 0);
+    Dft<N, true>::run(x);
+#pragma unroll
+    for (int m = 0; m < N; ++m) spec[base + m * N * NH] = x[m];
+  }
+  __syncthreads();
+  if (line) line_pass<N, true>(spec, lo * N * NH + kz, NH);
+  __syncthreads();
+  if (row) {
+    float2 X[NH], z[N / 2];
+#pragma unroll
+    for (int k = 0; k < NH; ++k) X[k] = spec[t * NH + k];
+    join<N, 0>(X, z);
+    Dft<N / 2, true>::run(z);
+    float2 *dst = reinterpret_cast<float2 *>(ug + (size_t)t * N);
+#pragma unroll
+    for (int m = 0; m < N / 2; ++m) dst[m] = z[m];
+  }
 }
 
-__device__ void solve16(float *__restrict__ ug, const float *__restrict__ fg, float scale,
-                        float mean, float h2, float *re, float *im) {
-  constexpr int count = kFftN * kFftN * kFftN;
-  for (int c = threadIdx.x; c < count; c += kThreads) {
-    re[pad16(c)] = scale * (fg[c] - mean);
-    im[pad16(c)] = 0.f;
+// any coarsest size (uniform n)
+__device__ __forceinline__ void solve_any(float *__restrict__ ug, const float *__restrict__ fg, float scale,
+                                          float mean, int n, float h2, float2 *spec) {
+  switch (n) {
+    case 8: solve<8>(ug, fg, scale, mean, h2, spec); break;
+    case 10: solve<10>(ug, fg, scale, mean, h2, spec); break;
+    case 12: solve<12>(ug, fg, scale, mean, h2, spec); break;
+    case 14: solve<14>(ug, fg, scale, mean, h2, spec); break;
+    case 16: solve<16>(ug, fg, scale, mean, h2, spec); break;
+    default: solve<18>(ug, fg, scale, mean, h2, spec); break;
   }
-  __syncthreads();
-  for (int axis = 0; axis < 3; ++axis) fft16_pass(re, im, axis, -1.0f);
-  const float inv_h2 = 1.0f / h2;
-  for (int c = threadIdx.x; c < count; c += kThreads) {
-    const int a = c >> 8, b = (c >> 4) & 15, k = c & 15;
-    auto cs = [](int m) { return m < 8 ? kC16[m] : -kC16[m - 8]; };  // cos(2 pi m / 16)
-    const float lam = (2.0f * (cs(a) + cs(b) + cs(k)) - 6.0f) * inv_h2;
-    const float r = c == 0 ? 0.f : 1.0f / lam;
-    re[pad16(c)] *= r;
-    im[pad16(c)] *= r;
-  }
-  __syncthreads();
-  for (int axis = 0; axis < 3; ++axis) fft16_pass(re, im, axis, 1.0f);
-  const float inv_count = 1.0f / (float)count;
-  for (int c = threadIdx.x; c < count; c += kThreads) ug[c] = re[pad16(c)] * inv_count;
-}
-
-// ug = L^-1 (scale (fg - mean)) with zero mean. re, im: LDS arrays of kMaxCells floats;
-// tc, ts: LDS arrays of kMaxN floats (cosine and sine table).
-__device__ void solve_any(float *__restrict__ ug, const float *__restrict__ fg, float scale,
-                          float mean, int n, float h2, float *re, float *im, float *tc,
-                          float *ts) {
-  if (n == kFftN) {
-    solve16(ug, fg, scale, mean, h2, re, im);
-    return;
-  }
-  const int count = n * n * n;
-  for (int c = threadIdx.x; c < count; c += kThreads) {
-    re[c] = scale * (fg[c] - mean);
-    im[c] = 0.f;
-  }
-  for (int m = threadIdx.x; m < n; m += kThreads) {
-    double s, co;
-    sincospi(2.0 * m / n, &s, &co);  // table in FP64, then rounded
-    tc[m] = (float)co;
-    ts[m] = (float)s;
-  }
-  __syncthreads();
-  for (int axis = 0; axis < 3; ++axis) dft_pass(re, im, tc, ts, n, axis, -1.0f);
-  const float inv_h2 = 1.0f / h2;
-  for (int c = threadIdx.x; c < count; c += kThreads) {
-    const int a = c / (n * n), b = (c / n) % n, k = c % n;
-    const float lam = (2.0f * (tc[a] + tc[b] + tc[k]) - 6.0f) * inv_h2;
-    const float r = c == 0 ? 0.f : 1.0f / lam;
-    re[c] *= r;
-    im[c] *= r;
-  }
-  __syncthreads();
-  for (int axis = 0; axis < 3; ++axis) dft_pass(re, im, tc, ts, n, axis, 1.0f);
-  const float inv_count = 1.0f / (float)count;
-  for (int c = threadIdx.x; c < count; c += kThreads) ug[c] = re[c] * inv_count;
 }
 
 }  // namespace pm_coarse

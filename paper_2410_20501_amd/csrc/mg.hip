@@ -14,6 +14,7 @@
 #include <cmath>
 
 #include "coarse_solve.h"
+#include "mg_tile.h"
 
 // streaming levels at least this large add the prolonged correction inside the first
 // post-smoothing pass (measured: 519 us against 434 + 209 us at 512^3; at 256^3 the
@@ -26,8 +27,6 @@
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kCoarseThreads = 1024;
-constexpr int kCoarseMax = 8000;  // cells held in LDS by the coarsest-level solve (20^3)
 
 __device__ __forceinline__ int wrap_index(int i, int n) {
   i += (i < 0) ? n : 0;
@@ -283,14 +282,6 @@ __global__ __launch_bounds__(kThreads) void k_scale(float *__restrict__ u, int64
   u[c] *= s;
 }
 
-// Subtract the device-resident mean from a grid.
-__global__ __launch_bounds__(kThreads) void k_subtract_mean(float *__restrict__ u, int64_t count,
-                                                            const float *__restrict__ mean) {
-  const int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (c >= count) return;
-  u[c] -= *mean;
-}
-
 // Totals of the three per-block sums of the norm-summing smoother pass.
 __global__ __launch_bounds__(RED_THREADS) void k_triple_final(const double *__restrict__ partial,
                                                               int nblocks,
@@ -415,18 +406,109 @@ __global__ __launch_bounds__(kThreads) void k_finish_phi4(const float4 *__restri
                        fmaf(scale, v.w, -m));
 }
 
-// Coarsest level: one workgroup, in LDS (coarse_solve.h).
-__global__ __launch_bounds__(kCoarseThreads) void k_coarse_solve(
+// Coarsest level: one workgroup (coarse_solve.h).
+template <int N>
+__global__ __launch_bounds__(pm_coarse::kThreads) void k_coarse_solve(
     float *__restrict__ ug, const float *__restrict__ fg, float scale,
-    const float *__restrict__ mean, int n, float h2) {
-  __shared__ float re[kCoarseMax];
-  __shared__ float im[kCoarseMax];
-  __shared__ float tc[pm_coarse::kMaxN], ts[pm_coarse::kMaxN];
-  pm_coarse::solve_any(ug, fg, scale, src_mean(mean), n, h2, re, im, tc, ts);
+    const float *__restrict__ mean, float h2) {
+  __shared__ float2 spec[N * N * (N / 2 + 1)];
+  pm_coarse::solve<N>(ug, fg, scale, src_mean(mean), h2, spec);
+}
+
+// the block's tile of an n^3 level in TI x TJ x TK tiles (XCD-aware: neighbours along k,
+// then j, share an L2 and each other's halos)
+template <class S>
+__device__ __forceinline__ void block_tile(int n, int &i0, int &j0, int &k0) {
+  const unsigned b = xcd_block(blockIdx.x, gridDim.x);
+  const unsigned tk = (unsigned)pm_tile::tiles_of(n, S::TK), tj = (unsigned)pm_tile::tiles_of(n, S::TJ);
+  const unsigned q = b / tk;
+  k0 = (int)(b - q * tk) * S::TK;
+  j0 = (int)(q % tj) * S::TJ;
+  i0 = (int)(q / tj) * S::TI;
+}
+
+// The tile kernels (mg_tile.h). down: pre-smoothing, residual and restriction of a level,
+// with NORM also the three sums of the convergence test (three doubles per block); up:
+// prolongation and post-smoothing.
+template <int TI, int TJ, int TK, int KIND, bool OM1, bool NORM>
+__global__ __launch_bounds__((pm_tile::Down<TI, TJ, TK>::NT)) void k_tile_down(
+    pm_tile::Level a, const float *__restrict__ mean, int hs, float *__restrict__ fc,
+    double *__restrict__ partial) {
+  using S = pm_tile::Down<TI, TJ, TK>;
+  __shared__ __align__(16) float lds[S::LDS];
+  int i0, j0, k0;
+  block_tile<S>(a.n, i0, j0, k0);
+  a.mean = src_mean(mean);
+  double sum[3];
+  pm_tile::tile_down<TI, TJ, TK, KIND, OM1, NORM>(a, i0, j0, k0, hs, fc, lds, sum);
+  if constexpr (NORM) {
+    __shared__ double l[3][S::NT / 64];
+#pragma unroll
+    for (int v = 0; v < 3; ++v) {
+      const double w = wave_sum(sum[v]);
+      if ((threadIdx.x & 63) == 0) l[v][threadIdx.x >> 6] = w;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+      double t = 0.0;
+      for (int w = 0; w < S::NT / 64; ++w) t += l[threadIdx.x][w];
+      partial[3 * blockIdx.x + threadIdx.x] = t;
+    }
+  }
+}
+
+template <int TI, int TJ, int TK, bool OM1>
+__global__ __launch_bounds__((pm_tile::Up<TI, TJ, TK>::NT)) void k_tile_up(
+    pm_tile::Level a, const float *__restrict__ mean, const float *__restrict__ ec, int hs) {
+  using S = pm_tile::Up<TI, TJ, TK>;
+  __shared__ __align__(16) float lds[S::LDS];
+  __shared__ float raw[S::RAW];
+  int i0, j0, k0;
+  block_tile<S>(a.n, i0, j0, k0);
+  a.mean = src_mean(mean);
+  pm_tile::tile_up<TI, TJ, TK, OM1>(a, ec, i0, j0, k0, hs, lds, raw);
 }
 
 inline unsigned blocks_for(int64_t count, int threads) {
   return (unsigned)((count + threads - 1) / threads);
+}
+
+inline unsigned tile_blocks(int n, int ti, int tj, int tk) {
+  return (unsigned)(pm_tile::tiles_of(n, ti) * pm_tile::tiles_of(n, tj) * pm_tile::tiles_of(n, tk));
+}
+
+// Tile shape of a level (cells along i, j, k). A larger tile recomputes less halo, a
+// smaller one shortens a workgroup's chain and gives a small grid more workgroups. Us per
+// V(2,2) cycle measured with 2 x 4 x 16 | 4 x 8 x 32 | 8 x 16 x 32 tiles on the finest level:
+// 32^3 17 | 19 | -, 48^3 32 | 30 | -, 64^3 - | 32 | 35, 80^3 - | 54 | 52, 128^3 - | 85 | 71.
+#ifndef PM_TILE_BIG_N
+#define PM_TILE_BIG_N 80
+#endif
+#ifndef PM_TILE_MID_N
+#define PM_TILE_MID_N 48
+#endif
+#ifndef PM_TILE_BIG
+#define PM_TILE_BIG 8, 16, 32
+#endif
+#ifndef PM_TILE_MID
+#define PM_TILE_MID 4, 8, 32
+#endif
+#ifndef PM_TILE_LOW
+#define PM_TILE_LOW 2, 4, 16
+#endif
+#define PM_TILE_SHAPES(n, CALL)                    \
+  do {                                             \
+    if ((n) >= PM_TILE_BIG_N) CALL(PM_TILE_BIG);   \
+    else if ((n) >= PM_TILE_MID_N) CALL(PM_TILE_MID); \
+    else CALL(PM_TILE_LOW);                           \
+  } while (0)
+
+inline unsigned norm_blocks(int n) {
+  unsigned nb;
+#define PM_BLOCKS(...) nb = tile_blocks(n, __VA_ARGS__)
+  PM_TILE_SHAPES(n, PM_BLOCKS);
+#undef PM_BLOCKS
+  return nb;
 }
 
 // Floor detection of the tolerance loop: below a relative residual of kFloorBelow, a
@@ -440,11 +522,11 @@ struct Src {
   const float *mean;
 };
 
-// Host-side V-cycle driver. Levels with n >= PM_STREAM_MIN_N (and an alt buffer)
-// run the streaming kernels with ping-pong buffers: cur[l] holds the current
-// iterate, a smoothing pass writes alt and the two are swapped. Every full
-// V-cycle swaps twice, so level 0 ends in the caller's phi. Smaller levels run
-// one kernel per red-black half-sweep, in place.
+// Host-side V-cycle driver. Every level above the coarsest has two iterate buffers:
+// cur[l] holds the current iterate, a pass of the streaming or tile kernels writes alt
+// and the two are swapped; the solve's last pass copies the result to the caller's phi.
+// In a reference context the levels have one buffer and run one kernel per red-black
+// half-sweep, in place.
 struct Solver {
   pm_ctx *ctx;
   hipStream_t s;
@@ -458,8 +540,85 @@ struct Solver {
     const double h = 1.0 / ctx->lev[l].n;
     return (float)(h * h);
   }
-  bool streaming(int l) const {
-    return alt[l] != nullptr && !(ctx->flags & PM_CREATE_REFERENCE_KERNELS);
+  // levels of PM_STREAM_MIN_N cells a side and more stream, smaller ones (above the
+  // coarsest) run the tile kernels; a reference context runs the plain kernels everywhere
+  bool streaming(int l) const { return alt[l] != nullptr && ctx->lev[l].n >= PM_STREAM_MIN_N; }
+  bool tiled(int l) const { return alt[l] != nullptr && ctx->lev[l].n < PM_STREAM_MIN_N; }
+  float guess_factor(int l) const { return -h2(l) / 6.0f; }  // Jacobi step from zero
+
+  pm_tile::Level tile_level(int l, bool from_guess, float uscale) const {
+    const Src sr = src(l);
+    const float hh = h2(l);
+    return pm_tile::Level{from_guess ? nullptr : cur[l], alt[l], sr.f, sr.scale, 0.0f, uscale,
+                          guess_factor(l), ctx->lev[l].n, hh, 1.0f / hh, p->omega};
+  }
+
+  // Down a tiled level: `left` sweeps in passes of at most two and, where `restricts`, in
+  // the last pass the residual and its restriction. The first pass may start from the
+  // Jacobi guess, scale its input, and sum the norms of it (partial).
+  hipError_t tile_down(int l, int left, bool restricts, bool from_guess = false, float uscale = 1.0f,
+                       double *partial = nullptr) {
+    do {
+      const int now = std::min(left, 2);
+      left -= now;
+      launch_tile_down(tile_level(l, from_guess, uscale), src(l).mean, 2 * now,
+                       left == 0 && restricts ? ctx->lev[l + 1].f : nullptr, partial);
+      std::swap(cur[l], alt[l]);
+      from_guess = false;
+      uscale = 1.0f;
+      partial = nullptr;
+    } while (left > 0);
+    return hipGetLastError();
+  }
+
+  // Up a tiled level: prolongation with the first two of p->post sweeps, then the rest.
+  hipError_t tile_up(int l) {
+    int left = p->post;
+    const float *ec = cur[l + 1];
+    do {
+      const int now = std::min(left, 2);
+      left -= now;
+      launch_tile_up(tile_level(l, false, 1.0f), src(l).mean, ec, 2 * now);
+      std::swap(cur[l], alt[l]);
+      ec = nullptr;
+    } while (left > 0);
+    return hipGetLastError();
+  }
+
+  template <int TI, int TJ, int TK>
+  void launch_tile_down_shape(const pm_tile::Level &a, const float *mean, int hs, float *fc,
+                              double *partial) {
+    const unsigned nb = tile_blocks(a.n, TI, TJ, TK);
+    constexpr int NT = pm_tile::Down<TI, TJ, TK>::NT;
+    const bool om1 = a.omega == 1.0f, norm = partial != nullptr;
+#define PM_TILE_DOWN(K_, O_, N_) k_tile_down<TI, TJ, TK, K_, O_, N_><<<nb, NT, 0, s>>>(a, mean, hs, fc, partial)
+#define PM_TILE_DOWN_KIND(K_)                                                        \
+  do {                                                                               \
+    if (om1) { if (norm) PM_TILE_DOWN(K_, true, true); else PM_TILE_DOWN(K_, true, false); } \
+    else { if (norm) PM_TILE_DOWN(K_, false, true); else PM_TILE_DOWN(K_, false, false); }   \
+  } while (0)
+    if (p->restrict_kind == PM_RESTRICT_AVG) PM_TILE_DOWN_KIND(PM_RESTRICT_AVG);
+    else PM_TILE_DOWN_KIND(PM_RESTRICT_FW);
+#undef PM_TILE_DOWN_KIND
+#undef PM_TILE_DOWN
+  }
+  void launch_tile_down(const pm_tile::Level &a, const float *mean, int hs, float *fc, double *partial) {
+#define PM_DOWN_SHAPE(...) launch_tile_down_shape<__VA_ARGS__>(a, mean, hs, fc, partial)
+    PM_TILE_SHAPES(a.n, PM_DOWN_SHAPE);
+#undef PM_DOWN_SHAPE
+  }
+
+  template <int TI, int TJ, int TK>
+  void launch_tile_up_shape(const pm_tile::Level &a, const float *mean, const float *ec, int hs) {
+    const unsigned nb = tile_blocks(a.n, TI, TJ, TK);
+    constexpr int NT = pm_tile::Up<TI, TJ, TK>::NT;
+    if (a.omega == 1.0f) k_tile_up<TI, TJ, TK, true><<<nb, NT, 0, s>>>(a, mean, ec, hs);
+    else k_tile_up<TI, TJ, TK, false><<<nb, NT, 0, s>>>(a, mean, ec, hs);
+  }
+  void launch_tile_up(const pm_tile::Level &a, const float *mean, const float *ec, int hs) {
+#define PM_UP_SHAPE(...) launch_tile_up_shape<__VA_ARGS__>(a, mean, ec, hs)
+    PM_TILE_SHAPES(a.n, PM_UP_SHAPE);
+#undef PM_UP_SHAPE
   }
 
   hipError_t half_sweeps(int l, int first_colour, int sweeps) {
@@ -512,8 +671,10 @@ struct Solver {
     // coarse starting guess: one Jacobi step -H^2 d_H / 6, written with the restriction
     const float gscale = -h2(l + 1) / 6.0f;
     if (streaming(l)) {
+      // (a tiled level forms its starting guess from its right-hand side itself)
       hipError_t e = launch_rr_stream(cur[l], sr.f, sr.scale, sr.mean, n, inv_h2, p->restrict_kind,
-                                      ctx->lev[l + 1].f, cur[l + 1], gscale, s);
+                                      ctx->lev[l + 1].f, tiled(l + 1) ? nullptr : cur[l + 1],
+                                      gscale, s);
       if (e != hipSuccess) return e;
     } else {
       float *r = ctx->lev[l].res;
@@ -531,6 +692,7 @@ struct Solver {
 
   hipError_t correct_and_post_smooth(int l) {
     const int n = ctx->lev[l].n;
+    if (tiled(l)) return tile_up(l);
     // streaming levels: the first post-smoothing pass adds the prolonged correction as
     // it reads each plane (coarse planes staged in LDS), so u is not read and written
     // an extra time
@@ -544,21 +706,41 @@ struct Solver {
 
   hipError_t coarse(int l) {
     const Src sr = src(l);
-    k_coarse_solve<<<1, kCoarseThreads, 0, s>>>(cur[l], sr.f, sr.scale, sr.mean, ctx->lev[l].n,
-                                                h2(l));
+    const int n = ctx->lev[l].n;
+#define PM_COARSE(N_)                                                                      \
+  case N_:                                                                                 \
+    k_coarse_solve<N_><<<1, (N_ * N_ + 63) / 64 * 64, 0, s>>>(cur[l], sr.f, sr.scale,      \
+                                                              sr.mean, h2(l));             \
+    break
+    switch (n) {
+      PM_COARSE(8);
+      PM_COARSE(10);
+      PM_COARSE(12);
+      PM_COARSE(14);
+      PM_COARSE(16);
+      PM_COARSE(18);
+      default: return hipErrorInvalidValue;  // (pm_mg_setup ends at one of these)
+    }
+#undef PM_COARSE
     return hipGetLastError();
   }
 
   // One cycle from level l (shape p->cycle unless given); when pre_done, the
-  // pre-smoothing of level l has run. The coarse error equation is treated by one V
+  // pre-smoothing of level l has run (and, on a tiled level, the restriction); with
+  // from_guess its iterate is the Jacobi guess (on a tiled level: not yet formed). The coarse error equation is treated by one V
   // cycle (V), two W cycles in a row (W) or an F cycle and then a V cycle (F); the
   // second recursion continues from the first one's coarse iterate.
-  hipError_t vcycle(int l, bool pre_done = false, int shape = -1) {
+  hipError_t vcycle(int l, bool pre_done = false, int shape = -1, bool from_guess = false) {
     if (shape < 0) shape = p->cycle;
     if (l == ctx->nlevels - 1) return coarse(l);
-    hipError_t e = pre_done ? hipSuccess : pre_smooth(l);
-    if (e == hipSuccess) e = restrict_residual(l);
-    if (e == hipSuccess) e = vcycle(l + 1, false, shape == PM_CYCLE_V ? PM_CYCLE_V : shape);
+    hipError_t e = hipSuccess;
+    if (tiled(l)) {
+      if (!pre_done) e = tile_down(l, p->pre, true, from_guess);
+    } else {
+      if (!pre_done) e = pre_smooth(l);
+      if (e == hipSuccess) e = restrict_residual(l);
+    }
+    if (e == hipSuccess) e = vcycle(l + 1, false, shape == PM_CYCLE_V ? PM_CYCLE_V : shape, true);
     if (e == hipSuccess && shape != PM_CYCLE_V)
       e = vcycle(l + 1, false, shape == PM_CYCLE_W ? PM_CYCLE_W : PM_CYCLE_V);
     if (e == hipSuccess) e = correct_and_post_smooth(l);
@@ -614,23 +796,13 @@ int pm_mg_setup(pm_ctx *ctx) {
       return PM_ERR_NOMEM;
     ctx->lev[ctx->nlevels++] = L;
   }
-  if ((int64_t)n * n * n > kCoarseMax) return PM_ERR_SHAPE;
-  // residual scratch of the two-pass restriction (levels that do not stream)
+  if (n > pm_coarse::kMaxN) return PM_ERR_SHAPE;
+  // second iterate buffers of the out-of-place kernels (not the coarsest level), or, for a
+  // reference context, the residual scratch of its two-pass restriction
   for (int l = 0; l + 1 < ctx->nlevels; ++l) {
     const int m = ctx->lev[l].n;
-    const bool streams = m >= PM_STREAM_MIN_N && !(ctx->flags & PM_CREATE_REFERENCE_KERNELS) &&
-                         smooth_stream_blocks(m) <= RED_PARTIAL_CAP;
-    if (streams) continue;
-    if (hipMalloc(&ctx->lev[l].res, sizeof(float) * (size_t)m * m * m) != hipSuccess)
-      return PM_ERR_NOMEM;
-  }
-  // ping-pong buffers for the streaming levels (not the coarsest)
-  for (int l = 0; l + 1 < ctx->nlevels; ++l) {
-    const int m = ctx->lev[l].n;
-    if (m < PM_STREAM_MIN_N || (ctx->flags & PM_CREATE_REFERENCE_KERNELS)) continue;
-    if (smooth_stream_blocks(m) > RED_PARTIAL_CAP) continue;
-    if (hipMalloc(&ctx->lev[l].alt, sizeof(float) * (size_t)m * m * m) != hipSuccess)
-      return PM_ERR_NOMEM;
+    float **buf = ctx->flags & PM_CREATE_REFERENCE_KERNELS ? &ctx->lev[l].res : &ctx->lev[l].alt;
+    if (hipMalloc(buf, sizeof(float) * (size_t)m * m * m) != hipSuccess) return PM_ERR_NOMEM;
   }
   return PM_OK;
 }
@@ -647,12 +819,20 @@ int pm_mg_solve(pm_ctx *ctx, const float *rho, float coef, float *phi, const pm_
     sv.cur[l] = l == 0 ? phi : ctx->lev[l].u;
     sv.alt[l] = ctx->lev[l].alt;
   }
-  const bool fused_norm = sv.streaming(0) && p->pre > 0 && ctx->nlevels > 1;
+  const bool tiled = sv.tiled(0);
+  const bool fused_norm = tiled || (sv.streaming(0) && p->pre > 0);
+  // the norm pass of a tiled finest level also restricts, unless sweeps are left to do or
+  // the alpha rule is going to use the coarse level's arrays
+  const bool restrict_now = p->pre <= 2 && !(p->alpha > 0.0f);
   if (p->alpha > 0.0f && p->fixed_cycles <= 0 && ctx->nlevels < 2)
     return pm_fail(ctx, PM_ERR_ARG, "alpha needs a coarser multigrid level (n > 16)");
-  // with the fused norm, the tolerance loop's first pass reads the warm start rescaled
+  // with the fused norm, the tolerance loop's first pass reads the warm start rescaled; a
+  // tiled finest level forms the Jacobi guess in its first pass (the alpha rule reads it)
   float uscale = 1.0f;
-  if (p->guess == PM_GUESS_JACOBI)
+  bool from_guess = false;
+  if (p->guess == PM_GUESS_JACOBI && tiled && !(p->alpha > 0.0f))
+    from_guess = true;
+  else if (p->guess == PM_GUESS_JACOBI)
     k_jacobi_guess<<<blocks_for(count, kThreads), kThreads, 0, s>>>(phi, rho, coef, ctx->mean_f,
                                                                      count, sv.h2(0));
   else if (warm_scale != 1.0f && fused_norm && p->fixed_cycles <= 0)
@@ -664,7 +844,8 @@ int pm_mg_solve(pm_ctx *ctx, const float *rho, float coef, float *phi, const pm_
   int status = PM_OK;
   int cycles = 0;
   if (p->fixed_cycles > 0) {
-    for (int c = 0; c < p->fixed_cycles; ++c) PM_HIP(ctx, sv.vcycle(0));
+    for (int c = 0; c < p->fixed_cycles; ++c)
+      PM_HIP(ctx, sv.vcycle(0, false, -1, from_guess && c == 0));
     cycles = p->fixed_cycles;
   } else {
     double rel[64];
@@ -674,9 +855,11 @@ int pm_mg_solve(pm_ctx *ctx, const float *rho, float coef, float *phi, const pm_
       // residual norm of the current iterate: fused into the next pre-smoothing
       // pass when streaming (its output is used only if another cycle is needed)
       if (fused_norm) {
-        const int64_t nb = smooth_stream_blocks(n);
-        PM_HIP(ctx, sv.stream_sweeps(0, 0, std::min(p->pre, 2), ctx->red_partial,
-                                     cycles == 0 ? uscale : 1.0f));
+        const int64_t nb = tiled ? (int64_t)norm_blocks(n) : smooth_stream_blocks(n);
+        const float us = cycles == 0 ? uscale : 1.0f;
+        if (tiled) PM_HIP(ctx, sv.tile_down(0, std::min(p->pre, 2), restrict_now,
+                                            from_guess && cycles == 0, us, ctx->red_partial));
+        else PM_HIP(ctx, sv.stream_sweeps(0, 0, std::min(p->pre, 2), ctx->red_partial, us));
         k_triple_final<<<1, RED_THREADS, 0, s>>>(ctx->red_partial, (int)nb, ctx->red_result,
                                                   count, ctx->mean_f + 1);
       } else {
@@ -726,7 +909,11 @@ int pm_mg_solve(pm_ctx *ctx, const float *rho, float coef, float *phi, const pm_
       }
       if (fused_norm) {
         // finish the cycle whose pre-smoothing already ran (remaining pre sweeps first)
-        if (p->pre > 2) PM_HIP(ctx, sv.stream_sweeps(0, 0, p->pre - 2, nullptr));
+        if (tiled) {
+          if (!restrict_now) PM_HIP(ctx, sv.tile_down(0, std::max(p->pre - 2, 0), true));
+        } else if (p->pre > 2) {
+          PM_HIP(ctx, sv.stream_sweeps(0, 0, p->pre - 2, nullptr));
+        }
         PM_HIP(ctx, sv.vcycle(0, true));
       } else {
         PM_HIP(ctx, sv.vcycle(0));
@@ -736,25 +923,20 @@ int pm_mg_solve(pm_ctx *ctx, const float *rho, float coef, float *phi, const pm_
     if (stats)
       for (int c = 0; c <= cycles; ++c) stats->relres[c] = rel[c];
   }
-  if (have_sum) {
-    // copy (when the iterate is in the other buffer) and remove the mean (gauge) in one
-    // pass
-    const bool vec = count % 4 == 0 && reinterpret_cast<uintptr_t>(sv.cur[0]) % 16 == 0 &&
-                     reinterpret_cast<uintptr_t>(phi) % 16 == 0;
-    if (vec)
-      k_finish_phi4<<<blocks_for(count / 4, kThreads), kThreads, 0, s>>>(
-          reinterpret_cast<const float4 *>(sv.cur[0]), reinterpret_cast<float4 *>(phi), count / 4,
-          1.0f, ctx->mean_f + 1);
-    else
-      k_finish_phi<<<blocks_for(count, kThreads), kThreads, 0, s>>>(sv.cur[0], phi, count,
-                                                                     1.0f, ctx->mean_f + 1);
-  } else {
-    if (sv.cur[0] != phi)
-      PM_HIP(ctx, hipMemcpyAsync(phi, sv.cur[0], sizeof(float) * count, hipMemcpyDeviceToDevice, s));
-    // remove the mean of phi (gauge)
-    PM_HIP(ctx, launch_sum_moments(phi, count, ctx->red_partial, ctx->red_result, ctx->mean_f + 1, s));
-    k_subtract_mean<<<blocks_for(count, kThreads), kThreads, 0, s>>>(phi, count, ctx->mean_f + 1);
-  }
+  // the mean of the final iterate (gauge) is removed as the iterate, in whichever buffer
+  // the last pass left it, is copied to phi; the norm pass has summed it already
+  if (!have_sum)
+    PM_HIP(ctx, launch_sum_moments(sv.cur[0], count, ctx->red_partial, ctx->red_result,
+                                   ctx->mean_f + 1, s));
+  const bool vec = count % 4 == 0 && reinterpret_cast<uintptr_t>(sv.cur[0]) % 16 == 0 &&
+                   reinterpret_cast<uintptr_t>(phi) % 16 == 0;
+  if (vec)
+    k_finish_phi4<<<blocks_for(count / 4, kThreads), kThreads, 0, s>>>(
+        reinterpret_cast<const float4 *>(sv.cur[0]), reinterpret_cast<float4 *>(phi), count / 4,
+        1.0f, ctx->mean_f + 1);
+  else
+    k_finish_phi<<<blocks_for(count, kThreads), kThreads, 0, s>>>(sv.cur[0], phi, count, 1.0f,
+                                                                   ctx->mean_f + 1);
   PM_HIP(ctx, hipGetLastError());
   if (stats) {
     stats->cycles = cycles;
