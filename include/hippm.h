@@ -587,10 +587,10 @@ int pm_batch_kdk(pm_batch *batch, float *pos, float *vel, float *acc, float *phi
 int pm_graph_capture_step(pm_batch *batch, float *pos, float *vel, float *acc, float *phi,
                           const pm_step_params *params, pm_stream stream);
 
-/* Autotuner for the stencil tile shapes of the batch (rows of the plane each
- * thread owns in the red-black smoother and in the gradient: 1, 2 or 4): times
- * every usable shape on the batch's own finest grids with HIP events and keeps
- * the fastest; choice (host, [2], may be NULL) receives the smoother and
+/* Autotuner for the stencil tile shapes of the batch (for the multigrid the coarse
+ * planes of a tile, for the gradient the rows of the plane each thread owns: 1, 2
+ * or 4): times every usable shape on the batch's own finest grids with HIP events
+ * and keeps the fastest; without it a rule on the number of tiles chooses; choice (host, [2], may be NULL) receives the smoother and
  * gradient picks. pos supplies a density; phi is used as scratch and
  * overwritten. Drops a captured step graph (capture again afterwards). */
 int pm_tune(pm_batch *batch, float *pos, float *phi, const pm_step_params *params, int *choice,

@@ -17,6 +17,7 @@
 #include "coarse_solve.h"
 #include "deposit_chunk.h"
 #include "internal.h"
+#include "mg_tile.h"
 
 namespace {
 
@@ -250,33 +251,6 @@ __global__ __launch_bounds__(kThreads) void kb_fill(float *__restrict__ x, int64
   for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < count; t += stride) x[t] = v;
 }
 
-// u *= warm factor of the step (growth rescaling of the previous potential)
-__global__ __launch_bounds__(kThreads) void kb_scale(float *__restrict__ x, int64_t count,
-                                                     const StepDev *__restrict__ steps,
-                                                     const int *__restrict__ ctr) {
-  const float s = steps[*ctr].warm;
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < count; t += stride) x[t] *= s;
-}
-
-// Per-item FP64 partial sums of a level-0 field (fixed order: deterministic).
-__global__ __launch_bounds__(kThreads) void kb_sum_partial(const float *__restrict__ x,
-                                                           const int2 *__restrict__ items,
-                                                           int nitems,
-                                                           const BoxDev *__restrict__ boxes,
-                                                           double *__restrict__ partial) {
-  __shared__ double lds[kThreads / 64];
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const int2 item = items[it];
-    const BoxDev &bx = boxes[item.x];
-    const int64_t count = (int64_t)bx.n * bx.n * bx.n;
-    const int64_t c = (int64_t)item.y * kThreads + threadIdx.x;
-    const double v = c < count ? (double)x[bx.c0 + c] : 0.0;
-    const double s = block_sum<kThreads>(v, lds);
-    if (threadIdx.x == 0) partial[it] = s;
-  }
-}
-
 // mean[b] = sum of the box's partials / n^3 (one workgroup per box)
 __global__ __launch_bounds__(kThreads) void kb_sum_final(const double *__restrict__ partial,
                                                          const int *__restrict__ range,
@@ -293,16 +267,40 @@ __global__ __launch_bounds__(kThreads) void kb_sum_final(const double *__restric
   }
 }
 
-__global__ __launch_bounds__(kThreads) void kb_subtract_mean(float *__restrict__ x,
-                                                             const int2 *__restrict__ items,
-                                                             int nitems,
-                                                             const BoxDev *__restrict__ boxes,
-                                                             const float *__restrict__ mean) {
+// The level-0 iterate of a box: in the buffer the last pass of its level left it in, or,
+// for a box whose finest level is the coarsest, in phi (solved there).
+__device__ __forceinline__ const float *level0(const BoxDev &bx, const float *cur, const float *phi) {
+  return (bx.nlev == 1 ? phi : cur) + bx.c0;
+}
+
+// Per-item FP64 partial sums of a level-0 field (fixed order: deterministic).
+__global__ __launch_bounds__(kThreads) void kb_sum_partial(const float *cur, const float *phi,
+                                                           const int2 *__restrict__ items,
+                                                           int nitems,
+                                                           const BoxDev *__restrict__ boxes,
+                                                           double *__restrict__ partial) {
+  __shared__ double lds[kThreads / 64];
+  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
+    const int2 item = items[it];
+    const BoxDev &bx = boxes[item.x];
+    const int64_t count = (int64_t)bx.n * bx.n * bx.n;
+    const int64_t c = (int64_t)item.y * kThreads + threadIdx.x;
+    const double v = c < count ? (double)level0(bx, cur, phi)[c] : 0.0;
+    const double s = block_sum<kThreads>(v, lds);
+    if (threadIdx.x == 0) partial[it] = s;
+  }
+}
+
+// phi = iterate - mean (gauge)
+__global__ __launch_bounds__(kThreads) void kb_finish(const float *cur, float *phi,
+                                                      const int2 *__restrict__ items, int nitems,
+                                                      const BoxDev *__restrict__ boxes,
+                                                      const float *__restrict__ mean) {
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int2 item = items[it];
     const BoxDev &bx = boxes[item.x];
     const int64_t c = (int64_t)item.y * kThreads + threadIdx.x;
-    if (c < (int64_t)bx.n * bx.n * bx.n) x[bx.c0 + c] -= mean[item.x];
+    if (c < (int64_t)bx.n * bx.n * bx.n) phi[bx.c0 + c] = level0(bx, cur, phi)[c] - mean[item.x];
   }
 }
 
@@ -343,64 +341,6 @@ struct Arenas {
   const int *ctr;
 };
 
-// u = -h^2 scale (f - mean) / 6 on level 0 (first solve of a run)
-__global__ __launch_bounds__(kThreads) void kb_jacobi0(Arenas A, const int2 *__restrict__ items,
-                                                       int nitems,
-                                                       const BoxDev *__restrict__ boxes) {
-  const float coef = A.steps[*A.ctr].coef;
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const int2 item = items[it];
-    const BoxDev &bx = boxes[item.x];
-    const LevelView v = level_view(bx, 0, A.phi, A.rho, A.lu, A.lf, coef, A.rmean, item.x);
-    const int64_t c = (int64_t)item.y * kThreads + threadIdx.x;
-    if (c >= (int64_t)v.n * v.n * v.n) continue;
-    const float h = 1.0f / (float)v.n;
-    v.u[c] = (-(h * h) / 6.0f) * (v.scale * (v.f[c] - v.mean));
-  }
-}
-
-// One colour of a red-black Gauss-Seidel sweep on level l of every listed box.
-// Tile shape (chosen by the tuner): a thread owns one k-position of its colour in CPT
-// consecutive rows j of one plane i (CPT divides n), so a wavefront still reads
-// contiguous runs along k.
-template <int CPT>
-__global__ __launch_bounds__(kThreads) void kb_rbgs_half(Arenas A, const int2 *__restrict__ items,
-                                                         int nitems,
-                                                         const BoxDev *__restrict__ boxes, int l,
-                                                         float omega, int colour) {
-  const float coef = A.steps[*A.ctr].coef;
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const int2 item = items[it];
-    const BoxDev &bx = boxes[item.x];
-    const LevelView v = level_view(bx, l, A.phi, A.rho, A.lu, A.lf, coef, A.rmean, item.x);
-    const int n = v.n, half = n >> 1;
-    const float h = 1.0f / (float)n, h2 = h * h;
-    const size_t nn = (size_t)n * n;
-    const unsigned tid = (unsigned)item.y * kThreads + threadIdx.x;
-    const unsigned rg = tid / (unsigned)half;  // row group: CPT rows j of plane i
-    const int k2 = (int)(tid - rg * (unsigned)half);
-    const unsigned groups = (unsigned)(n / CPT);
-    if (rg >= (unsigned)n * groups) continue;
-    const int i = (int)(rg / groups), j0 = (int)(rg - (unsigned)i * groups) * CPT;
-    const size_t ci = (size_t)i * nn;
-    const size_t cip = (size_t)wrap_index(i + 1, n) * nn, cim = (size_t)wrap_index(i - 1, n) * nn;
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-      const int j = j0 + q;
-      const int k = 2 * k2 + ((i + j + colour) & 1);
-      const size_t cj = (size_t)j * n;
-      const size_t c = ci + cj + k;
-      const float fv = v.scale * (v.f[c] - v.mean);
-      const float nb = v.u[cip + cj + k] + v.u[cim + cj + k] +
-                       v.u[ci + (size_t)wrap_index(j + 1, n) * n + k] +
-                       v.u[ci + (size_t)wrap_index(j - 1, n) * n + k] +
-                       v.u[ci + cj + wrap_index(k + 1, n)] + v.u[ci + cj + wrap_index(k - 1, n)];
-      const float gs = (nb - h2 * fv) * (1.0f / 6.0f);
-      v.u[c] = (omega == 1.0f) ? gs : fmaf(omega, gs - v.u[c], v.u[c]);
-    }
-  }
-}
-
 __device__ __forceinline__ float residual_at(const LevelView &v, int i, int j, int k,
                                              float inv_h2) {
   const int n = v.n;
@@ -424,130 +364,67 @@ __device__ __forceinline__ void decode3(unsigned t, unsigned n, int &i, int &j, 
   j = (int)(r - (unsigned)i * n);
 }
 
-// r = f - L u on level l of every box that has a level l+1, into a scratch arena (the
-// force-grid arena, idle during the solve) at the box's level-0 offset.
-__global__ __launch_bounds__(kThreads) void kb_residual(Arenas A, const int2 *__restrict__ items,
-                                                        int nitems,
-                                                        const BoxDev *__restrict__ boxes, int l,
-                                                        float *__restrict__ rbuf) {
-  const float coef = A.steps[*A.ctr].coef;
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const int2 item = items[it];
-    const BoxDev &bx = boxes[item.x];
-    const LevelView v = level_view(bx, l, A.phi, A.rho, A.lu, A.lf, coef, A.rmean, item.x);
-    const unsigned n = (unsigned)v.n;
-    const unsigned t = (unsigned)item.y * kThreads + threadIdx.x;
-    if (t >= n * n * n) continue;
-    int i, j, k;
-    decode3(t, n, i, j, k);
-    rbuf[bx.c0 + t] = residual_at(v, i, j, k, (float)n * (float)n);
-  }
+// The multigrid passes of a level (mg_tile.h), one tile per workgroup: item = (box, tile).
+// One V(2,2) cycle of 48 boxes of 32^3 to 128^3 (31.8 M cells): 695 us, with a launch per
+// half-sweep, residual, restriction and prolongation 1250 us (each of those a pass over
+// all the boxes' grids).
+// The two iterate buffers of a level alternate (uin, uout); a box's offset in them is its
+// level-0 or its level offset.
+struct TilePass {
+  const float *uin;
+  float *uout;
+  const float *ec;     // up: iterates of level l + 1 (boxes with a coarser level than it)
+  float *fc;           // down: right-hand sides of level l + 1 (NULL: no restriction)
+  int l, hs;
+  bool guess, warm;    // start from the Jacobi guess; scale the input by the step's warm factor
+  float omega;
+};
+
+template <class S>
+__device__ __forceinline__ pm_tile::Level tile_item(const Arenas &A, const TilePass &t, const BoxDev &bx,
+                                                    const int2 item, int &i0, int &j0, int &k0) {
+  const StepDev st = A.steps[*A.ctr];
+  const int64_t off = t.l == 0 ? bx.c0 : bx.lo[t.l];
+  const int n = bx.n >> t.l;
+  const float h = 1.0f / (float)n, h2 = h * h;
+  const unsigned tk = (unsigned)pm_tile::tiles_of(n, S::TK), tj = (unsigned)pm_tile::tiles_of(n, S::TJ);
+  const unsigned b = (unsigned)item.y, q = b / tk;
+  k0 = (int)(b - q * tk) * S::TK;
+  j0 = (int)(q % tj) * S::TJ;
+  i0 = (int)(q / tj) * S::TI;
+  return pm_tile::Level{t.guess ? nullptr : t.uin + off, t.uout + off,
+                        (t.l == 0 ? A.rho : (const float *)A.lf) + off,
+                        t.l == 0 ? st.coef : 1.0f, t.l == 0 ? A.rmean[item.x] : 0.0f,
+                        t.warm ? st.warm : 1.0f, -h2 / 6.0f, n, h2, (float)n * (float)n, t.omega};
 }
 
-// Restriction of the level-l residual to level l+1 (full weighting (1,3,3,1)/8 per
-// axis, or the 8-child average), with the coarse starting guess -H^2 f_H / 6.
-template <int KIND>
-__global__ __launch_bounds__(kThreads) void kb_restrict(Arenas A, const int2 *__restrict__ items,
-                                                        int nitems,
-                                                        const BoxDev *__restrict__ boxes, int l,
-                                                        const float *__restrict__ rbuf) {
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const int2 item = items[it];
-    const BoxDev &bx = boxes[item.x];
-    const int n = bx.n >> l;
-    const unsigned nc = (unsigned)n >> 1;
-    const unsigned t = (unsigned)item.y * kThreads + threadIdx.x;
-    if (t >= nc * nc * nc) continue;
-    int I, J, K;
-    decode3(t, nc, I, J, K);
-    const float *r = rbuf + bx.c0;
-    const size_t nn = (size_t)n * n;
-    float acc = 0.0f;
-    if constexpr (KIND == PM_RESTRICT_FW) {
-      const float w[4] = {1.0f, 3.0f, 3.0f, 1.0f};
-      int kk[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) kk[c] = wrap_index(2 * K - 1 + c, n);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const size_t ri = (size_t)wrap_index(2 * I - 1 + a, n) * nn;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const size_t rj = ri + (size_t)wrap_index(2 * J - 1 + b, n) * n;
-          const float wab = w[a] * w[b];
-          const float row = fmaf(w[0], r[rj + kk[0]], fmaf(w[1], r[rj + kk[1]],
-                                 fmaf(w[2], r[rj + kk[2]], w[3] * r[rj + kk[3]])));
-          acc = fmaf(wab, row, acc);
-        }
-      }
-      acc *= (1.0f / 512.0f);
-    } else {
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int c = 0; c < 2; ++c)
-            acc += r[(size_t)(2 * I + a) * nn + (size_t)(2 * J + b) * n + (2 * K + c)];
-      acc *= 0.125f;
-    }
-    const float H = 1.0f / (float)nc;
-    A.lf[bx.lo[l + 1] + t] = acc;
-    A.lu[bx.lo[l + 1] + t] = (-(H * H) / 6.0f) * acc;
-  }
+template <int TI, int TJ, int TK, int KIND, bool OM1>
+__global__ __launch_bounds__((pm_tile::Down<TI, TJ, TK>::NT)) void kb_tile_down(
+    Arenas A, TilePass t, const int2 *__restrict__ items, const BoxDev *__restrict__ boxes) {
+  using S = pm_tile::Down<TI, TJ, TK>;
+  __shared__ __align__(16) float lds[S::LDS];
+  const int2 item = items[xcd_block(blockIdx.x, gridDim.x)];
+  const BoxDev &bx = boxes[item.x];
+  int i0, j0, k0;
+  const pm_tile::Level a = tile_item<S>(A, t, bx, item, i0, j0, k0);
+  double sum[3];
+  pm_tile::tile_down<TI, TJ, TK, KIND, OM1, false>(a, i0, j0, k0, t.hs,
+                                                   t.fc ? t.fc + bx.lo[t.l + 1] : nullptr, lds, sum);
 }
 
-// u_l += P u_{l+1} (trilinear: 3/4 nearest coarse centre, 1/4 the next, per axis);
-// one thread per coarse cell reads its 27 coarse neighbours once and updates its 8
-// fine children (k-pairs as float2)
-__global__ __launch_bounds__(kThreads) void kb_prolong_add(Arenas A, const int2 *__restrict__ items,
-                                                           int nitems,
-                                                           const BoxDev *__restrict__ boxes,
-                                                           int l) {
-  const float near = 0.75f, far = 0.25f;
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const int2 item = items[it];
-    const BoxDev &bx = boxes[item.x];
-    const int n = bx.n >> l, c = n >> 1;
-    const unsigned t = (unsigned)item.y * kThreads + threadIdx.x;
-    if (t >= (unsigned)c * c * c) continue;
-    float *u = l == 0 ? A.phi + bx.c0 : A.lu + bx.lo[l];
-    const float *vc = A.lu + bx.lo[l + 1];
-    int I, J, K;
-    decode3(t, (unsigned)c, I, J, K);
-    const int ix[3] = {wrap_index(I - 1, c), I, wrap_index(I + 1, c)};
-    const int jx[3] = {wrap_index(J - 1, c), J, wrap_index(J + 1, c)};
-    const int kx[3] = {wrap_index(K - 1, c), K, wrap_index(K + 1, c)};
-    float ek[3][3], ok[3][3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        const float *row = vc + ((size_t)ix[a] * c + jx[b]) * c;
-        const float vm = row[kx[0]], v0 = row[kx[1]], vp = row[kx[2]];
-        ek[a][b] = near * v0 + far * vm;
-        ok[a][b] = near * v0 + far * vp;
-      }
-    const size_t nn = (size_t)n * n;
-#pragma unroll
-    for (int ai = 0; ai < 2; ++ai) {
-      const int af = ai ? 2 : 0;
-#pragma unroll
-      for (int bj = 0; bj < 2; ++bj) {
-        const int bf = bj ? 2 : 0;
-        const float se = near * (near * ek[1][1] + far * ek[1][bf]) +
-                         far * (near * ek[af][1] + far * ek[af][bf]);
-        const float so = near * (near * ok[1][1] + far * ok[1][bf]) +
-                         far * (near * ok[af][1] + far * ok[af][bf]);
-        float2 *dst = reinterpret_cast<float2 *>(u + (size_t)(2 * I + ai) * nn +
-                                                 (size_t)(2 * J + bj) * n + 2 * K);
-        float2 cur = *dst;
-        cur.x += se;
-        cur.y += so;
-        *dst = cur;
-      }
-    }
-  }
+template <int TI, int TJ, int TK, bool OM1>
+__global__ __launch_bounds__((pm_tile::Up<TI, TJ, TK>::NT)) void kb_tile_up(
+    Arenas A, TilePass t, const int2 *__restrict__ items, const BoxDev *__restrict__ boxes) {
+  using S = pm_tile::Up<TI, TJ, TK>;
+  __shared__ __align__(16) float lds[S::LDS];
+  __shared__ float raw[S::RAW];
+  const int2 item = items[xcd_block(blockIdx.x, gridDim.x)];
+  const BoxDev &bx = boxes[item.x];
+  int i0, j0, k0;
+  const pm_tile::Level a = tile_item<S>(A, t, bx, item, i0, j0, k0);
+  // the coarse correction: the coarsest level's solution lies in lu itself
+  const float *ec = t.ec ? (bx.nlev - 1 == t.l + 1 ? A.lu : t.ec) + bx.lo[t.l + 1] : nullptr;
+  pm_tile::tile_up<TI, TJ, TK, OM1>(a, ec, i0, j0, k0, t.hs, lds, raw);
 }
 
 // Coarsest level of every box, one workgroup per box, in LDS (coarse_solve.h).
@@ -563,7 +440,7 @@ __global__ __launch_bounds__(pm_coarse::kThreads) void kb_coarse_solve(
 }
 
 // Per-item partial sums of |f - L u|^2 and |f|^2 on level 0 (convergence records).
-__global__ __launch_bounds__(kThreads) void kb_residual_partial(Arenas A,
+__global__ __launch_bounds__(kThreads) void kb_residual_partial(Arenas A, const float *cur,
                                                                 const int2 *__restrict__ items,
                                                                 int nitems,
                                                                 const BoxDev *__restrict__ boxes,
@@ -573,7 +450,8 @@ __global__ __launch_bounds__(kThreads) void kb_residual_partial(Arenas A,
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int2 item = items[it];
     const BoxDev &bx = boxes[item.x];
-    const LevelView v = level_view(bx, 0, A.phi, A.rho, A.lu, A.lf, coef, A.rmean, item.x);
+    LevelView v = level_view(bx, 0, A.phi, A.rho, A.lu, A.lf, coef, A.rmean, item.x);
+    v.u = const_cast<float *>(level0(bx, cur, A.phi));
     const int n = v.n;
     const unsigned t = (unsigned)item.y * kThreads + threadIdx.x;
     double r2 = 0.0, f2 = 0.0;
@@ -692,9 +570,7 @@ struct pm_batch {
   List part;                        // particle blocks
   List chunks;                      // deposit chunks (lattice blocks or runs of 2048 rows)
   List cells[PM_MAX_LEVELS];        // cell blocks of level l (boxes with nlev > l)
-  List halfc[PM_MAX_LEVELS][3];     // red-black half-sweep blocks of level l, per tile shape
-  List finer[PM_MAX_LEVELS];        // cell blocks of level l for boxes with a level l+1
-  List coarser[PM_MAX_LEVELS];      // cell blocks of level l+1 (restriction targets)
+  List tiles[PM_MAX_LEVELS][3];     // multigrid tiles of level l (boxes with a level l+1), per shape
   List grad[3];                     // gradient blocks per tile shape
   int *range = nullptr;             // [nboxes + 1] item range of each box in cells[0]
   // arenas
@@ -709,10 +585,11 @@ struct pm_batch {
   hipEvent_t steps_copied = nullptr;  // recorded after the last copy out of steps_host
   bool steps_pending = false;
   int *ctr = nullptr;
-  // tuned tile shapes (rows per thread of the stencil kernels); a shape is usable only
-  // when it divides the side of every level it would run on
-  int cpt_smooth = 1, cpt_grad = 1;
-  bool ok_smooth[3] = {true, true, true}, ok_grad[3] = {true, true, true};
+  // tuned tile shapes: coarse planes per multigrid tile on the finest levels (1, 2 or 4; 0:
+  // the rule of tile_shape), and rows per thread of the gradient, which must divide the
+  // side of every box
+  int cpt_smooth = 0, cpt_grad = 1;
+  bool ok_grad[3] = {true, true, true};
   // captured step graph
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -746,6 +623,68 @@ int levels_of(int n) {
   return l;
 }
 
+// Multigrid tile shapes (cells along i, j, k), by their coarse planes per tile (1, 2, 4).
+struct TileShape {
+  int ti, tj, tk;
+};
+constexpr TileShape kTileShapes[3] = {{2, 4, 16}, {4, 8, 32}, {8, 16, 32}};
+#define PM_BATCH_SHAPES(si, CALL)     \
+  do {                                \
+    if ((si) == 0) CALL(2, 4, 16);    \
+    else if ((si) == 1) CALL(4, 8, 32); \
+    else CALL(8, 16, 32);             \
+  } while (0)
+
+// Shape index of level l: the larger tiles recompute less halo, so the largest shape that
+// still gives half the compute units one. Measured, us per V(2,2) cycle: 32 boxes of 32^3
+// (256 large tiles) 29 with 8 x 16 x 32 tiles, 41 with 4 x 8 x 32; 4 boxes of 32^3 (32 and
+// 128 tiles) 23, 20 and, with 2 x 4 x 16 tiles, 23. Level 0 takes the tuner's choice when
+// it has run.
+int tile_shape(const pm_batch *B, int l) {
+  if (l == 0 && B->cpt_smooth) return cpt_index(B->cpt_smooth);
+  if (B->tiles[l][2].count >= 128) return 2;
+  return B->tiles[l][1].count >= 128 ? 1 : 0;
+}
+
+void launch_tile_down(const pm_batch *B, const Arenas &A, const TilePass &t, int si, int kind,
+                      hipStream_t s) {
+  const pm_batch::List &L = B->tiles[t.l][si];
+  if (L.count == 0) return;
+  const bool om1 = t.omega == 1.0f;
+#define PM_KBD(K_, O_, ...)                                                                  \
+  kb_tile_down<__VA_ARGS__, K_, O_><<<L.count, (pm_tile::Down<__VA_ARGS__>::NT), 0, s>>>(    \
+      A, t, B->items + L.off, B->boxes)
+#define PM_KB_DOWN(...)                                                                      \
+  do {                                                                                       \
+    if (kind == PM_RESTRICT_AVG) {                                                           \
+      if (om1) PM_KBD(PM_RESTRICT_AVG, true, __VA_ARGS__);                                   \
+      else PM_KBD(PM_RESTRICT_AVG, false, __VA_ARGS__);                                      \
+    } else {                                                                                 \
+      if (om1) PM_KBD(PM_RESTRICT_FW, true, __VA_ARGS__);                                    \
+      else PM_KBD(PM_RESTRICT_FW, false, __VA_ARGS__);                                       \
+    }                                                                                        \
+  } while (0)
+  PM_BATCH_SHAPES(si, PM_KB_DOWN);
+#undef PM_KB_DOWN
+#undef PM_KBD
+}
+
+void launch_tile_up(const pm_batch *B, const Arenas &A, const TilePass &t, int si, hipStream_t s) {
+  const pm_batch::List &L = B->tiles[t.l][si];
+  if (L.count == 0) return;
+#define PM_KB_UP(...)                                                                           \
+  do {                                                                                          \
+    if (t.omega == 1.0f)                                                                        \
+      kb_tile_up<__VA_ARGS__, true><<<L.count, (pm_tile::Up<__VA_ARGS__>::NT), 0, s>>>(         \
+          A, t, B->items + L.off, B->boxes);                                                    \
+    else                                                                                        \
+      kb_tile_up<__VA_ARGS__, false><<<L.count, (pm_tile::Up<__VA_ARGS__>::NT), 0, s>>>(        \
+          A, t, B->items + L.off, B->boxes);                                                    \
+  } while (0)
+  PM_BATCH_SHAPES(si, PM_KB_UP);
+#undef PM_KB_UP
+}
+
 // all stencil launches of one step, on stream s; first = true for the Jacobi-guess solve
 int enqueue_accel(pm_batch *B, const float *pos, float *acc, float *vel, float *phi,
                   const pm_step_params *p, bool first, bool with_residual, hipStream_t s) {
@@ -762,66 +701,57 @@ int enqueue_accel(pm_batch *B, const float *pos, float *acc, float *vel, float *
   kb_fix_to_rho<<<persist_grid(c0.count), kThreads, 0, s>>>(B->fix, B->rho, B->items + c0.off,
                                                             c0.count, B->boxes, B->partial);
   kb_sum_final<<<B->nboxes, kThreads, 0, s>>>(B->partial, B->range, B->boxes, B->rmean);
-  // multigrid: starting guess, then a fixed number of V-cycles
-  if (first)
-    kb_jacobi0<<<persist_grid(c0.count), kThreads, 0, s>>>(A, B->items + c0.off, c0.count,
-                                                           B->boxes);
-  else
-    kb_scale<<<flat_grid(B->ncell_total), kThreads, 0, s>>>(phi, B->ncell_total, B->steps, B->ctr);
-  const int ci = cpt_index(B->cpt_smooth);
-  auto sweeps = [&](int l, int count, int first_colour) {
-    const pm_batch::List &L = B->halfc[l][ci];
-    for (int sw = 0; sw < count; ++sw)
-      for (int c = 0; c < 2; ++c) {
-        const int colour = c ^ first_colour;
-        if (B->cpt_smooth == 1)
-          kb_rbgs_half<1><<<persist_grid(L.count), kThreads, 0, s>>>(
-              A, B->items + L.off, L.count, B->boxes, l, p->mg.omega, colour);
-        else if (B->cpt_smooth == 2)
-          kb_rbgs_half<2><<<persist_grid(L.count), kThreads, 0, s>>>(
-              A, B->items + L.off, L.count, B->boxes, l, p->mg.omega, colour);
-        else
-          kb_rbgs_half<4><<<persist_grid(L.count), kThreads, 0, s>>>(
-              A, B->items + L.off, L.count, B->boxes, l, p->mg.omega, colour);
-      }
-  };
-  const int cycles = p->mg.fixed_cycles;
-  for (int cyc = 0; cyc < cycles; ++cyc) {
+  // multigrid: a fixed number of V-cycles, each level down (pre-smoothing, residual and
+  // restriction) and up (prolongation and post-smoothing) in passes of at most two sweeps.
+  // The first pass forms the Jacobi guess or scales the warm start; the second iterate
+  // buffers lie in the force-grid arena, idle during the solve.
+  float *cur[PM_MAX_LEVELS], *alt[PM_MAX_LEVELS];
+  for (int l = 0; l < B->maxlev; ++l) {
+    cur[l] = l == 0 ? phi : B->lu;
+    alt[l] = l == 0 ? B->g : B->g + B->ncell_total;
+  }
+  const pm_mg_params &mg = p->mg;
+  for (int cyc = 0; cyc < mg.fixed_cycles; ++cyc) {
     for (int l = 0; l + 1 < B->maxlev; ++l) {
-      if (B->finer[l].count == 0) break;
-      sweeps(l, p->mg.pre, 0);
-      const pm_batch::List &F = B->finer[l];
-      kb_residual<<<persist_grid(F.count), kThreads, 0, s>>>(A, B->items + F.off, F.count,
-                                                             B->boxes, l, B->g);
-      const pm_batch::List &R = B->coarser[l];
-      if (p->mg.restrict_kind == PM_RESTRICT_AVG)
-        kb_restrict<PM_RESTRICT_AVG><<<persist_grid(R.count), kThreads, 0, s>>>(
-            A, B->items + R.off, R.count, B->boxes, l, B->g);
-      else
-        kb_restrict<PM_RESTRICT_FW><<<persist_grid(R.count), kThreads, 0, s>>>(
-            A, B->items + R.off, R.count, B->boxes, l, B->g);
+      int left = mg.pre;
+      bool fresh = true;
+      do {
+        const int now = std::min(left, 2);
+        left -= now;
+        const bool guess = fresh && (l > 0 || (cyc == 0 && first));
+        const bool warm = fresh && l == 0 && cyc == 0 && !first;
+        launch_tile_down(B, A, TilePass{cur[l], alt[l], nullptr, left == 0 ? B->lf : nullptr, l,
+                                        2 * now, guess, warm, mg.omega},
+                         tile_shape(B, l), mg.restrict_kind, s);
+        std::swap(cur[l], alt[l]);
+        fresh = false;
+      } while (left > 0);
     }
     kb_coarse_solve<<<B->nboxes, pm_coarse::kThreads, 0, s>>>(A, B->boxes);
     for (int l = B->maxlev - 2; l >= 0; --l) {
-      const pm_batch::List &F = B->finer[l];
-      if (F.count == 0) continue;
-      const pm_batch::List &Cl = B->coarser[l];  // one thread per coarse cell
-      kb_prolong_add<<<persist_grid(Cl.count), kThreads, 0, s>>>(A, B->items + Cl.off, Cl.count,
-                                                                 B->boxes, l);
-      sweeps(l, p->mg.post, 1);
+      int left = mg.post;
+      const float *ec = cur[l + 1];
+      do {
+        const int now = std::min(left, 2);
+        left -= now;
+        launch_tile_up(B, A, TilePass{cur[l], alt[l], ec, nullptr, l, 2 * now, false, false, mg.omega},
+                       tile_shape(B, l), s);
+        std::swap(cur[l], alt[l]);
+        ec = nullptr;
+      } while (left > 0);
     }
   }
   if (with_residual) {
-    kb_residual_partial<<<persist_grid(c0.count), kThreads, 0, s>>>(A, B->items + c0.off, c0.count,
-                                                                    B->boxes, B->partial);
+    kb_residual_partial<<<persist_grid(c0.count), kThreads, 0, s>>>(
+        A, cur[0], B->items + c0.off, c0.count, B->boxes, B->partial);
     kb_residual_final<<<B->nboxes, kThreads, 0, s>>>(B->partial, B->range, B->relres);
   }
   // zero-mean potential (gauge), gradient, interpolation (+ kick)
-  kb_sum_partial<<<persist_grid(c0.count), kThreads, 0, s>>>(phi, B->items + c0.off, c0.count,
-                                                             B->boxes, B->partial);
+  kb_sum_partial<<<persist_grid(c0.count), kThreads, 0, s>>>(cur[0], phi, B->items + c0.off,
+                                                             c0.count, B->boxes, B->partial);
   kb_sum_final<<<B->nboxes, kThreads, 0, s>>>(B->partial, B->range, B->boxes, B->pmean);
-  kb_subtract_mean<<<persist_grid(c0.count), kThreads, 0, s>>>(phi, B->items + c0.off, c0.count,
-                                                               B->boxes, B->pmean);
+  kb_finish<<<persist_grid(c0.count), kThreads, 0, s>>>(cur[0], phi, B->items + c0.off, c0.count,
+                                                        B->boxes, B->pmean);
   const pm_batch::List &G = B->grad[cpt_index(B->cpt_grad)];
   if (B->cpt_grad == 1)
     kb_gradient<1><<<persist_grid(G.count), kThreads, 0, s>>>(phi, B->items + G.off, G.count,
@@ -998,34 +928,19 @@ int pm_batch_create(pm_batch **out, int nboxes, const int *n, const int64_t *np,
     }
     if (l == 0) range[nboxes] = B->cells[0].count;
   }
-  for (int l = 0; l + 1 < B->maxlev; ++l) {
-    const int cpts[3] = {1, 2, 4};
-    for (int ci = 0; ci < 3; ++ci) {
-      B->halfc[l][ci].off = (int64_t)B->items_h.size();
+  for (int l = 0; l + 1 < B->maxlev; ++l)
+    for (int si = 0; si < 3; ++si) {
+      const TileShape &t = kTileShapes[si];
+      B->tiles[l][si].off = (int64_t)B->items_h.size();
       for (int b = 0; b < nboxes; ++b) {
         if (B->boxes_h[b].nlev <= l + 1) continue;
-        const int64_t m = n[b] >> l;
-        if (m % cpts[ci]) {
-          B->ok_smooth[ci] = false;  // shape not usable for this batch (tuner skips it)
-          continue;
-        }
-        append_blocks(B, B->halfc[l][ci], b, m * (m / cpts[ci]) * (m / 2));
+        const int m = n[b] >> l;
+        const int nb = pm_tile::tiles_of(m, t.ti) * pm_tile::tiles_of(m, t.tj) *
+                       pm_tile::tiles_of(m, t.tk);
+        for (int k = 0; k < nb; ++k) B->items_h.push_back(int2{b, k});
+        B->tiles[l][si].count += nb;
       }
     }
-    B->finer[l].off = (int64_t)B->items_h.size();
-    B->coarser[l].off = 0;
-    for (int b = 0; b < nboxes; ++b) {
-      if (B->boxes_h[b].nlev <= l + 1) continue;
-      const int64_t m = n[b] >> l;
-      append_blocks(B, B->finer[l], b, m * m * m);
-    }
-    B->coarser[l].off = (int64_t)B->items_h.size();
-    for (int b = 0; b < nboxes; ++b) {
-      if (B->boxes_h[b].nlev <= l + 1) continue;
-      const int64_t m = n[b] >> (l + 1);
-      append_blocks(B, B->coarser[l], b, m * m * m);
-    }
-  }
   {
     const int cpts[3] = {1, 2, 4};
     for (int ci = 0; ci < 3; ++ci) {
@@ -1211,21 +1126,14 @@ int pm_tune(pm_batch *B, float *pos, float *phi, const pm_step_params *params, i
   float best_s = 1e30f, best_g = 1e30f;
   int pick_s = 1, pick_g = 1;
   for (int ci = 0; ci < 3; ++ci) {
-    if (!B->ok_smooth[ci] || !B->ok_grad[ci]) continue;
-    const pm_batch::List &L = B->halfc[0][ci];
     const pm_batch::List &G = B->grad[ci];
     for (int rep = 0; rep < 2; ++rep) {  // first repetition warms caches and code
       BHIP(B, hipEventRecord(e0, s));
-      for (int c = 0; c < 4; ++c) {
-        if (cpts[ci] == 1)
-          kb_rbgs_half<1><<<persist_grid(L.count), kThreads, 0, s>>>(A, B->items + L.off, L.count,
-                                                                     B->boxes, 0, 1.0f, c & 1);
-        else if (cpts[ci] == 2)
-          kb_rbgs_half<2><<<persist_grid(L.count), kThreads, 0, s>>>(A, B->items + L.off, L.count,
-                                                                     B->boxes, 0, 1.0f, c & 1);
-        else
-          kb_rbgs_half<4><<<persist_grid(L.count), kThreads, 0, s>>>(A, B->items + L.off, L.count,
-                                                                     B->boxes, 0, 1.0f, c & 1);
+      if (B->maxlev > 1) {
+        // the two passes of a V-cycle on level 0, into the scratch arenas
+        launch_tile_down(B, A, TilePass{phi, B->g, nullptr, B->lf, 0, 4, false, false, 1.0f}, ci,
+                         params->mg.restrict_kind, s);
+        launch_tile_up(B, A, TilePass{B->g, phi, B->lu, nullptr, 0, 4, false, false, 1.0f}, ci, s);
       }
       BHIP(B, hipEventRecord(e1, s));
       BHIP(B, hipEventSynchronize(e1));
@@ -1235,6 +1143,7 @@ int pm_tune(pm_batch *B, float *pos, float *phi, const pm_step_params *params, i
         best_s = ms;
         pick_s = cpts[ci];
       }
+      if (!B->ok_grad[ci]) continue;
       BHIP(B, hipEventRecord(e0, s));
       for (int c = 0; c < 2; ++c) {
         if (cpts[ci] == 1)

@@ -88,3 +88,34 @@ def test_coarsest_solve_is_exact(lib, n):
     ref = opm.solve_exact7(opm.source(rho.astype(np.float64), 0.1), 1.0 / n)
     assert rel_l2(phi.cpu().numpy(), ref) <= 2e-6
     ctx.close()
+
+
+@pytest.mark.parametrize("sizes", [[32], [12, 18, 20, 36, 80, 16], [64] * 5 + [48, 96], [32] * 40])
+def test_batched_tile_levels_match_single_boxes(lib, sizes):
+    """The batched passes in each of their tile shapes, with sweep counts that leave the
+    iterate in either buffer, against single boxes that run one kernel per half-sweep: the
+    documented bound between the batched and the single-box force, 1e-5."""
+    print(f"batched tile levels {sizes}", flush=True)
+    batch = lib.Batch(sizes, [n ** 3 for n in sizes])
+    rng = np.random.default_rng(len(sizes))
+    pos = []
+    for n in sizes:
+        q = (np.indices((n, n, n)).reshape(3, -1).T + 0.5) / n
+        pos.append(((q + 0.3 / n * rng.standard_normal(q.shape)) % 1.0).astype(np.float32) % 1.0)
+    x = torch.from_numpy(np.concatenate(pos)).cuda()
+    plain = {n: lib.Context(n, n ** 3, lib.PM_CREATE_REFERENCE_KERNELS) for n in set(sizes)}
+    for kw in (dict(), dict(pre=3, post=1), dict(pre=1, post=3, omega=1.2), dict(pre=0, post=0),
+               dict(pre=2, post=1, restrict_kind="avg")):
+        p = lib.default_step_params(fixed_cycles=2, **kw)
+        acc, phi = torch.empty_like(x), torch.zeros(batch.ncell_total, device="cuda")
+        lib.pm_batch_accel(batch, x, acc, phi, 0.1, p)
+        for b in range(0, len(sizes), max(1, len(sizes) // 6)):
+            n = sizes[b]
+            rows, cells = slice(*batch.p_off[b:b + 2]), slice(*batch.c_off[b:b + 2])
+            one, pot = torch.empty_like(x[rows]), torch.zeros((n, n, n), device="cuda")
+            lib.pm_accel(plain[n], x[rows].contiguous(), 0.1, pot, one, params=p)
+            assert rel_l2(phi[cells].cpu().numpy(), pot.reshape(-1).cpu().numpy()) <= 1e-5, (n, kw)
+            assert rel_l2(acc[rows].cpu().numpy(), one.cpu().numpy()) <= 1e-5, (n, kw)
+    batch.close()
+    for ctx in plain.values():
+        ctx.close()
