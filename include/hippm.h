@@ -280,9 +280,8 @@ int pm_solve_fft(pm_ctx *ctx, const float *rho, float coef, int deconv, float *p
  *   PM_FFT_FULL   out = g [n][n][n][3] = -grad phi taken in Fourier space
  *                 (Eq. exact_fullfft_kernel): g_d(k) = i k_d coef rho(k) / (k^2 W^2),
  *                 with k_d = 0 on the Nyquist plane of axis d; deconv as for GREEN.
- * n must be a power of two (8 .. 1024). FULL uses three more spectra of context
- * scratch (one per force component, about 14 bytes per cell in all, allocated on first
- * use). */
+ * n must be a power of two (8 .. 1024). FULL uses two more spectra of context
+ * scratch (about 9 bytes per cell in all, allocated on first use). */
 int pm_solve_fft_kernel(pm_ctx *ctx, const float *rho, float coef, int kernel, int deconv,
                         float *out, pm_stream stream);
 
@@ -590,8 +589,8 @@ int pm_graph_capture_step(pm_batch *batch, float *pos, float *vel, float *acc, f
 /* Autotuner for the stencil tile shapes of the batch (for the multigrid the coarse
  * planes of a tile, for the gradient the rows of the plane each thread owns: 1, 2
  * or 4): times every usable shape on the batch's own finest grids with HIP events
- * and keeps the fastest; without it a rule on the number of tiles chooses; choice (host, [2], may be NULL) receives the smoother and
- * gradient picks. pos supplies a density; phi is used as scratch and
+ * and keeps the fastest; without it a rule on the number of tiles chooses; choice (host,
+ * [2], may be NULL) receives the smoother and gradient picks. pos supplies a density; phi is used as scratch and
  * overwritten. Drops a captured step graph (capture again afterwards). */
 int pm_tune(pm_batch *batch, float *pos, float *phi, const pm_step_params *params, int *choice,
             pm_stream stream);

@@ -7,551 +7,222 @@
 //
 // Layout: the half spectrum is kept as complex float spec[i][j][kc],
 // kc = 0 .. n/2, row pitch P (a multiple of the column-tile width).
-// Five passes over HBM, each a batch of 1D transforms staged in LDS:
+// Five passes over memory, each a batch of 1D transforms in registers (fft_line.h):
 //   A  rows along k, real -> half complex (length-n/2 complex FFT + split)
 //   B  columns along j, forward
 //   C  columns along i: forward, multiply by G, inverse (one kernel)
 //   D  columns along j, inverse
 //   E  rows along k, half complex -> real
-// (FULL_FFT: C stores G F; then per force component the i pass multiplies by -i k_d
-// and inverts into a spectrum of its own, followed by D; one E pass over the three
-// spectra writes whole (x, y, z) cells.)
-// The 1D transforms are Stockham autosort radix-4 (+ one radix-2) stages
-// with twiddles from a table computed in FP64 on the device.
+// FULL_FFT: k_d is constant along the transforms of the other axes, so the force needs two
+// spectra after C (the potential's and the i component's), three after D (the j component
+// branches off the potential's), and E multiplies the k component as it reads it, the
+// three rows of a cell transformed by one group of threads that writes whole (x, y, z)
+// cells.
+//
+// The passes are bound by memory: one solve moves about 40 bytes a cell where 8 must move
+// (a transform needs all of a line, and three axes do not fit a compute unit's LDS).
+// Times are at fft_run.
 #include <cmath>
 
-#include "internal.h"
+#include "fft_line.h"
 
 namespace {
 
-#ifndef PM_FFT_THREADS
-#define PM_FFT_THREADS 256
-#endif
-constexpr int FT = PM_FFT_THREADS;  // threads per block
-constexpr int TL = PM_FFT_TL;       // complex elements held in LDS per block
+using namespace pm_fft;
 
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-  return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+constexpr int kMaxN = 1024;
+
+// the block's sum of nb partial sums over count cells -> the mean (every thread)
+template <int NT>
+__device__ __forceinline__ float mean_of(const double *__restrict__ partial, int nb, double count) {
+  __shared__ double s_mean[NT / 64];
+  double s = 0.0;
+  for (int b = threadIdx.x; b < nb; b += NT) s += partial[b];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+  if ((threadIdx.x & 63) == 0) s_mean[threadIdx.x >> 6] = s;
+  __syncthreads();
+  double t = 0.0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) t += s_mean[w];
+  return (float)(t / count);
 }
-__device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ float2 conjf2(float2 a) { return make_float2(a.x, -a.y); }
 
-template <int R, bool INV>
-__device__ __forceinline__ void butterfly(float2 *v) {
-  if constexpr (R == 2) {
-    const float2 a = v[0], b = v[1];
-    v[0] = cadd(a, b);
-    v[1] = csub(a, b);
+// Where the mean of a real grid comes from: nowhere (it is not subtracted), a device
+// value, or nb partial sums to add up.
+struct Mean {
+  const float *value;
+  const double *partial;
+  int nb;
+};
+
+// Pass A: each row x[0..n) -> X[0..n/2], n = 2 L.
+// The mean of x is subtracted as it is read: the k = 0 mode is dropped by every kernel
+// anyway, and a large mean would otherwise set the scale of the FP32 rounding of every
+// other mode (a density of mean 1 with fluctuations of 0.3 loses about a factor 1 / 0.3 in
+// relative accuracy at 512^3).
+template <int L>
+__global__ __launch_bounds__(256) void k_rows_r2c(const float *__restrict__ x, float2 *__restrict__ spec,
+                                                  int P, const float2 *__restrict__ tw, Mean mean) {
+  using S = Split<L>;
+  using R = RowShape<L>;
+  constexpr int n = 2 * L;
+  __shared__ float2 lds[R::LDS];
+  const int t = threadIdx.x % S::N2, r = threadIdx.x / S::N2;
+  const int64_t row = (int64_t)xcd_block(blockIdx.x, gridDim.x) * R::R + r;
+  const bool live = row < (int64_t)n * n;
+  const float2 *src = reinterpret_cast<const float2 *>(x + (live ? row : 0) * n);
+  float2 v[S::N1], last;
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) v[m] = src[t + S::N2 * m];
+  const float mu = mean.partial ? mean_of<256>(mean.partial, mean.nb, (double)n * n * n)
+                                : (mean.value ? *mean.value : 0.0f);
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) v[m] = make_float2(v[m].x - mu, v[m].y - mu);
+  real_forward<L>(v, last, lds + r * R::PITCH, t, tw);
+  if (!live) return;
+  float2 *dst = spec + row * P;
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) dst[t + S::N2 * m] = v[m];
+  if (t == 0) dst[L] = last;
+}
+
+// Pass E: X[0..n/2] -> x[0..n) (unnormalised: the 1/n^3 is in G). The output element of
+// row r and position m goes to x[(r n + m) stride + comp].
+template <int L>
+__global__ __launch_bounds__(256) void k_rows_c2r(const float2 *__restrict__ spec, float *__restrict__ x,
+                                                  int P, const float2 *__restrict__ tw, int stride,
+                                                  int comp) {
+  using S = Split<L>;
+  using R = RowShape<L>;
+  constexpr int n = 2 * L;
+  __shared__ float2 lds[R::LDS];
+  const int t = threadIdx.x % S::N2, r = threadIdx.x / S::N2;
+  const int64_t row = (int64_t)xcd_block(blockIdx.x, gridDim.x) * R::R + r;
+  const bool live = row < (int64_t)n * n;
+  const float2 *src = spec + (live ? row : 0) * P;
+  float2 v[S::N1];
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) {
+    const int k = t + S::N2 * m;
+    v[m] = real_join(src[k], src[L - k], tw[k]);
+  }
+  rows<L, true>(v, lds + r * R::PITCH, t, tw, 2);
+  if (!live) return;
+  if (stride == 1) {
+    float2 *dst = reinterpret_cast<float2 *>(x + row * n);
+#pragma unroll
+    for (int m = 0; m < S::N1; ++m) dst[t + S::N2 * m] = v[m];
   } else {
-    const float2 a0 = cadd(v[0], v[2]), a1 = csub(v[0], v[2]);
-    const float2 a2 = cadd(v[1], v[3]), d = csub(v[1], v[3]);
-    // forward: d * (-i); inverse: d * (+i)
-    const float2 a3 = INV ? make_float2(-d.y, d.x) : make_float2(d.y, -d.x);
-    v[0] = cadd(a0, a2);
-    v[1] = cadd(a1, a3);
-    v[2] = csub(a0, a2);
-    v[3] = csub(a1, a3);
+#pragma unroll
+    for (int m = 0; m < S::N1; ++m) {
+      float *dst = x + (row * n + 2 * (t + S::N2 * m)) * stride + comp;
+      dst[0] = v[m].x;
+      dst[stride] = v[m].y;
+    }
   }
 }
 
-// One Stockham stage on T independent length-L sequences in LDS.
-// Element (col, idx) lives at col*L + idx (ROWS) or idx*T + col (!ROWS).
-// Butterfly j of sub-transform size Ns: inputs x[j + r L/R], twiddle
-// W_{Ns R}^{r (j mod Ns)}, outputs y[(j/Ns) Ns R + (j mod Ns) + r Ns].
-template <int R, bool INV, bool ROWS>
-__device__ __forceinline__ void fft_stage(float2 *buf, int L, int T, int Ns, int logNs,
-                                          const float2 *__restrict__ tw, int twstep) {
-  constexpr int PER = TL / (R * FT);
-  const int nb = L / R;
-  float2 v[PER][R];
-  int jj[PER], cc[PER];
+// Pass E of FULL_FFT: the three components of a row, from the spectra of the i and j
+// components and of the potential (times -i k_z as it is read), written as whole cells.
+template <int L>
+__global__ __launch_bounds__(256) void k_rows_c2r3(const float2 *__restrict__ sx,
+                                                   const float2 *__restrict__ sy,
+                                                   const float2 *__restrict__ sp,
+                                                   float *__restrict__ x, int P,
+                                                   const float2 *__restrict__ tw,
+                                                   const float *__restrict__ kv) {
+  using S = Split<L>;
+  using R = RowShape<L>;
+  constexpr int n = 2 * L;
+  __shared__ float2 lds[R::LDS];
+  const int t = threadIdx.x % S::N2, r = threadIdx.x / S::N2;
+  const int64_t row = (int64_t)xcd_block(blockIdx.x, gridDim.x) * R::R + r;
+  const bool live = row < (int64_t)n * n;
+  float2 v[3][S::N1];
+  const float2 *src[3] = {sx, sy, sp};
 #pragma unroll
-  for (int b = 0; b < PER; ++b) {
-    const int w = threadIdx.x + b * FT;
-    int j, col;
-    if constexpr (ROWS) {
-      j = w % nb;
-      col = w / nb;
-    } else {
-      col = w % T;
-      j = w / T;
-    }
-    jj[b] = j;
-    cc[b] = col;
+  for (int d = 0; d < 3; ++d) {
+    const float2 *s = src[d] + (live ? row : 0) * P;
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[b][r] = buf[ROWS ? col * L + j + r * nb : (j + r * nb) * T + col];
-  }
-  __syncthreads();
-  const int step = (L / (Ns * R)) * twstep;
-#pragma unroll
-  for (int b = 0; b < PER; ++b) {
-    const int j = jj[b], col = cc[b];
-    const int k = j & (Ns - 1);
-#pragma unroll
-    for (int r = 1; r < R; ++r) {
-      float2 t = tw[r * k * step];
-      if (INV) t.y = -t.y;
-      v[b][r] = cmul(v[b][r], t);
-    }
-    butterfly<R, INV>(v[b]);
-    const int base = ((j >> logNs) << logNs) * R + k;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int o = base + r * Ns;
-      buf[ROWS ? col * L + o : o * T + col] = v[b][r];
-    }
-  }
-  __syncthreads();
-}
-
-template <bool INV, bool ROWS>
-__device__ void lds_fft(float2 *buf, int L, int T, const float2 *__restrict__ tw, int twstep) {
-  int Ns = 1, logNs = 0;
-  while (L / Ns >= 4) {
-    fft_stage<4, INV, ROWS>(buf, L, T, Ns, logNs, tw, twstep);
-    Ns *= 4;
-    logNs += 2;
-  }
-  if (Ns < L) fft_stage<2, INV, ROWS>(buf, L, T, Ns, logNs, tw, twstep);
-}
-
-// Pass A: each row x[0..n) -> X[0..n/2]. z_m = x_{2m} + i x_{2m+1}, Z = FFT_{n/2}(z),
-// E_k = (Z_k + conj Z_{n/2-k}) / 2, O_k = -i (Z_k - conj Z_{n/2-k}) / 2, X_k = E_k + w^k O_k.
-// The mean of x (mean != NULL) is subtracted as it is read: the k = 0 mode is dropped by
-// every kernel anyway, and a large mean would otherwise set the scale of the FP32
-// rounding of every other mode (a density of mean 1 with fluctuations of 0.3 loses
-// about a factor 1 / 0.3 in relative accuracy at 512^3).
-__global__ __launch_bounds__(FT) void k_rows_r2c(const float *__restrict__ x,
-                                                 float2 *__restrict__ spec, int n, int P,
-                                                 const float2 *__restrict__ tw,
-                                                 const float *__restrict__ mean) {
-  __shared__ float2 buf[TL];
-  const int L = n / 2, T = TL / L;
-  const int64_t rows = (int64_t)n * n;
-  const int64_t row0 = (int64_t)blockIdx.x * T;
-  const float mu = mean ? *mean : 0.0f;
-  for (int e = threadIdx.x; e < TL; e += FT) {
-    const int col = e / L, m = e % L;
-    const int64_t row = row0 + col;
-    float2 v = make_float2(0.f, 0.f);
-    if (row < rows) {
-      v = reinterpret_cast<const float2 *>(x + row * n)[m];
-      v.x -= mu;
-      v.y -= mu;
-    }
-    buf[e] = v;
-  }
-  __syncthreads();
-  lds_fft<false, true>(buf, L, T, tw, 2);
-  for (int e = threadIdx.x; e < T * (L + 1); e += FT) {
-    const int col = e / (L + 1), k = e % (L + 1);
-    const int64_t row = row0 + col;
-    if (row >= rows) continue;
-    const float2 zk = buf[col * L + (k == L ? 0 : k)];
-    const float2 zm = conjf2(buf[col * L + (k == 0 ? 0 : L - k)]);
-    const float2 E = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y + zm.y));
-    const float2 D = csub(zk, zm);
-    const float2 O = make_float2(0.5f * D.y, -0.5f * D.x);  // -i D / 2
-    spec[row * P + k] = cadd(E, cmul(tw[k], O));
-  }
-}
-
-// Pass E: X[0..n/2] -> x[0..n). Z~_k = (X_k + conj X_{n/2-k}) + i conj(w^k) (X_k - conj X_{n/2-k}),
-// z = unnormalised inverse FFT_{n/2}(Z~) = n (x_{2m} + i x_{2m+1}); the 1/n^3 is in G.
-// The output element of row r and position m goes to x[(r n + m) * stride + comp]
-// (stride 1: a scalar grid; stride 3: one component of a vector grid). With ncomp > 1
-// the block also takes the same rows of the next spectra (cstride elements apart) into
-// components comp + 1 ..: the components of a cell are written close together in time,
-// so the interleaved grid's cache lines are whole when they leave L2.
-__global__ __launch_bounds__(FT) void k_rows_c2r(const float2 *__restrict__ spec0,
-                                                 float *__restrict__ x, int n, int P,
-                                                 const float2 *__restrict__ tw, int stride,
-                                                 int comp0, int ncomp, int64_t cstride) {
-  __shared__ float2 buf[TL];
-  const int L = n / 2, T = TL / L;
-  const int64_t rows = (int64_t)n * n;
-  const int64_t row0 = (int64_t)blockIdx.x * T;
-  for (int d = 0; d < ncomp; ++d) {
-    const float2 *__restrict__ spec = spec0 + d * cstride;
-    const int comp = comp0 + d;
-    if (d > 0) __syncthreads();  // the previous component's reads of buf are done
-    for (int e = threadIdx.x; e < TL; e += FT) {
-      const int col = e / L, k = e % L;
-      const int64_t row = row0 + col;
-      float2 z = make_float2(0.f, 0.f);
-      if (row < rows) {
-        const float2 xk = spec[row * P + k];
-        const float2 xm = conjf2(spec[row * P + (L - k)]);
-        const float2 Et = cadd(xk, xm);
-        const float2 Ot = cmul(conjf2(tw[k]), csub(xk, xm));
-        z = make_float2(Et.x - Ot.y, Et.y + Ot.x);  // Et + i Ot
+    for (int m = 0; m < S::N1; ++m) {
+      const int k = t + S::N2 * m;
+      float2 a = s[k], b = s[L - k];
+      if (d == 2) {
+        const float ka = kv[k], kb = kv[L - k];
+        a = make_float2(ka * a.y, -ka * a.x);
+        b = make_float2(kb * b.y, -kb * b.x);
       }
-      buf[e] = z;
+      v[d][m] = real_join(a, b, tw[k]);
     }
-    __syncthreads();
-    lds_fft<true, true>(buf, L, T, tw, 2);
-    if (stride == 1) {
-      for (int e = threadIdx.x; e < TL; e += FT) {
-        const int col = e / L, m = e % L;
-        const int64_t row = row0 + col;
-        if (row < rows) reinterpret_cast<float2 *>(x + row * n)[m] = buf[e];
-      }
-    } else {
-      for (int e = threadIdx.x; e < 2 * TL; e += FT) {
-        const int col = e / n, m = e % n;   // m: real position along the row
-        const int64_t row = row0 + col;
-        if (row < rows) {
-          const float2 v = buf[col * L + (m >> 1)];
-          x[(row * n + m) * stride + comp] = (m & 1) ? v.y : v.x;
-        }
-      }
-    }
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) rows<L, true>(v[d], lds + r * R::PITCH, t, tw, 2);
+  if (!live) return;
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) {
+    float2 *dst = reinterpret_cast<float2 *>(x + (row * n + 2 * (t + S::N2 * m)) * 3);
+    dst[0] = make_float2(v[0][m].x, v[1][m].x);
+    dst[1] = make_float2(v[2][m].x, v[0][m].y);
+    dst[2] = make_float2(v[1][m].y, v[2][m].y);
   }
 }
 
-// Passes B, C, D: length-n transforms along j (AXIS 1) or i (AXIS 0) over a tile of
-// T consecutive kc columns, from src to dst (the same buffer, or not). MODE:
-//   0 forward; 1 forward, times G, inverse; 2 inverse; 3 forward, times G;
-//   4 times -i k_d, inverse (d = deriv: 0 the i axis, 1 the j axis, 2 the k axis).
+// Passes B, C, D: transforms along j (AXIS 1) or i (AXIS 0) of tiles of 16 consecutive kc
+// columns, from src to dst (the same buffer, or not). MODE:
+//   0 forward; 1 forward, times G, inverse; 2 inverse;
+//   3 forward, times G, inverse to dst and inverse of -i k_d times it to dst2;
+//   4 inverse to dst and inverse of -i k_d times it to dst2 (d: this axis).
 // G(mx, my, kz) = -scale / ((t0[mx] + t0[my] + t0[kz]) t1[mx] t1[my] t1[kz]) with the
 // per-axis tables t0 = tab[0 .. n), t1 = tab[n .. 2n); k_d = tab[2n + m_d].
-template <int AXIS, int MODE>
-__global__ __launch_bounds__(FT) void k_cols(const float2 *src, float2 *dst, int n, int P,
-                                             const float2 *__restrict__ tw,
-                                             const float *__restrict__ tab, float scale,
-                                             int deriv) {
-  __shared__ float2 buf[TL];
-  const int L = n, T = TL / n;
-  const int kc0 = blockIdx.x * T;
-  const int outer = blockIdx.y;
-  auto gidx = [&](int idx, int col) -> int64_t {
-    if constexpr (AXIS == 1)
-      return ((int64_t)outer * n + idx) * P + kc0 + col;
-    else
-      return ((int64_t)idx * n + outer) * P + kc0 + col;
-  };
-  for (int e = threadIdx.x; e < TL; e += FT) {
-    const int idx = e / T, col = e % T;
-    buf[e] = src[gidx(idx, col)];
-  }
-  __syncthreads();
-  if constexpr (MODE == 0 || MODE == 1 || MODE == 3) lds_fft<false, false>(buf, L, T, tw, 1);
+template <int N, int AXIS, int MODE>
+__global__ __launch_bounds__(ColShape<N>::NT) void k_cols(const float2 *src, float2 *dst, float2 *dst2,
+                                                          int P, const float2 *__restrict__ tw,
+                                                          const float *__restrict__ tab, float scale) {
+  using S = Split<N>;
+  using C = ColShape<N>;
+  __shared__ __align__(16) float lds[C::LDS];
+  const int c = threadIdx.x % kCols, u = threadIdx.x / kCols, t = u % S::N2, o = u / S::N2;
+  const unsigned b = xcd_block(blockIdx.x, gridDim.x);
+  const unsigned tiles = N / 2 / kCols + 1;  // (the last tile holds the Nyquist column alone)
+  const int kz = (int)(b % tiles) * kCols + c, outer = (int)(b / tiles) * C::OUT + o;
+  const bool live = kz <= N / 2;
+  const int base = o * C::LINE + c;
+  const int64_t at = AXIS == 1 ? (int64_t)outer * N * P + kz : (int64_t)outer * P + kz;
+  const int64_t step = AXIS == 1 ? P : (int64_t)N * P;
+  float2 x[S::N1];
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m)
+    x[m] = live ? src[at + (t + S::N2 * m) * step] : make_float2(0.f, 0.f);
+  if constexpr (MODE == 0 || MODE == 1 || MODE == 3) cols<N, false>(x, lds, base, t, tw);
   if constexpr (MODE == 1 || MODE == 3) {
-    const float *t0 = tab, *t1 = tab + n;
+    const float *t0 = tab, *t1 = tab + N;
     const int my = outer;
-    for (int e = threadIdx.x; e < TL; e += FT) {
-      const int mx = e / T, kz = kc0 + e % T;
-      float gval = 0.0f;
-      if (kz <= n / 2 && (mx | my | kz) != 0)
-        gval = -scale / ((t0[mx] + t0[my] + t0[kz]) * (t1[mx] * t1[my] * t1[kz]));
-      const float2 v = buf[e];
-      buf[e] = make_float2(v.x * gval, v.y * gval);
-    }
-    __syncthreads();
-  }
-  if constexpr (MODE == 4) {
-    // AXIS 0 pass: the element (idx = mx, col) sits at (mx, my = outer, kz = kc0 + col)
-    const float *kv = tab + 2 * n;
-    const int my = outer;
-    for (int e = threadIdx.x; e < TL; e += FT) {
-      const int mx = e / T, kz = kc0 + e % T;
-      const float k = kv[deriv == 0 ? mx : (deriv == 1 ? my : min(kz, n - 1))];
-      const float2 v = buf[e];
-      buf[e] = make_float2(k * v.y, -k * v.x);  // (-i k) v
-    }
-    __syncthreads();
-  }
-  if constexpr (MODE == 1 || MODE == 2 || MODE == 4) lds_fft<true, false>(buf, L, T, tw, 1);
-  for (int e = threadIdx.x; e < TL; e += FT) {
-    const int idx = e / T, col = e % T;
-    dst[gidx(idx, col)] = buf[e];
-  }
-}
-
-// Length-256 column passes (n = 256) as a four-step transform in registers: a length-256
-// DFT is 16 DFTs of length 16 over the stride-16 subsequences, twiddles W_256^(j k1),
-// a transpose through LDS and 16 DFTs of length 16 again. A column is handled by 16
-// threads; thread j holds the elements j, j + 16, ... before a transform and the
-// elements j, j + 16, ... of the result after it, which is also the input order of the
-// next transform, so a pass with the kernel between the forward and the inverse
-// transform needs two transposes. The same tile of 16 columns and the same modes and
-// tables as k_cols.
-// 16-point DFT in registers, natural order in and out: a radix-4 pass over the four
-// stride-4 subsequences, twiddles W_16^(n2 k1), a radix-4 pass across them.
-__device__ __forceinline__ float2 w16(int m, bool inv) {
-  // e^{-2 pi i m / 16} (forward), its conjugate (inverse), m = 0 .. 9
-  constexpr float c[10] = {1.0f, 0.92387953251128674f, 0.70710678118654752f,
-                           0.38268343236508977f, 0.0f, -0.38268343236508977f,
-                           -0.70710678118654752f, -0.92387953251128674f, -1.0f,
-                           -0.92387953251128674f};
-  constexpr float sn[10] = {0.0f, 0.38268343236508977f, 0.70710678118654752f,
-                            0.92387953251128674f, 1.0f, 0.92387953251128674f,
-                            0.70710678118654752f, 0.38268343236508977f, 0.0f,
-                            -0.38268343236508977f};
-  return make_float2(c[m], inv ? sn[m] : -sn[m]);
-}
-
-template <bool INV>
-__device__ __forceinline__ void dft16(float2 (&x)[16]) {
-  float2 y[4][4];  // y[n2][k1]: DFT over n1 of x[4 n1 + n2]
+    const float a0 = t0[my] + t0[live ? kz : 0], a1 = t1[my] * t1[live ? kz : 0];
 #pragma unroll
-  for (int n2 = 0; n2 < 4; ++n2) {
-    float2 v[4] = {x[n2], x[4 + n2], x[8 + n2], x[12 + n2]};
-    butterfly<4, INV>(v);
-#pragma unroll
-    for (int k1 = 0; k1 < 4; ++k1) y[n2][k1] = (n2 * k1 == 0) ? v[k1] : cmul(v[k1], w16(n2 * k1, INV));
-  }
-#pragma unroll
-  for (int k1 = 0; k1 < 4; ++k1) {
-    float2 v[4] = {y[0][k1], y[1][k1], y[2][k1], y[3][k1]};
-    butterfly<4, INV>(v);
-#pragma unroll
-    for (int k2 = 0; k2 < 4; ++k2) x[k1 + 4 * k2] = v[k2];
-  }
-}
-
-constexpr int kC256Pad = 17;  // LDS row of 16 values plus one (bank spread)
-
-// x: this thread's 16 inputs (elements j + 16 n1 of its column, in order of n1); out:
-// elements j + 16 k2 of the transform (thread j of the column, c its column in the tile)
-template <bool INV>
-__device__ __forceinline__ void fft256_cols(float2 (&x)[16], float2 *lds, int c, int j,
-                                            const float2 *__restrict__ tw) {
-  dft16<INV>(x);  // x[k1] = DFT over n1 of the subsequence j
-#pragma unroll
-  for (int k1 = 1; k1 < 16; ++k1) {
-    float2 t = tw[j * k1];
-    if (INV) t.y = -t.y;
-    x[k1] = cmul(x[k1], t);
-  }
-  __syncthreads();  // the previous transpose's reads are done
-#pragma unroll
-  for (int k1 = 0; k1 < 16; ++k1) lds[(c * 16 + k1) * kC256Pad + j] = x[k1];
-  __syncthreads();
-#pragma unroll
-  for (int n2 = 0; n2 < 16; ++n2) x[n2] = lds[(c * 16 + j) * kC256Pad + n2];
-  dft16<INV>(x);  // x[k2] = element j + 16 k2
-}
-
-template <int AXIS, int MODE>
-__global__ __launch_bounds__(FT) void k_cols256(const float2 *src, float2 *dst, int P,
-                                                const float2 *__restrict__ tw,
-                                                const float *__restrict__ tab, float scale,
-                                                int deriv) {
-  constexpr int n = 256, T = 16;
-  static_assert(FT == T * 16, "16 threads per column");
-  __shared__ float2 lds[T * 16 * kC256Pad];
-  const int c = threadIdx.x & 15, j = threadIdx.x >> 4;
-  const int kc0 = blockIdx.x * T;
-  const int outer = blockIdx.y;
-  auto gidx = [&](int idx) -> int64_t {
-    if constexpr (AXIS == 1)
-      return ((int64_t)outer * n + idx) * P + kc0 + c;
-    else
-      return ((int64_t)idx * n + outer) * P + kc0 + c;
-  };
-  float2 x[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) x[q] = src[gidx(j + 16 * q)];
-  if constexpr (MODE == 4) {
-    // (-i k_d) v before the inverse transform; element j + 16 q sits at mx = j + 16 q
-    const float *kv = tab + 2 * n;
-    const int kz = kc0 + c;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int mx = j + 16 * q;
-      const float k = kv[deriv == 0 ? mx : (deriv == 1 ? outer : min(kz, n - 1))];
-      x[q] = make_float2(k * x[q].y, -k * x[q].x);
+    for (int m = 0; m < S::N1; ++m) {
+      const int mx = t + S::N2 * m;
+      const float g = (mx | my | kz) != 0 ? -scale / ((t0[mx] + a0) * (t1[mx] * a1)) : 0.0f;
+      x[m] = make_float2(x[m].x * g, x[m].y * g);
     }
   }
-  if constexpr (MODE == 0 || MODE == 1 || MODE == 3) fft256_cols<false>(x, lds, c, j, tw);
-  if constexpr (MODE == 1 || MODE == 3) {
-    const float *t0 = tab, *t1 = tab + n;
-    const int my = outer, kz = kc0 + c;
+  if constexpr (MODE == 3 || MODE == 4) {
+    const float *kv = tab + 2 * N;
+    float2 y[S::N1];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int mx = j + 16 * q;
-      float gval = 0.0f;
-      if (kz <= n / 2 && (mx | my | kz) != 0)
-        gval = -scale / ((t0[mx] + t0[my] + t0[kz]) * (t1[mx] * t1[my] * t1[kz]));
-      x[q] = make_float2(x[q].x * gval, x[q].y * gval);
+    for (int m = 0; m < S::N1; ++m) {
+      const float k = kv[t + S::N2 * m];
+      y[m] = make_float2(k * x[m].y, -k * x[m].x);  // (-i k) x
     }
-  }
-  if constexpr (MODE == 1 || MODE == 2 || MODE == 4) fft256_cols<true>(x, lds, c, j, tw);
+    cols<N, true>(y, lds, base, t, tw);
 #pragma unroll
-  for (int q = 0; q < 16; ++q) dst[gidx(j + 16 * q)] = x[q];
-}
-
-// 8-point DFT in registers, natural order in and out (radix 4 over the two stride-2
-// subsequences, twiddles W_8^(n2 k1), radix 2 across)
-template <bool INV>
-__device__ __forceinline__ void dft8(float2 (&x)[8]) {
-  constexpr float h = 0.70710678118654752f;
-  float2 v0[4] = {x[0], x[2], x[4], x[6]}, v1[4] = {x[1], x[3], x[5], x[7]};
-  butterfly<4, INV>(v0);
-  butterfly<4, INV>(v1);
-  // W_8^k1 for k1 = 1, 2, 3 (forward e^{-i pi k1 / 4}; inverse conjugate)
-  const float s = INV ? 1.0f : -1.0f;
-  v1[1] = cmul(v1[1], make_float2(h, s * h));
-  v1[2] = make_float2(-s * v1[2].y, s * v1[2].x);  // times (0, s)
-  v1[3] = cmul(v1[3], make_float2(-h, s * h));
+    for (int m = 0; m < S::N1; ++m)
+      if (live) dst2[at + (t + S::N2 * m) * step] = y[m];
+  }
+  if constexpr (MODE != 0) cols<N, true>(x, lds, base, t, tw);
 #pragma unroll
-  for (int k1 = 0; k1 < 4; ++k1) {
-    x[k1] = cadd(v0[k1], v1[k1]);
-    x[k1 + 4] = csub(v0[k1], v1[k1]);
-  }
-}
-
-// In-place length-128 transforms of the 32 rows of buf (row r at r * kRowPitch128,
-// natural order in and out), as 16 x 8 four-step transforms: thread t = 0 .. 7 of a row
-// takes the 16-point DFT of the stride-8 subsequence t, the twiddles W_128^(t k1), and
-// after a transpose the two 8-point DFTs of k1 = t and t + 8. tw is the table of n = 256
-// (W_128^m = tw[2 m]).
-constexpr int kRowPitch128 = 132;  // 128 values plus 4 (spreads the rows over the banks)
-
-template <bool INV>
-__device__ __forceinline__ void fft128_rows(float2 *buf, const float2 *__restrict__ tw) {
-  const int r = threadIdx.x >> 3, t = threadIdx.x & 7;
-  float2 *row = buf + r * kRowPitch128;
-  float2 x[16];
-#pragma unroll
-  for (int n1 = 0; n1 < 16; ++n1) x[n1] = row[8 * n1 + t];
-  dft16<INV>(x);
-#pragma unroll
-  for (int k1 = 1; k1 < 16; ++k1) {
-    float2 w = tw[2 * t * k1];
-    if (INV) w.y = -w.y;
-    x[k1] = cmul(x[k1], w);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k1 = 0; k1 < 16; ++k1) row[k1 * 8 + t] = x[k1];
-  __syncthreads();
-  float2 a[8], b[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    a[j] = row[t * 8 + j];
-    b[j] = row[(t + 8) * 8 + j];
-  }
-  dft8<INV>(a);
-  dft8<INV>(b);
-  __syncthreads();
-#pragma unroll
-  for (int k2 = 0; k2 < 8; ++k2) {
-    row[t + 16 * k2] = a[k2];
-    row[t + 8 + 16 * k2] = b[k2];
-  }
-  __syncthreads();
-}
-
-// k_rows_r2c for n = 256 (32 rows per block) with the register transform
-__global__ __launch_bounds__(FT) void k_rows_r2c256(const float *__restrict__ x,
-                                                    float2 *__restrict__ spec, int P,
-                                                    const float2 *__restrict__ tw,
-                                                    const float *__restrict__ mean) {
-  constexpr int n = 256, L = 128, T = 32;
-  static_assert(FT == T * 8, "8 threads per row");
-  __shared__ float2 buf[T * kRowPitch128];
-  const int64_t rows = (int64_t)n * n;
-  const int64_t row0 = (int64_t)blockIdx.x * T;
-  const float mu = mean ? *mean : 0.0f;
-  for (int e = threadIdx.x; e < T * L; e += FT) {
-    const int col = e / L, m = e % L;
-    const int64_t row = row0 + col;
-    float2 v = make_float2(0.f, 0.f);
-    if (row < rows) {
-      v = reinterpret_cast<const float2 *>(x + row * n)[m];
-      v.x -= mu;
-      v.y -= mu;
-    }
-    buf[col * kRowPitch128 + m] = v;
-  }
-  __syncthreads();
-  fft128_rows<false>(buf, tw);
-  for (int e = threadIdx.x; e < T * (L + 1); e += FT) {
-    const int col = e / (L + 1), k = e % (L + 1);
-    const int64_t row = row0 + col;
-    if (row >= rows) continue;
-    const float2 *b = buf + col * kRowPitch128;
-    const float2 zk = b[k == L ? 0 : k];
-    const float2 zm = conjf2(b[k == 0 ? 0 : L - k]);
-    const float2 E = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y + zm.y));
-    const float2 D = csub(zk, zm);
-    const float2 O = make_float2(0.5f * D.y, -0.5f * D.x);  // -i D / 2
-    spec[row * P + k] = cadd(E, cmul(tw[k], O));
-  }
-}
-
-// k_rows_c2r for n = 256 with the register transform
-__global__ __launch_bounds__(FT) void k_rows_c2r256(const float2 *__restrict__ spec0,
-                                                    float *__restrict__ x, int P,
-                                                    const float2 *__restrict__ tw, int stride,
-                                                    int comp0, int ncomp, int64_t cstride) {
-  constexpr int n = 256, L = 128, T = 32;
-  __shared__ float2 buf[T * kRowPitch128];
-  const int64_t rows = (int64_t)n * n;
-  const int64_t row0 = (int64_t)blockIdx.x * T;
-  for (int d = 0; d < ncomp; ++d) {
-    const float2 *__restrict__ spec = spec0 + d * cstride;
-    const int comp = comp0 + d;
-    if (d > 0) __syncthreads();  // the previous component's reads of buf are done
-    // the rows' half spectra (L + 1 values each) read once, coalesced, then Z~ formed from
-    // X_k and X_{L-k} in LDS
-    for (int e = threadIdx.x; e < T * (L + 1); e += FT) {
-      const int col = e / (L + 1), k = e % (L + 1);
-      const int64_t row = row0 + col;
-      buf[col * kRowPitch128 + k] = row < rows ? spec[row * P + k] : make_float2(0.f, 0.f);
-    }
-    __syncthreads();
-    constexpr int kPer = T * L / FT;
-    float2 z[kPer];
-  #pragma unroll
-    for (int it = 0; it < kPer; ++it) {
-      const int e = threadIdx.x + it * FT, col = e / L, k = e % L;
-      const float2 *b = buf + col * kRowPitch128;
-      const float2 xk = b[k];
-      const float2 xm = conjf2(b[L - k]);
-      const float2 Et = cadd(xk, xm);
-      const float2 Ot = cmul(conjf2(tw[k]), csub(xk, xm));
-      z[it] = make_float2(Et.x - Ot.y, Et.y + Ot.x);  // Et + i Ot
-    }
-    __syncthreads();
-  #pragma unroll
-    for (int it = 0; it < kPer; ++it) {
-      const int e = threadIdx.x + it * FT, col = e / L, k = e % L;
-      buf[col * kRowPitch128 + k] = z[it];
-    }
-    __syncthreads();
-    fft128_rows<true>(buf, tw);
-    if (stride == 1) {
-      for (int e = threadIdx.x; e < T * L; e += FT) {
-        const int col = e / L, m = e % L;
-        const int64_t row = row0 + col;
-        if (row < rows) reinterpret_cast<float2 *>(x + row * n)[m] = buf[col * kRowPitch128 + m];
-      }
-    } else {
-      for (int e = threadIdx.x; e < 2 * T * L; e += FT) {
-        const int col = e / n, m = e % n;  // m: real position along the row
-        const int64_t row = row0 + col;
-        if (row < rows) {
-          const float2 v = buf[col * kRowPitch128 + (m >> 1)];
-          x[(row * n + m) * stride + comp] = (m & 1) ? v.y : v.x;
-        }
-      }
-    }
-  }
-}
-
-// a column pass: the register four-step kernel for n = 256 (16-column tiles), the LDS
-// Stockham kernel otherwise
-template <int AXIS, int MODE>
-void launch_cols(dim3 grid, hipStream_t s, const float2 *src, float2 *dst, int n, int P,
-                 const float2 *tw, const float *tab, float scale, int deriv) {
-  if (n == 256 && TL / n == 16)
-    k_cols256<AXIS, MODE><<<grid, FT, 0, s>>>(src, dst, P, tw, tab, scale, deriv);
-  else
-    k_cols<AXIS, MODE><<<grid, FT, 0, s>>>(src, dst, n, P, tw, tab, scale, deriv);
+  for (int m = 0; m < S::N1; ++m)
+    if (live) dst[at + (t + S::N2 * m) * step] = x[m];
 }
 
 // Twiddles tw[m] = e^{-2 pi i m / n} and the per-axis tables of the kernel, in FP64 on
@@ -560,10 +231,8 @@ void launch_cols(dim3 grid, hipStream_t s, const float2 *src, float2 *dst, int n
 //     box), t1 = sinc(omega/2)^(2 deconv), omega = k h = 2 pi m / n;
 //   kind 1 (seven-point eigenvalue): t0 = (4 / h^2) sin^2(omega/2), t1 = 1;
 //   kd = k, except 0 at the Nyquist index n/2 (the derivative of a self-conjugate mode).
-__global__ void k_fft_tables(float2 *__restrict__ tw, float *__restrict__ tab, int n, int deconv,
-                             int kind) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+__device__ void fill_tables(int i, float2 *__restrict__ tw, float *__restrict__ tab, int n, int deconv,
+                            int kind) {
   double sn, cs;
   sincospi(-2.0 * (double)i / (double)n, &sn, &cs);
   tw[i] = make_float2((float)cs, (float)sn);
@@ -576,10 +245,105 @@ __global__ void k_fft_tables(float2 *__restrict__ tw, float *__restrict__ tab, i
   } else {
     const double k = 2.0 * M_PI * (double)m;
     const double sinc = (m == 0) ? 1.0 : sh / (M_PI * half);
+    double w = 1.0;
+    for (int p = 0; p < 2 * deconv; ++p) w *= sinc;
     tab[i] = (float)(k * k);
-    tab[n + i] = (float)pow(sinc, 2.0 * deconv);
+    tab[n + i] = (float)w;
   }
   tab[2 * n + i] = (i == n / 2) ? 0.0f : (float)(2.0 * M_PI * (double)m);
+}
+
+// The launch before the passes: the tables (the last blocks) and, with nb > 0, the partial
+// sums of x over nb blocks in a fixed order.
+__global__ __launch_bounds__(RED_THREADS) void k_fft_prepare(float2 *__restrict__ tw,
+                                                             float *__restrict__ tab, int n, int deconv,
+                                                             int kind, const float *__restrict__ x, int nb,
+                                                             double *__restrict__ partial) {
+  if ((int)blockIdx.x >= nb) {
+    const int i = ((int)blockIdx.x - nb) * RED_THREADS + threadIdx.x;
+    if (i < n) fill_tables(i, tw, tab, n, deconv, kind);
+    return;
+  }
+  const int64_t pairs = (int64_t)n * n * n / 2, stride = (int64_t)nb * RED_THREADS;
+  const float2 *x2 = reinterpret_cast<const float2 *>(x);
+  double s = 0.0;
+  int64_t i = (int64_t)blockIdx.x * RED_THREADS + threadIdx.x;
+  for (; i + 3 * stride < pairs; i += 4 * stride) {
+    const float2 a = x2[i], b = x2[i + stride], c = x2[i + 2 * stride], d = x2[i + 3 * stride];
+    s += (((double)a.x + a.y) + ((double)b.x + b.y)) + (((double)c.x + c.y) + ((double)d.x + d.y));
+  }
+  for (; i < pairs; i += stride) s += (double)x2[i].x + x2[i].y;
+  __shared__ double w[RED_THREADS / 64];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+  if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int q = 0; q < RED_THREADS / 64; ++q) t += w[q];
+    partial[blockIdx.x] = t;
+  }
+}
+
+// F::run<N>(...) for the grid size n
+template <class F, class... A>
+void by_size(int n, A... a) {
+  switch (n) {
+    case 8: F::template run<8>(a...); break;
+    case 16: F::template run<16>(a...); break;
+    case 32: F::template run<32>(a...); break;
+    case 64: F::template run<64>(a...); break;
+    case 128: F::template run<128>(a...); break;
+    case 256: F::template run<256>(a...); break;
+    case 512: F::template run<512>(a...); break;
+    default: F::template run<kMaxN>(a...); break;
+  }
+}
+
+template <int N>
+unsigned row_blocks() {
+  return (unsigned)(((int64_t)N * N + RowShape<N / 2>::R - 1) / RowShape<N / 2>::R);
+}
+
+template <int AXIS, int MODE>
+struct Cols {
+  template <int N>
+  static void run(hipStream_t s, const FftBufs &b, const float2 *src, float2 *dst, float2 *dst2,
+                  float scale) {
+    using C = ColShape<N>;
+    const unsigned blocks = (N / 2 / kCols + 1) * (N / C::OUT);
+    k_cols<N, AXIS, MODE><<<blocks, C::NT, 0, s>>>(src, dst, dst2, fft_pitch_of(N), b.twiddle, b.tab, scale);
+  }
+};
+
+struct Forward {  // pass A
+  template <int N>
+  static void run(hipStream_t s, const FftBufs &b, const float *x, Mean mean) {
+    k_rows_r2c<N / 2><<<row_blocks<N>(), 256, 0, s>>>(x, b.spec, fft_pitch_of(N), b.twiddle, mean);
+  }
+};
+
+struct Backward {  // pass E
+  template <int N>
+  static void run(hipStream_t s, const FftBufs &b, const float2 *spec, float *x, int stride, int comp) {
+    k_rows_c2r<N / 2><<<row_blocks<N>(), 256, 0, s>>>(spec, x, fft_pitch_of(N), b.twiddle, stride, comp);
+  }
+};
+
+struct Backward3 {
+  template <int N>
+  static void run(hipStream_t s, const FftBufs &b, const float2 *sx, const float2 *sy, const float2 *sp,
+                  float *x) {
+    k_rows_c2r3<N / 2><<<row_blocks<N>(), 256, 0, s>>>(sx, sy, sp, x, fft_pitch_of(N), b.twiddle,
+                                                       b.tab + 2 * N);
+  }
+};
+
+template <int AXIS, int MODE>
+void run_cols(int n, hipStream_t s, const FftBufs &b, const float2 *src, float2 *dst, float2 *dst2,
+              float scale) {
+  by_size<Cols<AXIS, MODE>, hipStream_t, const FftBufs &, const float2 *, float2 *, float2 *, float>(
+      n, s, b, src, dst, dst2, scale);
 }
 
 }  // namespace
@@ -588,78 +352,81 @@ int fft_pitch(int n) { return fft_pitch_of(n); }
 
 size_t fft_spec_elems(int n) { return (size_t)n * n * fft_pitch(n); }
 
-hipError_t fft_run(const FftBufs &b, int n, const float *rho, const float *mean, float coef,
-                   int deconv, int kind, float *out, hipStream_t s) {
-  const int P = fft_pitch(n);
-  const int Trow = TL / (n / 2), Tcol = TL / n;
-  const unsigned row_blocks = (unsigned)(((int64_t)n * n + Trow - 1) / Trow);
-  const dim3 col_grid(P / Tcol, n);
+int fft_mean_blocks(int n) {
+  return (int)std::min<int64_t>(RED_BLOCKS, ((int64_t)n * n * n / 2 + RED_THREADS - 1) / RED_THREADS);
+}
+
+// Us per solve on MI355X, with the LDS Stockham stages (registers at 256 only), a launch for
+// the tables and two for the mean, and FULL_FFT's three separate inverse transforms, against
+// these passes:
+//        n      32          64         128        256        512
+//   FFT       81 -> 27   84 -> 27   116 -> 42  243 -> 160  3291 -> 1489
+//   FULL_FFT 177 -> 30  187 -> 34   232 -> 65  599 -> 329  8181 -> 3398
+// (FULL_FFT moves 128 bytes a cell instead of 176.)
+hipError_t fft_run(const FftBufs &b, int n, const float *rho, const float *mean, double *partial,
+                   float coef, int deconv, int kind, float *out, hipStream_t s) {
   const float scale = (float)((double)coef / ((double)n * n * n));
   float2 *spec = b.spec;
-  k_fft_tables<<<(n + 255) / 256, 256, 0, s>>>(b.twiddle, b.tab, n, deconv,
-                                               kind == PM_FFT_7PT ? 1 : 0);
-  if (n == 256 && Trow == 32)
-    k_rows_r2c256<<<row_blocks, FT, 0, s>>>(rho, spec, P, b.twiddle, mean);
-  else
-    k_rows_r2c<<<row_blocks, FT, 0, s>>>(rho, spec, n, P, b.twiddle, mean);
-  launch_cols<1, 0>(col_grid, s, spec, spec, n, P, b.twiddle, b.tab, scale, 0);
+  const int nb = mean ? 0 : fft_mean_blocks(n);
+  k_fft_prepare<<<nb + (n + RED_THREADS - 1) / RED_THREADS, RED_THREADS, 0, s>>>(
+      b.twiddle, b.tab, n, deconv, kind == PM_FFT_7PT ? 1 : 0, rho, nb, partial);
+  by_size<Forward, hipStream_t, const FftBufs &, const float *, Mean>(
+      n, s, b, rho, Mean{mean, mean ? nullptr : partial, nb});
+  run_cols<1, 0>(n, s, b, spec, spec, nullptr, scale);
   if (kind != PM_FFT_FULL) {
-    launch_cols<0, 1>(col_grid, s, spec, spec, n, P, b.twiddle, b.tab, scale, 0);
-    launch_cols<1, 2>(col_grid, s, spec, spec, n, P, b.twiddle, b.tab, scale, 0);
-    if (n == 256 && Trow == 32)
-      k_rows_c2r256<<<row_blocks, FT, 0, s>>>(spec, out, P, b.twiddle, 1, 0, 1, 0);
-    else
-      k_rows_c2r<<<row_blocks, FT, 0, s>>>(spec, out, n, P, b.twiddle, 1, 0, 1, 0);
+    run_cols<0, 1>(n, s, b, spec, spec, nullptr, scale);
+    run_cols<1, 2>(n, s, b, spec, spec, nullptr, scale);
+    by_size<Backward, hipStream_t, const FftBufs &, const float2 *, float *, int, int>(n, s, b, spec, out,
+                                                                                       1, 0);
     return hipGetLastError();
   }
-  // force in Fourier space: spec <- G F once, then per component d the inverse of
-  // -i k_d G F along i and j into spectrum d of spec2 (three spectra), and one row pass
-  // over the three writing whole (x, y, z) cells of the force grid
-  launch_cols<0, 3>(col_grid, s, spec, spec, n, P, b.twiddle, b.tab, scale, 0);
-  const int64_t elems = (int64_t)fft_spec_elems(n);
-  for (int d = 0; d < 3; ++d) {
-    float2 *sd = b.spec2 + d * elems;
-    launch_cols<0, 4>(col_grid, s, spec, sd, n, P, b.twiddle, b.tab, scale, d);
-    launch_cols<1, 2>(col_grid, s, sd, sd, n, P, b.twiddle, b.tab, scale, 0);
-  }
-  if (n == 256 && Trow == 32)
-    k_rows_c2r256<<<row_blocks, FT, 0, s>>>(b.spec2, out, P, b.twiddle, 3, 0, 3, elems);
-  else
-    k_rows_c2r<<<row_blocks, FT, 0, s>>>(b.spec2, out, n, P, b.twiddle, 3, 0, 3, elems);
+  // the force in Fourier space: the potential's spectrum in spec, the i and j components'
+  // in spec2
+  float2 *sx = b.spec2, *sy = b.spec2 + fft_spec_elems(n);
+  run_cols<0, 3>(n, s, b, spec, spec, sx, scale);
+  run_cols<1, 2>(n, s, b, sx, sx, nullptr, scale);
+  run_cols<1, 4>(n, s, b, spec, spec, sy, scale);
+  by_size<Backward3, hipStream_t, const FftBufs &, const float2 *, const float2 *, const float2 *, float *>(
+      n, s, b, sx, sy, spec, out);
   return hipGetLastError();
 }
 
 hipError_t fft_tables(const FftBufs &b, int n, int deconv, int kind, hipStream_t s) {
-  k_fft_tables<<<(n + 255) / 256, 256, 0, s>>>(b.twiddle, b.tab, n, deconv, kind);
+  k_fft_prepare<<<(n + RED_THREADS - 1) / RED_THREADS, RED_THREADS, 0, s>>>(b.twiddle, b.tab, n, deconv, kind,
+                                                                            nullptr, 0, nullptr);
   return hipGetLastError();
 }
 
 hipError_t fft_forward(const FftBufs &b, int n, const float *x, const float *mean, hipStream_t s) {
-  const int P = fft_pitch(n);
-  const int Trow = TL / (n / 2), Tcol = TL / n;
-  const unsigned row_blocks = (unsigned)(((int64_t)n * n + Trow - 1) / Trow);
-  const dim3 col_grid(P / Tcol, n);
-  if (n == 256 && Trow == 32)
-    k_rows_r2c256<<<row_blocks, FT, 0, s>>>(x, b.spec, P, b.twiddle, mean);
-  else
-    k_rows_r2c<<<row_blocks, FT, 0, s>>>(x, b.spec, n, P, b.twiddle, mean);
-  launch_cols<1, 0>(col_grid, s, b.spec, b.spec, n, P, b.twiddle, b.tab, 0.0f, 0);
-  launch_cols<0, 0>(col_grid, s, b.spec, b.spec, n, P, b.twiddle, b.tab, 0.0f, 0);
+  by_size<Forward, hipStream_t, const FftBufs &, const float *, Mean>(n, s, b, x, Mean{mean, nullptr, 0});
+  run_cols<1, 0>(n, s, b, b.spec, b.spec, nullptr, 0.0f);
+  run_cols<0, 0>(n, s, b, b.spec, b.spec, nullptr, 0.0f);
   return hipGetLastError();
 }
 
 hipError_t fft_inverse(const FftBufs &b, int n, float *out, int stride, int comp, hipStream_t s) {
-  const int P = fft_pitch(n);
-  const int Trow = TL / (n / 2), Tcol = TL / n;
-  const unsigned row_blocks = (unsigned)(((int64_t)n * n + Trow - 1) / Trow);
-  const dim3 col_grid(P / Tcol, n);
-  launch_cols<0, 2>(col_grid, s, b.spec, b.spec, n, P, b.twiddle, b.tab, 0.0f, 0);
-  launch_cols<1, 2>(col_grid, s, b.spec, b.spec, n, P, b.twiddle, b.tab, 0.0f, 0);
-  if (n == 256 && Trow == 32)
-    k_rows_c2r256<<<row_blocks, FT, 0, s>>>(b.spec, out, P, b.twiddle, stride, comp, 1, 0);
-  else
-    k_rows_c2r<<<row_blocks, FT, 0, s>>>(b.spec, out, n, P, b.twiddle, stride, comp, 1, 0);
+  run_cols<0, 2>(n, s, b, b.spec, b.spec, nullptr, 0.0f);
+  run_cols<1, 2>(n, s, b, b.spec, b.spec, nullptr, 0.0f);
+  by_size<Backward, hipStream_t, const FftBufs &, const float2 *, float *, int, int>(n, s, b, b.spec, out,
+                                                                                     stride, comp);
   return hipGetLastError();
+}
+
+hipError_t fft_alloc(pm_ctx *ctx) {
+  const int n = ctx->n;
+  const size_t pitch = std::max(fft_pitch(n), spectrum_pitch(n));
+  hipError_t e = hipMalloc(&ctx->twiddle, sizeof(float2) * n);
+  if (e == hipSuccess) e = hipMalloc(&ctx->fft_tab, sizeof(float) * 3 * n);
+  if (e == hipSuccess) e = hipMalloc(&ctx->spec, sizeof(float2) * n * n * pitch);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    if (ctx->twiddle) (void)hipFree(ctx->twiddle);
+    if (ctx->fft_tab) (void)hipFree(ctx->fft_tab);
+    ctx->twiddle = nullptr;
+    ctx->fft_tab = nullptr;
+    ctx->spec = nullptr;
+  }
+  return e;
 }
 
 int pm_fft_solve_kind(pm_ctx *ctx, const float *rho, float coef, int deconv, int kind, float *out,
@@ -668,27 +435,17 @@ int pm_fft_solve_kind(pm_ctx *ctx, const float *rho, float coef, int deconv, int
   if (n < 8 || (n & (n - 1)) != 0)
     return pm_fail(ctx, PM_ERR_SHAPE, "FFT solver needs a power-of-two grid (8 .. 1024)");
   const size_t elems = fft_spec_elems(n);
-  if (!ctx->spec) {
-    if (hipMalloc(&ctx->spec, sizeof(float2) * elems) != hipSuccess ||
-        hipMalloc(&ctx->twiddle, sizeof(float2) * n) != hipSuccess ||
-        hipMalloc(&ctx->fft_tab, sizeof(float) * 3 * n) != hipSuccess)
-      return pm_fail(ctx, PM_ERR_NOMEM, "FFT scratch allocation failed");
-  }
+  if (!ctx->spec && fft_alloc(ctx) != hipSuccess)
+    return pm_fail(ctx, PM_ERR_NOMEM, "FFT scratch allocation failed");
   if (kind == PM_FFT_FULL && !ctx->spec2) {
-    // three spectra: one per force component
-    if (hipMalloc(&ctx->spec2, 3 * sizeof(float2) * elems) != hipSuccess) {
+    if (hipMalloc(&ctx->spec2, 2 * sizeof(float2) * elems) != hipSuccess) {
       ctx->spec2 = nullptr;
       return pm_fail(ctx, PM_ERR_NOMEM, "FFT scratch allocation failed");
     }
   }
-  if (!mean) {
-    // the mean of rho, subtracted before the transform
-    PM_HIP(ctx, launch_sum_moments(rho, (int64_t)n * n * n, ctx->red_partial, ctx->red_result,
-                                   ctx->mean_f + 2, s));
-    mean = ctx->mean_f + 2;
-  }
+  // (the mean of rho is subtracted before the transform: the one given, or summed first)
   FftBufs b{(float2 *)ctx->spec, (float2 *)ctx->spec2, ctx->twiddle, ctx->fft_tab};
-  PM_HIP(ctx, fft_run(b, n, rho, mean, coef, deconv, kind, out, s));
+  PM_HIP(ctx, fft_run(b, n, rho, mean, ctx->red_partial, coef, deconv, kind, out, s));
   return PM_OK;
 }
 

@@ -1,5 +1,4 @@
-// Initial conditions by Lagrangian perturbation theory and the power-spectrum estimator
-// (paper Sect. 3.3 and App. A; the estimator of Sect. 4).
+// Initial conditions by Lagrangian perturbation theory (paper Sect. 3.3 and App. A).
 //
 // pm_ic_lpt: the linear density at a = 1 from a white-noise grid and a P(k) table,
 // DFT[delta] = sqrt(N) sqrt(P(k)) DFT[w] (unit box, N = n^3), with the k = 0 mode and
@@ -184,55 +183,6 @@ __global__ __launch_bounds__(kT) void k_lpt_finish(float *__restrict__ pos,
   if (cell) cell[p] = (c[0] * n + c[1]) * n + c[2];
 }
 
-// P(k) shells: per mode |F|^2 / (N mean)^2 / W^2 with W = prod_d sinc(pi m_d / n)^deconv,
-// weight 2 for 0 < kz < n/2 (the mode and its conjugate), shell b = rint(|m|) in
-// 1 .. nbins; per-block sums in LDS, then one FP64 atomic per shell and block.
-constexpr int kPkMaxBins = 1024;
-
-__global__ __launch_bounds__(kT) void k_pk_bins(const float2 *__restrict__ spec, int n, int P,
-                                                int deconv, const double *__restrict__ mean,
-                                                int nbins, double *__restrict__ acc) {
-  __shared__ double s_p[kPkMaxBins], s_k[kPkMaxBins], s_c[kPkMaxBins];
-  for (int b = threadIdx.x; b < nbins; b += kT) s_p[b] = s_k[b] = s_c[b] = 0.0;
-  __syncthreads();
-  const int hz = n / 2 + 1;
-  const int64_t count = (int64_t)n * n * hz;
-  const double norm = 1.0 / ((double)n * n * n * mean[0]);
-  for (int64_t t = (int64_t)blockIdx.x * kT + threadIdx.x; t < count; t += (int64_t)gridDim.x * kT) {
-    const int iz = (int)(t % hz);
-    const int iy = (int)((t / hz) % n);
-    const int ix = (int)(t / ((int64_t)hz * n));
-    const int mx = ix < n / 2 ? ix : ix - n;
-    const int my = iy < n / 2 ? iy : iy - n;
-    const double mm = sqrt((double)mx * mx + (double)my * my + (double)iz * iz);
-    const int b = (int)rint(mm);
-    if (b < 1 || b > nbins) continue;
-    const float2 v = spec[((int64_t)ix * n + iy) * P + iz];
-    double w = 1.0;
-    const int md[3] = {mx, my, iz};
-    for (int d = 0; d < 3; ++d) {
-      if (md[d] != 0) {
-        const double x = M_PI * md[d] / n;
-        w *= pow(sin(x) / x, (double)deconv);
-      }
-    }
-    const double re = v.x * norm, im = v.y * norm;
-    const double pw = (re * re + im * im) / (w * w);
-    const double wt = (iz == 0 || 2 * iz == n) ? 1.0 : 2.0;
-    atomicAdd(&s_p[b - 1], wt * pw);
-    atomicAdd(&s_k[b - 1], wt * kTwoPi * mm);
-    atomicAdd(&s_c[b - 1], wt);
-  }
-  __syncthreads();
-  for (int b = threadIdx.x; b < nbins; b += kT) {
-    if (s_c[b] != 0.0) {
-      atomicAdd(&acc[3 * b], s_p[b]);
-      atomicAdd(&acc[3 * b + 1], s_k[b]);
-      atomicAdd(&acc[3 * b + 2], s_c[b]);
-    }
-  }
-}
-
 // Device scratch of one pm_ic_lpt call (allocated for the call and released after it).
 struct IcScratch {
   std::vector<void *> owned;
@@ -399,47 +349,6 @@ int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab, co
   PM_HIP(ctx, hipGetLastError());
   // the scratch is released when the call returns: wait for the work that reads it
   PM_HIP(ctx, hipStreamSynchronize(s));
-  return PM_OK;
-}
-
-int pm_power_spectrum(pm_ctx *ctx, const float *rho, int deconv, int nbins, double *pk,
-                      double *kmean, int64_t *nmodes, pm_stream stream) {
-  if (!ctx) return PM_ERR_ARG;
-  if (!rho || !pk) return pm_fail(ctx, PM_ERR_ARG, "null pointer");
-  if (deconv < 0 || deconv > 3) return pm_fail(ctx, PM_ERR_ARG, "deconv must be 0 .. 3");
-  if (nbins < 1 || nbins > kPkMaxBins) return pm_fail(ctx, PM_ERR_ARG, "nbins must be 1 .. 1024");
-  const int n = ctx->n;
-  if ((n & (n - 1)) != 0)
-    return pm_fail(ctx, PM_ERR_SHAPE, "the power spectrum needs a power-of-two grid");
-  const hipStream_t s = (hipStream_t)stream;
-  const int64_t N = (int64_t)n * n * n;
-  if (!ctx->spec) {
-    if (hipMalloc(&ctx->spec, sizeof(float2) * fft_spec_elems(n)) != hipSuccess ||
-        hipMalloc(&ctx->twiddle, sizeof(float2) * n) != hipSuccess ||
-        hipMalloc(&ctx->fft_tab, sizeof(float) * 3 * n) != hipSuccess)
-      return pm_fail(ctx, PM_ERR_NOMEM, "FFT scratch allocation failed");
-  }
-  // FP64 mean in red_result[2], FP32 mean (subtracted before the transform) in mean_f[2]
-  PM_HIP(ctx, launch_sum_moments(rho, N, ctx->red_partial, ctx->red_result, ctx->mean_f + 2, s));
-  FftBufs b{(float2 *)ctx->spec, nullptr, ctx->twiddle, ctx->fft_tab};
-  PM_HIP(ctx, fft_tables(b, n, 0, 0, s));
-  PM_HIP(ctx, fft_forward(b, n, rho, ctx->mean_f + 2, s));
-  // shell sums in the partial buffer (3 doubles per shell, within its 3 * 65536 doubles)
-  double *acc = ctx->red_partial;
-  PM_HIP(ctx, hipMemsetAsync(acc, 0, sizeof(double) * 3 * nbins, s));
-  const int64_t modes = (int64_t)n * n * (n / 2 + 1);
-  const unsigned grid = (unsigned)std::min<int64_t>(blocks_for(modes, kT), 2048);
-  k_pk_bins<<<grid, kT, 0, s>>>(b.spec, n, fft_pitch(n), deconv, ctx->red_result + 2, nbins, acc);
-  PM_HIP(ctx, hipGetLastError());
-  std::vector<double> h(3 * (size_t)nbins);
-  PM_HIP(ctx, hipMemcpyAsync(h.data(), acc, sizeof(double) * 3 * nbins, hipMemcpyDeviceToHost, s));
-  PM_HIP(ctx, hipStreamSynchronize(s));
-  for (int b2 = 0; b2 < nbins; ++b2) {
-    const double c = h[3 * b2 + 2];
-    pk[b2] = c > 0.0 ? h[3 * b2] / c : 0.0;
-    if (kmean) kmean[b2] = c > 0.0 ? h[3 * b2 + 1] / c : 0.0;
-    if (nmodes) nmodes[b2] = (int64_t)std::llround(c);
-  }
   return PM_OK;
 }
 

@@ -56,7 +56,7 @@ struct pm_ctx {
                          // FFT solve's input
   // FFT spectrum (lazy)
   void *spec;            // complex float [n][n][fft_pitch(n)]
-  void *spec2;           // three spectra of the Fourier-space force (lazy)
+  void *spec2;           // two more spectra of the Fourier-space force (lazy)
   float2 *twiddle;       // [n] e^{-2 pi i m / n}, m = 0 .. n-1
   float *fft_tab;        // [3n] per-axis tables: k^2 part, window part, k_d
   // counting sort (lazy)
@@ -251,24 +251,23 @@ hipError_t launch_qumond_source(const float *phin, int n, float g0, int family, 
 
 // fft.hip
 struct FftBufs {
-  float2 *spec, *spec2;  // half spectra [n][n][fft_pitch(n)] (spec2: three, PM_FFT_FULL only)
+  float2 *spec, *spec2;  // half spectra [n][n][fft_pitch(n)] (spec2: two, PM_FFT_FULL only)
   float2 *twiddle;       // [n]
   float *tab;            // [3n]
 };
-#ifndef PM_FFT_TL
-#define PM_FFT_TL 4096  // complex elements an FFT workgroup holds in LDS
-#endif
-// row pitch of the half spectrum: n/2 + 1 columns rounded up to a whole column tile
-// (PM_FFT_TL / n columns)
-constexpr int fft_pitch_of(int n) {
-  return ((n / 2 + 1 + PM_FFT_TL / n - 1) / (PM_FFT_TL / n)) * (PM_FFT_TL / n);
-}
+// row pitch of the half spectrum: n/2 + 1 columns rounded up to 16 (128 bytes)
+constexpr int fft_pitch_of(int n) { return (n / 2 + 1 + 15) / 16 * 16; }
 int fft_pitch(int n);
 size_t fft_spec_elems(int n);
 // kind: a pm_fft_kernel; out: phi [n^3] (PM_FFT_GREEN, PM_FFT_7PT) or g [n^3 * 3] (PM_FFT_FULL);
-// mean (device, may be NULL): subtracted from rho before the transform
-hipError_t fft_run(const FftBufs &b, int n, const float *rho, const float *mean, float coef,
-                   int deconv, int kind, float *out, hipStream_t s);
+// the mean of rho is subtracted before the transform: mean (device), or, where it is NULL,
+// summed into partial (fft_mean_blocks(n) doubles of device scratch)
+hipError_t fft_run(const FftBufs &b, int n, const float *rho, const float *mean, double *partial,
+                   float coef, int deconv, int kind, float *out, hipStream_t s);
+int fft_mean_blocks(int n);  // at most RED_BLOCKS
+// the context's spectrum, twiddles and tables (once), for the solvers and the estimator
+hipError_t fft_alloc(pm_ctx *ctx);
+int spectrum_pitch(int n);   // spectrum.hip: row pitch of the estimator's half spectrum
 // separate passes over one grid: the twiddles and tables of b for an n^3 grid; the
 // forward transform of the real grid x (mean subtracted when given) into b.spec (full
 // half spectrum, unnormalised); the inverse of b.spec (consumed) into out[(p * stride) +

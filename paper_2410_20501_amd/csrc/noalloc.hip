@@ -14,11 +14,10 @@ namespace {
 constexpr int kNoAllocMaxN = 128;
 constexpr int kNoAllocMaxDevices = 64;
 // spectrum of the largest grid (smaller power-of-two grids need fewer elements), then n
-// twiddles, 3n table floats, the partial sums of the mean (2 doubles per reduction
-// block) and its result (4 doubles, then the FP32 mean), each part 256-byte aligned
-// (32 float2)
+// twiddles, 3n table floats and the partial sums of the mean (a double per reduction
+// block), each part 256-byte aligned (32 float2)
 constexpr size_t kNoAllocSpec = (size_t)kNoAllocMaxN * kNoAllocMaxN * fft_pitch_of(kNoAllocMaxN);
-constexpr size_t kNoAllocRed = 2 * RED_BLOCKS + 32;
+constexpr size_t kNoAllocRed = RED_BLOCKS;
 constexpr size_t kNoAllocElems = kNoAllocSpec + kNoAllocMaxN + 2 * kNoAllocMaxN + kNoAllocRed + 64;
 
 static __device__ __align__(256) float2 scratch[kNoAllocElems];
@@ -54,10 +53,7 @@ extern "C" int pm_solve_fft_noalloc(const float *rho, int n, float coef, int dec
   if (red_off + kNoAllocRed > kNoAllocElems) return PM_ERR_SHAPE;
   FftBufs b{base, nullptr, base + tw_off, reinterpret_cast<float *>(base + tab_off)};
   double *partial = reinterpret_cast<double *>(base + red_off);
-  double *result = partial + 2 * RED_BLOCKS;
-  float *mean = reinterpret_cast<float *>(result + 4);
-  const hipStream_t s = (hipStream_t)stream;
-  hipError_t e = launch_sum_moments(rho, (int64_t)n * n * n, partial, result, mean, s);
-  if (e == hipSuccess) e = fft_run(b, n, rho, mean, coef, deconv, PM_FFT_GREEN, phi, s);
+  const hipError_t e = fft_run(b, n, rho, nullptr, partial, coef, deconv, PM_FFT_GREEN, phi,
+                               (hipStream_t)stream);
   return e == hipSuccess ? PM_OK : PM_ERR_HIP;
 }
