@@ -515,9 +515,10 @@ int pm_ic_vjp(pm_ctx *ctx, const float *pos_bar, const float *vel_bar, int64_t n
  *     truncated back (free of aliasing for the quadratic and cubic terms; the paper uses
  *     Orszag's 3/2 rule, which this equals for the quadratic ones); 0: on the n grid;
  *   pos [np][3]: box units (cell == NULL) or in-cell offsets with cell [np]; vel [np][3].
- * n must be a power of two (2n <= 1024 with dealiasing). The call allocates its working
- * fields (up to 12 grids of (2n)^3 floats at third order) for its own duration and
- * synchronises the stream before it returns. Errors: PM_ERR_ARG, PM_ERR_SHAPE,
+ * n must be a power of two (2n <= 1024 with dealiasing). The working fields (up to 13 grids
+ * of (2n)^3 floats at third order) are allocated by the call; up to 2 GiB of them stay with
+ * the context for its next call, more are released before the call returns. It synchronises
+ * the stream before it returns. Errors: PM_ERR_ARG, PM_ERR_SHAPE,
  * PM_ERR_NOMEM, PM_ERR_HIP. */
 int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab,
               const double *p_tab, int order, int dealias, double a0, float *pos,

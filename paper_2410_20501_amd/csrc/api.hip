@@ -605,6 +605,7 @@ void pm_destroy(pm_ctx *ctx) {
   fr(ctx->spec2);
   fr(ctx->twiddle);
   fr(ctx->fft_tab);
+  ic_scratch_free(ctx->ic);
   fr(ctx->cell_count);
   fr(ctx->perm);
   fr(ctx->pcell);

@@ -87,12 +87,10 @@ __global__ __launch_bounds__(256) void k_rows_r2c(const float *__restrict__ x, f
   if (t == 0) dst[L] = last;
 }
 
-// Pass E: X[0..n/2] -> x[0..n) (unnormalised: the 1/n^3 is in G). The output element of
-// row r and position m goes to x[(r n + m) stride + comp].
+// Pass E: X[0..n/2] -> x[0..n) (unnormalised: the 1/n^3 is in G).
 template <int L>
 __global__ __launch_bounds__(256) void k_rows_c2r(const float2 *__restrict__ spec, float *__restrict__ x,
-                                                  int P, const float2 *__restrict__ tw, int stride,
-                                                  int comp) {
+                                                  int P, const float2 *__restrict__ tw) {
   using S = Split<L>;
   using R = RowShape<L>;
   constexpr int n = 2 * L;
@@ -109,18 +107,9 @@ __global__ __launch_bounds__(256) void k_rows_c2r(const float2 *__restrict__ spe
   }
   rows<L, true>(v, lds + r * R::PITCH, t, tw, 2);
   if (!live) return;
-  if (stride == 1) {
-    float2 *dst = reinterpret_cast<float2 *>(x + row * n);
+  float2 *dst = reinterpret_cast<float2 *>(x + row * n);
 #pragma unroll
-    for (int m = 0; m < S::N1; ++m) dst[t + S::N2 * m] = v[m];
-  } else {
-#pragma unroll
-    for (int m = 0; m < S::N1; ++m) {
-      float *dst = x + (row * n + 2 * (t + S::N2 * m)) * stride + comp;
-      dst[0] = v[m].x;
-      dst[stride] = v[m].y;
-    }
-  }
+  for (int m = 0; m < S::N1; ++m) dst[t + S::N2 * m] = v[m];
 }
 
 // Pass E of FULL_FFT: the three components of a row, from the spectra of the i and j
@@ -161,10 +150,10 @@ __global__ __launch_bounds__(256) void k_rows_c2r3(const float2 *__restrict__ sx
   if (!live) return;
 #pragma unroll
   for (int m = 0; m < S::N1; ++m) {
-    float2 *dst = reinterpret_cast<float2 *>(x + (row * n + 2 * (t + S::N2 * m)) * 3);
-    dst[0] = make_float2(v[0][m].x, v[1][m].x);
-    dst[1] = make_float2(v[2][m].x, v[0][m].y);
-    dst[2] = make_float2(v[1][m].y, v[2][m].y);
+    Pair4 *dst = reinterpret_cast<Pair4 *>(x + (row * n + 2 * (t + S::N2 * m)) * 3);
+    dst[0] = Pair4{v[0][m].x, v[1][m].x};
+    dst[1] = Pair4{v[2][m].x, v[0][m].y};
+    dst[2] = Pair4{v[1][m].y, v[2][m].y};
   }
 }
 
@@ -325,8 +314,8 @@ struct Forward {  // pass A
 
 struct Backward {  // pass E
   template <int N>
-  static void run(hipStream_t s, const FftBufs &b, const float2 *spec, float *x, int stride, int comp) {
-    k_rows_c2r<N / 2><<<row_blocks<N>(), 256, 0, s>>>(spec, x, fft_pitch_of(N), b.twiddle, stride, comp);
+  static void run(hipStream_t s, const FftBufs &b, const float2 *spec, float *x) {
+    k_rows_c2r<N / 2><<<row_blocks<N>(), 256, 0, s>>>(spec, x, fft_pitch_of(N), b.twiddle);
   }
 };
 
@@ -376,8 +365,7 @@ hipError_t fft_run(const FftBufs &b, int n, const float *rho, const float *mean,
   if (kind != PM_FFT_FULL) {
     run_cols<0, 1>(n, s, b, spec, spec, nullptr, scale);
     run_cols<1, 2>(n, s, b, spec, spec, nullptr, scale);
-    by_size<Backward, hipStream_t, const FftBufs &, const float2 *, float *, int, int>(n, s, b, spec, out,
-                                                                                       1, 0);
+    by_size<Backward, hipStream_t, const FftBufs &, const float2 *, float *>(n, s, b, spec, out);
     return hipGetLastError();
   }
   // the force in Fourier space: the potential's spectrum in spec, the i and j components'
@@ -394,21 +382,6 @@ hipError_t fft_run(const FftBufs &b, int n, const float *rho, const float *mean,
 hipError_t fft_tables(const FftBufs &b, int n, int deconv, int kind, hipStream_t s) {
   k_fft_prepare<<<(n + RED_THREADS - 1) / RED_THREADS, RED_THREADS, 0, s>>>(b.twiddle, b.tab, n, deconv, kind,
                                                                             nullptr, 0, nullptr);
-  return hipGetLastError();
-}
-
-hipError_t fft_forward(const FftBufs &b, int n, const float *x, const float *mean, hipStream_t s) {
-  by_size<Forward, hipStream_t, const FftBufs &, const float *, Mean>(n, s, b, x, Mean{mean, nullptr, 0});
-  run_cols<1, 0>(n, s, b, b.spec, b.spec, nullptr, 0.0f);
-  run_cols<0, 0>(n, s, b, b.spec, b.spec, nullptr, 0.0f);
-  return hipGetLastError();
-}
-
-hipError_t fft_inverse(const FftBufs &b, int n, float *out, int stride, int comp, hipStream_t s) {
-  run_cols<0, 2>(n, s, b, b.spec, b.spec, nullptr, 0.0f);
-  run_cols<1, 2>(n, s, b, b.spec, b.spec, nullptr, 0.0f);
-  by_size<Backward, hipStream_t, const FftBufs &, const float2 *, float *, int, int>(n, s, b, b.spec, out,
-                                                                                     stride, comp);
   return hipGetLastError();
 }
 

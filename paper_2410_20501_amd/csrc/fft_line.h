@@ -132,6 +132,14 @@ struct RowShape {
   static constexpr int LDS = R * PITCH;  // float2
 };
 
+// The threads of a line are N2 <= 16 neighbours, all of one wave, whose LDS accesses are
+// performed in order: the exchange only has to keep the compiler from moving them.
+__device__ __forceinline__ void line_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // one transform of the block's lines, in place (twiddles W_N^m = tw[m step])
 template <int N, bool INV>
 __device__ __forceinline__ void rows(float2 (&x)[Split<N>::N1], float2 *line, int t,
@@ -139,10 +147,10 @@ __device__ __forceinline__ void rows(float2 (&x)[Split<N>::N1], float2 *line, in
   using S = Split<N>;
   pm_dft::Dft<S::N1, INV>::run(x);
   twiddle<N, INV>(x, t, tw, step);
-  __syncthreads();
+  line_sync();
 #pragma unroll
   for (int k = 0; k < S::N1; ++k) line[k * (S::N2 + 1) + t] = x[k];
-  __syncthreads();
+  line_sync();
 #pragma unroll
   for (int h = 0; h < S::Q; ++h)
 #pragma unroll
@@ -158,10 +166,10 @@ __device__ __forceinline__ void real_forward(float2 (&x)[Split<N>::N1], float2 &
                                              const float2 *__restrict__ tw) {
   using S = Split<N>;
   rows<N, false>(x, line, t, tw, 2);
-  __syncthreads();
+  line_sync();
 #pragma unroll
   for (int m = 0; m < S::N1; ++m) line[t + S::N2 * m] = x[m];
-  __syncthreads();
+  line_sync();
   const float2 z0 = x[0];
 #pragma unroll
   for (int m = 0; m < S::N1; ++m) {

@@ -15,15 +15,29 @@
 // m = n (dealias 0) or m = 2n (dealias 1: zero-padded spectra, free of aliasing for the
 // quadratic and cubic terms) cells per side and truncated back to the band of the n grid.
 //
-// Every spectral step is one elementwise pass k_spec_op from one half spectrum to
-// another (the two grids may differ: padding and truncation are index maps) followed
-// by the inverse passes of fft.hip, or a forward transform of a real product field.
+// Everything is band limited: |m_d| < n/2 on every axis (the n grid's Nyquist planes are
+// dropped). A spectrum is stored as its band, [n][n][Pb] with Pb = n/2 rounded up to 16
+// (the rows of m_d = n/2 are ignored), and the transforms to and from the product grid
+// take and leave only the band: the inverse passes along i, j, k start from n n/2 columns,
+// m n/2 columns and m^2 rows. Wavenumber factors are constant along the other axes, so the
+// six second derivatives need three transforms along i (of 1, k_x, k_x^2 times phi) and six
+// along j; the k_z factors multiply the rows as they are read. At second order the rows of
+// the six fields meet in registers, where their product is formed and transformed back: no
+// field of the product grid goes to memory. At third order the twelve fields do (the
+// products mix both Hessians). The displacements and the velocities are one vector
+// transform each of the summed orders, written as whole particles with the lattice added.
+//
+// Bound by vector instructions and, above 128^3, by memory. Measured at second order with
+// dealiasing, kernels of a call: 128^3 1236 -> 370 us, 256^3 2970 us; a 128^3 call 4840 -> 394
+// us (two thirds of it were allocations, now kept: Scratch).
 #include <cmath>
 #include <vector>
 
-#include "internal.h"
+#include "fft_line.h"
 
 namespace {
+
+using namespace pm_fft;
 
 constexpr int kT = 256;
 constexpr double kTwoPi = 6.283185307179586;
@@ -31,16 +45,6 @@ constexpr double kTwoPi = 6.283185307179586;
 inline unsigned blocks_for(int64_t count, int threads) {
   return (unsigned)((count + threads - 1) / threads);
 }
-
-// dst = scale * (i)^imag * k_ka * k_kb / k^2 (inv_k2) * sqrt(P(|k|)) (pk) * src
-struct SpecOp {
-  float scale;
-  int ka, kb;      // axes of the k factors (-1: none)
-  int inv_k2;      // divide by k^2 (the k = 0 mode becomes 0)
-  int imag;        // multiply by i
-  int pk;          // multiply by sqrt(P(|k|)) from the table
-  int accumulate;  // dst += instead of dst =
-};
 
 // log-log interpolation of the table, constant beyond its ends
 __device__ double table_sqrt_p(double k, const double *__restrict__ lk, const double *__restrict__ lp,
@@ -58,47 +62,307 @@ __device__ double table_sqrt_p(double k, const double *__restrict__ lk, const do
   return exp(0.5 * (lp[lo] + t * (lp[hi] - lp[lo])));
 }
 
-// One thread per mode of the destination half spectrum (gd cells per side, pitch Pd).
-// A mode is kept when it lies inside the band of the n grid, |m_d| < n/2 on every axis
-// (so the n grid's Nyquist planes are dropped); its source is the same wavevector on the
-// source grid (gs cells per side, pitch Ps).
-__global__ __launch_bounds__(kT) void k_spec_op(const float2 *__restrict__ src, int gs, int Ps,
-                                                float2 *__restrict__ dst, int gd, int Pd, int nband,
-                                                SpecOp op, const double *__restrict__ lk,
-                                                const double *__restrict__ lp, int nt) {
-  const int hz = gd / 2 + 1;
-  const int64_t count = (int64_t)gd * gd * hz;
-  const int64_t t = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (t >= count) return;
-  const int iz = (int)(t % hz);
-  const int iy = (int)((t / hz) % gd);
-  const int ix = (int)(t / ((int64_t)hz * gd));
-  const int mx = ix < gd / 2 ? ix : ix - gd;
-  const int my = iy < gd / 2 ? iy : iy - gd;
-  const int mz = iz;
-  const int h = nband / 2;
-  const bool keep = mx > -h && mx < h && my > -h && my < h && mz < h;
-  float2 *out = dst + ((int64_t)ix * gd + iy) * Pd + iz;
-  float2 r = make_float2(0.f, 0.f);
-  if (keep) {
-    const int sx = mx >= 0 ? mx : mx + gs, sy = my >= 0 ? my : my + gs;
-    const float2 v = src[((int64_t)sx * gs + sy) * Ps + mz];
-    const double k[3] = {kTwoPi * mx, kTwoPi * my, kTwoPi * mz};
-    const double k2 = k[0] * k[0] + k[1] * k[1] + k[2] * k[2];
-    double mult = (double)op.scale;
-    if (op.ka >= 0) mult *= k[op.ka];
-    if (op.kb >= 0) mult *= k[op.kb];
-    if (op.inv_k2) mult = k2 > 0.0 ? mult / k2 : 0.0;
-    if (op.pk) mult = k2 > 0.0 ? mult * table_sqrt_p(sqrt(k2), lk, lp, nt) : 0.0;
-    const float fm = (float)mult;
-    r = op.imag ? make_float2(-fm * v.y, fm * v.x) : make_float2(fm * v.x, fm * v.y);
+// The place of a thread's column in a pass over 16-column tiles: line element t + N2 m.
+template <int M>
+struct Place {
+  int c, t, o, kz, outer, base;
+  __device__ __forceinline__ Place(int tiles) {
+    using S = Split<M>;
+    using C = ColShape<M>;
+    c = threadIdx.x % kCols;
+    const int u = threadIdx.x / kCols;
+    t = u % S::N2;
+    o = u / S::N2;
+    const unsigned b = xcd_block(blockIdx.x, gridDim.x);
+    kz = (int)(b % tiles) * kCols + c;
+    outer = (int)(b / tiles) * C::OUT + o;
+    base = o * C::LINE + c;
   }
-  if (op.accumulate) {
-    const float2 o = *out;
-    *out = make_float2(o.x + r.x, o.y + r.y);
-  } else {
-    *out = r;
+};
+
+// wavenumber of element e of a length-M axis and its place in the band of n (-1: outside)
+template <int M>
+__device__ __forceinline__ int signed_of(int e) {
+  return e < M / 2 ? e : e - M;
+}
+__device__ __forceinline__ int band_of(int m, int n) {
+  const int h = n / 2;
+  return m > -h && m < h ? (m < 0 ? m + n : m) : -1;
+}
+
+__device__ __forceinline__ float power(float k, int p) { return p == 0 ? 1.0f : (p == 1 ? k : k * k); }
+
+// sums of c[set][j] f[j] over the band spectra given
+struct Combo {
+  const float2 *f[4];
+  float c[2][4];
+  int count;
+};
+
+// sqrt(N P(k)) of every |m|^2 = t that the band holds (0 at 0): 3 (n/2)^2 logarithms and
+// exponentials in FP64 instead of n^3 / 2 (128^3: the pass that applies them 28.6 -> 9.7 us and this one 4.7)
+__global__ __launch_bounds__(kT) void k_amplitude(const double *__restrict__ lk,
+                                                  const double *__restrict__ lp, int nt, float scale,
+                                                  int count, float *__restrict__ amp) {
+  const int t = blockIdx.x * kT + threadIdx.x;
+  if (t < count) amp[t] = t ? (float)(scale * table_sqrt_p(kTwoPi * sqrt((double)t), lk, lp, nt)) : 0.0f;
+}
+
+// The k factors are formed from the integers m = k / (2 pi), exact in FP32, so that a factor
+// m_i m_j / m^2 costs three roundings; the powers of 2 pi left over go into the weights.
+
+// Inverse along i: U = (sum of the spectra) (/ m^2 with DIV), then for o = 0 .. NOUT - 1
+// out_o[i][ky][kz] = the transform of m_x^o U. With a grid of two in y, a second sum goes
+// `set` values further on (the passes after it, likewise).
+template <int M, int NOUT, bool DIV>
+__global__ __launch_bounds__(ColShape<M>::NT) void k_band_inv_x(Combo in, float2 *o0, float2 *o1,
+                                                                float2 *o2, int n, int Pb, size_t set,
+                                                                const float2 *__restrict__ tw) {
+  using S = Split<M>;
+  __shared__ __align__(16) float lds[ColShape<M>::LDS];
+  const Place<M> p(Pb / kCols);
+  set *= blockIdx.y;
+  const int my = p.outer < n / 2 ? p.outer : p.outer - n;
+  const bool live = p.kz < n / 2 && p.outer != n / 2;
+  const int yz = my * my + p.kz * p.kz;
+  float2 u[S::N1];
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) {
+    const int mx = signed_of<M>(p.t + S::N2 * m), sx = band_of(mx, n);
+    float2 v = make_float2(0.f, 0.f);
+    if (live && sx >= 0) {
+      const int64_t at = ((int64_t)sx * n + p.outer) * Pb + p.kz;
+      for (int j = 0; j < in.count; ++j) {
+        const float2 f = in.f[j][at];
+        v = make_float2(fmaf(in.c[blockIdx.y][j], f.x, v.x), fmaf(in.c[blockIdx.y][j], f.y, v.y));
+      }
+      if (DIV) {
+        const int m2 = mx * mx + yz;
+        const float r = m2 > 0 ? 1.0f / (float)m2 : 0.0f;
+        v = make_float2(v.x * r, v.y * r);
+      }
+    }
+    u[m] = v;
   }
+  float2 *out[3] = {o0, o1, o2};
+#pragma unroll
+  for (int o = 0; o < NOUT; ++o) {
+    float2 x[S::N1];
+#pragma unroll
+    for (int m = 0; m < S::N1; ++m) {
+      const float f = power((float)signed_of<M>(p.t + S::N2 * m), o);
+      x[m] = make_float2(f * u[m].x, f * u[m].y);
+    }
+    cols<M, true>(x, lds, p.base, p.t, tw);
+    if (p.kz < n / 2)
+#pragma unroll
+      for (int m = 0; m < S::N1; ++m)
+        out[o][set + ((size_t)(p.t + S::N2 * m) * n + p.outer) * Pb + p.kz] = x[m];
+  }
+}
+
+// Inverse along j of the planes i = x0 .. : out_o[i - x0][j][kz] = the transform of m_y^o in.
+template <int M, int NOUT>
+__global__ __launch_bounds__(ColShape<M>::NT) void k_band_inv_y(const float2 *__restrict__ in, float2 *o0,
+                                                                float2 *o1, float2 *o2, int x0, int n,
+                                                                int Pb, size_t set, const float2 *__restrict__ tw) {
+  using S = Split<M>;
+  __shared__ __align__(16) float lds[ColShape<M>::LDS];
+  const Place<M> p(Pb / kCols);
+  const bool live = p.kz < n / 2;
+  set *= blockIdx.y;
+  float2 u[S::N1];
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) {
+    const int sy = band_of(signed_of<M>(p.t + S::N2 * m), n);
+    u[m] = live && sy >= 0 ? in[set + ((size_t)(x0 + p.outer) * n + sy) * Pb + p.kz] : make_float2(0.f, 0.f);
+  }
+  float2 *out[3] = {o0, o1, o2};
+#pragma unroll
+  for (int o = 0; o < NOUT; ++o) {
+    float2 x[S::N1];
+#pragma unroll
+    for (int m = 0; m < S::N1; ++m) {
+      const float f = power((float)signed_of<M>(p.t + S::N2 * m), o);
+      x[m] = make_float2(f * u[m].x, f * u[m].y);
+    }
+    cols<M, true>(x, lds, p.base, p.t, tw);
+    if (live)
+#pragma unroll
+      for (int m = 0; m < S::N1; ++m)
+        out[o][set + ((size_t)p.outer * M + p.t + S::N2 * m) * Pb + p.kz] = x[m];
+  }
+}
+
+// Forward along j of the planes x0 .. : the band of the transform to out[i][ky][kz].
+template <int M>
+__global__ __launch_bounds__(ColShape<M>::NT) void k_band_fwd_y(const float2 *__restrict__ in,
+                                                                float2 *__restrict__ out, int x0, int n,
+                                                                int Pb, const float2 *__restrict__ tw) {
+  using S = Split<M>;
+  __shared__ __align__(16) float lds[ColShape<M>::LDS];
+  const Place<M> p(Pb / kCols);
+  const bool live = p.kz < n / 2;
+  float2 x[S::N1];
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m)
+    x[m] = live ? in[((int64_t)p.outer * M + p.t + S::N2 * m) * Pb + p.kz] : make_float2(0.f, 0.f);
+  cols<M, false>(x, lds, p.base, p.t, tw);
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) {
+    const int sy = band_of(signed_of<M>(p.t + S::N2 * m), n);
+    if (live && sy >= 0) out[((int64_t)(x0 + p.outer) * n + sy) * Pb + p.kz] = x[m];
+  }
+}
+
+// Forward along i: the band of the transform times scale or, with a table of them,
+// the amplitude at |m|^2.
+template <int M>
+__global__ __launch_bounds__(ColShape<M>::NT) void k_band_fwd_x(const float2 *__restrict__ in,
+                                                                float2 *__restrict__ out, int n, int Pb,
+                                                                float scale,
+                                                                const float2 *__restrict__ tw,
+                                                                const float *__restrict__ amp) {
+  using S = Split<M>;
+  __shared__ __align__(16) float lds[ColShape<M>::LDS];
+  const Place<M> p(Pb / kCols);
+  const bool live = p.kz < n / 2 && p.outer != n / 2;
+  float2 x[S::N1];
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m)
+    x[m] = live ? in[((int64_t)(p.t + S::N2 * m) * n + p.outer) * Pb + p.kz] : make_float2(0.f, 0.f);
+  cols<M, false>(x, lds, p.base, p.t, tw);
+  const int my = p.outer < n / 2 ? p.outer : p.outer - n;
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) {
+    const int mx = signed_of<M>(p.t + S::N2 * m), sx = band_of(mx, n);
+    if (!live || sx < 0) continue;
+    const float f = amp ? amp[mx * mx + my * my + p.kz * p.kz] : scale;
+    out[((int64_t)sx * n + p.outer) * Pb + p.kz] = make_float2(f * x[m].x, f * x[m].y);
+  }
+}
+
+// One row of a band spectrum (m_z < h), times m_z^kp and, with rot, times i: the packed line
+// whose inverse DFT is the real row.
+template <int L>
+__device__ __forceinline__ void band_row(const float2 *__restrict__ s, int h, int kp, bool rot, int t,
+                                         const float2 *__restrict__ tw, float2 (&v)[Split<L>::N1]) {
+  using S = Split<L>;
+  auto get = [&](int k) {
+    if (k >= h) return make_float2(0.f, 0.f);
+    const float f = power((float)k, kp);
+    const float2 a = s[k];
+    return rot ? make_float2(-f * a.y, f * a.x) : make_float2(f * a.x, f * a.y);
+  };
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) {
+    const int k = t + S::N2 * m;
+    v[m] = real_join(get(k), get(L - k), tw[k]);
+  }
+}
+
+// the band of a transformed row to memory
+template <int L>
+__device__ __forceinline__ void store_band(float2 *__restrict__ dst, int h, int t,
+                                           const float2 (&v)[Split<L>::N1]) {
+  using S = Split<L>;
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m)
+    if (t + S::N2 * m < h) dst[t + S::N2 * m] = v[m];
+}
+
+template <int L>
+struct RowPlace {
+  int t, r;
+  int64_t row;
+  __device__ __forceinline__ RowPlace() {
+    t = threadIdx.x % Split<L>::N2;
+    r = threadIdx.x / Split<L>::N2;
+    row = (int64_t)xcd_block(blockIdx.x, gridDim.x) * RowShape<L>::R + r;
+  }
+};
+
+// rows of a real grid -> band rows
+template <int L>
+__global__ __launch_bounds__(256) void k_rows_to_band(const float *__restrict__ x, float2 *__restrict__ out,
+                                                      int64_t rows_n, int h, int Pb,
+                                                      const float2 *__restrict__ tw) {
+  using S = Split<L>;
+  __shared__ float2 lds[RowShape<L>::LDS];
+  const RowPlace<L> p;
+  const bool live = p.row < rows_n;
+  const float2 *src = reinterpret_cast<const float2 *>(x + (live ? p.row : 0) * 2 * L);
+  float2 v[S::N1], last;
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) v[m] = src[p.t + S::N2 * m];
+  real_forward<L>(v, last, lds + p.r * RowShape<L>::PITCH, p.t, tw);
+  if (live) store_band<L>(out + p.row * Pb, h, p.t, v);
+}
+
+// band rows (times m_z^kp) -> rows of a real grid
+template <int L>
+__global__ __launch_bounds__(256) void k_band_to_rows(const float2 *__restrict__ in, float *__restrict__ x,
+                                                      int64_t rows_n, int h, int Pb, int kp,
+                                                      const float2 *__restrict__ tw) {
+  using S = Split<L>;
+  __shared__ float2 lds[RowShape<L>::LDS];
+  const RowPlace<L> p;
+  const bool live = p.row < rows_n;
+  float2 v[S::N1];
+  band_row<L>(in + (live ? p.row : 0) * Pb, h, kp, false, p.t, tw, v);
+  rows<L, true>(v, lds + p.r * RowShape<L>::PITCH, p.t, tw, 2);
+  if (!live) return;
+  float2 *dst = reinterpret_cast<float2 *>(x + p.row * 2 * L);
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) dst[p.t + S::N2 * m] = v[m];
+}
+
+// The six second derivatives' band rows -> the band rows of the second-order source
+// phi_xx (phi_yy + phi_zz) + phi_yy phi_zz - phi_xy^2 - phi_xz^2 - phi_yz^2. f: the fields
+// xx, yy, zz, xy, xz, yz before their powers of m_z, `field` values apart; out may be the
+// first of them (a block reads its rows whole before it writes them).
+// A block takes 32 / N2 rows: 6 x 32 threads transform the six fields, then the first 32
+// form the product and transform it back while the block's other waves have ended. Half
+// its time is vector instructions (65 a value). Against one thread group per row that does
+// the seven transforms in turn, which needs 256 registers (spills at lines of 512):
+// 128^2 lines of 64: 17 (18) us, 128 256 lines of 128: 80 (74), 32 512 of 256: 72 (83).
+template <int L>
+struct SourceShape {
+  using S = Split<L>;
+  static constexpr int R = 32 / S::N2, NT = 6 * 32, LDS = 6 * R * RowShape<L>::PITCH;
+};
+template <int L>
+__global__ __launch_bounds__(192) void k_rows_source2(const float2 *f, size_t field, float2 *out,
+                                                      int64_t rows_n, int h, int Pb,
+                                                      const float2 *__restrict__ tw) {
+  using S = Split<L>;
+  using B = SourceShape<L>;
+  constexpr int PITCH = RowShape<L>::PITCH;
+  __shared__ float2 lds[B::LDS];
+  const int t = threadIdx.x % S::N2, l = threadIdx.x / S::N2, q = l / B::R, r = l % B::R;
+  const int64_t row = (int64_t)xcd_block(blockIdx.x, gridDim.x) * B::R + r;
+  const bool live = row < rows_n;
+  float2 *line = lds + l * PITCH;
+  float2 v[S::N1];
+  band_row<L>(f + q * field + (size_t)(live ? row : 0) * Pb, h, q == 2 ? 2 : (q > 3 ? 1 : 0), false, t, tw,
+              v);
+  rows<L, true>(v, line, t, tw, 2);
+  line_sync();
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) line[t + S::N2 * m] = v[m];
+  __syncthreads();
+  if (q) return;
+#pragma unroll
+  for (int m = 0; m < S::N1; ++m) {
+    const float2 *e = line + t + S::N2 * m;
+    const float2 xx = v[m], yy = e[B::R * PITCH], zz = e[2 * B::R * PITCH];
+    const float2 xy = e[3 * B::R * PITCH], xz = e[4 * B::R * PITCH], yz = e[5 * B::R * PITCH];
+    v[m] = make_float2(xx.x * (yy.x + zz.x) + yy.x * zz.x - xy.x * xy.x - xz.x * xz.x - yz.x * yz.x,
+                       xx.y * (yy.y + zz.y) + yy.y * zz.y - xy.y * xy.y - xz.y * xz.y - yz.y * yz.y);
+  }
+  float2 last;
+  real_forward<L>(v, last, line, t, tw);
+  if (live) store_band<L>(out + row * Pb, h, t, v);
 }
 
 // The six distinct second derivatives of a potential, a[0..5] = xx, yy, zz, xy, xz, yz.
@@ -138,67 +402,251 @@ __global__ __launch_bounds__(kT) void k_lpt_source(Hess A, Hess B, int which, in
   out[p] = v;
 }
 
-// disp[p][comp] += cd f[p]; vel[p][comp] += cv f[p]
-__global__ __launch_bounds__(kT) void k_lpt_add(const float *__restrict__ f, int comp, float cd,
-                                                float cv, int64_t count, float *__restrict__ disp,
-                                                float *__restrict__ vel) {
-  const int64_t p = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (p >= count) return;
-  const float v = f[p];
-  disp[3 * p + comp] = fmaf(cd, v, disp[3 * p + comp]);
-  vel[3 * p + comp] = fmaf(cv, v, vel[3 * p + comp]);
+// Third order: the vector spectrum i m_d (sum of the potentials' sources) / m^2 plus
+// c (i m x R) / m^2, element by element over the band ([n][n][Pb]).
+__global__ __launch_bounds__(kT) void k_vector_spectrum(Combo pot, const float2 *__restrict__ rx,
+                                                        const float2 *__restrict__ ry,
+                                                        const float2 *__restrict__ rz, float c, int n,
+                                                        int Pb, float2 *__restrict__ ox,
+                                                        float2 *__restrict__ oy, float2 *__restrict__ oz) {
+  const int64_t at = (int64_t)blockIdx.x * kT + threadIdx.x;
+  if (at >= (int64_t)n * n * Pb) return;
+  const int kzi = (int)(at % Pb), iy = (int)(at / Pb % n), ix = (int)(at / ((int64_t)Pb * n));
+  const int mx = ix < n / 2 ? ix : ix - n, my = iy < n / 2 ? iy : iy - n;
+  if (kzi >= n / 2 || ix == n / 2 || iy == n / 2) return;
+  const float kx = (float)mx, ky = (float)my, kz = (float)kzi;
+  const int m2 = mx * mx + my * my + kzi * kzi;
+  const float r = m2 > 0 ? 1.0f / (float)m2 : 0.0f;
+  float2 s = make_float2(0.f, 0.f);
+  for (int j = 0; j < pot.count; ++j) {
+    const float2 f = pot.f[j][at];
+    s = make_float2(fmaf(pot.c[0][j], f.x, s.x), fmaf(pot.c[0][j], f.y, s.y));
+  }
+  const float2 X = rx[at], Y = ry[at], Z = rz[at];
+  auto put = [&](float2 *o, float k, float2 a, float ka, float2 b, float kb) {
+    // i r [k s + c (ka a - kb b)]
+    const float re = k * s.x + c * (ka * a.x - kb * b.x), im = k * s.y + c * (ka * a.y - kb * b.y);
+    o[at] = make_float2(-r * im, r * re);
+  };
+  put(ox, kx, Z, ky, Y, kz);
+  put(oy, ky, X, kz, Z, kx);
+  put(oz, kz, Y, kx, X, ky);
 }
 
-// Particle p = (i n + j) n + k starts at the cell centre q = ((i, j, k) + 1/2) / n;
-// pos holds its displacement on entry and the position on exit: box units wrapped into
-// [0, 1) (cell == NULL), or the in-cell offset with the cell index carried.
-__global__ __launch_bounds__(kT) void k_lpt_finish(float *__restrict__ pos,
-                                                   int32_t *__restrict__ cell, int n,
-                                                   int64_t count) {
-  const int64_t p = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (p >= count) return;
-  const int ijk[3] = {(int)(p / ((int64_t)n * n)), (int)((p / n) % n), (int)(p % n)};
-  int c[3];
+// The three components' band rows -> particles, whole: with `rot` the rows are those of
+// m_x phi, m_y phi and phi (times i, i and i m_z), else the vector's. pos != NULL: the
+// lattice point plus the field, box units wrapped into [0, 1) or, with cell, the in-cell
+// offset with the cell index carried; vel != NULL: vfac times the field. With a grid of two
+// in y the first field gives the positions, the second the velocities.
+template <int L>
+__global__ __launch_bounds__(256) void k_rows_particles(const float2 *__restrict__ sx,
+                                                        const float2 *__restrict__ sy,
+                                                        const float2 *__restrict__ sz, bool rot, int Pb,
+                                                        size_t set, const float2 *__restrict__ tw,
+                                                        float *__restrict__ pos, int32_t *__restrict__ cell,
+                                                        float *__restrict__ vel, float vfac) {
+  using S = Split<L>;
+  constexpr int n = 2 * L;
+  __shared__ float2 lds[RowShape<L>::LDS];
+  const RowPlace<L> p;
+  const bool live = p.row < (int64_t)n * n;
+  const size_t at = (size_t)(live ? p.row : 0) * Pb + blockIdx.y * set;
+  if (gridDim.y == 2) {
+    if (blockIdx.y == 0) vel = nullptr;
+    else pos = nullptr;
+  }
+  float2 *line = lds + p.r * RowShape<L>::PITCH;
+  float2 v[3][S::N1];
+  band_row<L>(sx + at, L, 0, rot, p.t, tw, v[0]);
+  band_row<L>(sy + at, L, 0, rot, p.t, tw, v[1]);
+  band_row<L>(sz + at, L, rot ? 1 : 0, rot, p.t, tw, v[2]);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) rows<L, true>(v[d], line, p.t, tw, 2);
+  if (!live) return;
+  const int i = (int)(p.row / n), j = (int)(p.row % n);
   const float fn = (float)n;
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const float dp = pos[3 * p + d];
-    if (!cell) {
-      float x = ((float)ijk[d] + 0.5f) / fn + dp;
-      x -= floorf(x);
-      pos[3 * p + d] = x >= 1.0f ? 0.0f : x;
-    } else {
-      const float s = fmaf(dp, fn, 0.5f);
-      float fl = floorf(s);
-      float o = s - fl;
-      if (o >= 1.0f) {
-        o = 0.0f;
-        fl += 1.0f;
-      }
-      int ci = (ijk[d] + (int)fl) % n;
-      c[d] = ci < 0 ? ci + n : ci;
-      pos[3 * p + d] = o;
+  for (int m = 0; m < S::N1; ++m) {
+    const int k0 = 2 * (p.t + S::N2 * m);
+    float f[2][3] = {{v[0][m].x, v[1][m].x, v[2][m].x}, {v[0][m].y, v[1][m].y, v[2][m].y}};
+    const int64_t q = p.row * n + k0;
+    if (vel) {
+      Pair4 *dst = reinterpret_cast<Pair4 *>(vel + 3 * q);
+      dst[0] = Pair4{vfac * f[0][0], vfac * f[0][1]};
+      dst[1] = Pair4{vfac * f[0][2], vfac * f[1][0]};
+      dst[2] = Pair4{vfac * f[1][1], vfac * f[1][2]};
     }
+    if (!pos) continue;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int ijk[3] = {i, j, k0 + e};
+      int c[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        if (!cell) {
+          float x = ((float)ijk[d] + 0.5f) / fn + f[e][d];
+          x -= floorf(x);
+          f[e][d] = x >= 1.0f ? 0.0f : x;
+        } else {
+          const float s = fmaf(f[e][d], fn, 0.5f);
+          float fl = floorf(s), o = s - fl;
+          if (o >= 1.0f) {
+            o = 0.0f;
+            fl += 1.0f;
+          }
+          const int ci = (ijk[d] + (int)fl) % n;
+          c[d] = ci < 0 ? ci + n : ci;
+          f[e][d] = o;
+        }
+      }
+      if (cell) cell[q + e] = (c[0] * n + c[1]) * n + c[2];
+    }
+    Pair4 *dst = reinterpret_cast<Pair4 *>(pos + 3 * q);
+    dst[0] = Pair4{f[0][0], f[0][1]};
+    dst[1] = Pair4{f[0][2], f[1][0]};
+    dst[2] = Pair4{f[1][1], f[1][2]};
   }
-  if (cell) cell[p] = (c[0] * n + c[1]) * n + c[2];
 }
 
-// Device scratch of one pm_ic_lpt call (allocated for the call and released after it).
-struct IcScratch {
-  std::vector<void *> owned;
-  hipError_t alloc(void **p, size_t bytes) {
-    const hipError_t e = hipMalloc(p, bytes);
-    if (e == hipSuccess) owned.push_back(*p);
-    return e;
+// ------------------------------------------------------------------ launches by size
+
+struct Grid {  // a transform size and the band it carries
+  int n, Pb;
+  const float2 *tw;
+  hipStream_t s;
+};
+
+template <int M>
+unsigned col_grid(const Grid &g, int outer) {
+  return (unsigned)(g.Pb / kCols * (outer / ColShape<M>::OUT));
+}
+template <int M>
+unsigned row_grid(int64_t rows_n) {
+  return (unsigned)((rows_n + RowShape<M / 2>::R - 1) / RowShape<M / 2>::R);
+}
+
+// the passes of one transform size M as a table of launches
+struct Passes {
+  // (a NULL output: fewer of them)
+  void (*inv_x)(const Grid &, const Combo &, float2 *, float2 *, float2 *, bool div, int sets);
+  void (*inv_y)(const Grid &, const float2 *, float2 *, float2 *, float2 *, int x0, int planes, int sets);
+  void (*fwd_y)(const Grid &, const float2 *, float2 *, int x0, int planes);
+  void (*fwd_x)(const Grid &, const float2 *, float2 *, float, const float *amp);
+  void (*to_band)(const Grid &, const float *, float2 *, int64_t rows_n);
+  void (*to_rows)(const Grid &, const float2 *, float *, int64_t rows_n, int kp);
+  void (*source2)(const Grid &, const float2 *, size_t field, float2 *, int64_t rows_n);
+  void (*particles)(const Grid &, const float2 *, const float2 *, const float2 *, bool rot, float *,
+                    int32_t *, float *, float, int sets);
+};
+
+template <int M>
+struct Launch {
+  static constexpr int NT = ColShape<M>::NT, L = M / 2;
+  static void inv_x(const Grid &g, const Combo &in, float2 *o0, float2 *o1, float2 *o2, bool div, int sets) {
+    const dim3 b(col_grid<M>(g, g.n), sets);
+    const size_t set = (size_t)g.n * g.n * g.Pb;
+    if (o2) k_band_inv_x<M, 3, true><<<b, NT, 0, g.s>>>(in, o0, o1, o2, g.n, g.Pb, set, g.tw);
+    else if (o1) k_band_inv_x<M, 2, true><<<b, NT, 0, g.s>>>(in, o0, o1, o2, g.n, g.Pb, set, g.tw);
+    else if (div) k_band_inv_x<M, 1, true><<<b, NT, 0, g.s>>>(in, o0, o1, o2, g.n, g.Pb, set, g.tw);
+    else k_band_inv_x<M, 1, false><<<b, NT, 0, g.s>>>(in, o0, o1, o2, g.n, g.Pb, set, g.tw);
   }
-  ~IcScratch() {
-    // queued work may still read the buffers (an early error return): wait for it
-    if (!owned.empty()) (void)hipDeviceSynchronize();
-    for (void *p : owned) (void)hipFree(p);
+  static void inv_y(const Grid &g, const float2 *in, float2 *o0, float2 *o1, float2 *o2, int x0, int planes,
+                    int sets) {
+    const dim3 b(col_grid<M>(g, planes), sets);
+    const size_t set = (size_t)g.n * g.n * g.Pb;
+    if (o2) k_band_inv_y<M, 3><<<b, NT, 0, g.s>>>(in, o0, o1, o2, x0, g.n, g.Pb, set, g.tw);
+    else if (o1) k_band_inv_y<M, 2><<<b, NT, 0, g.s>>>(in, o0, o1, o2, x0, g.n, g.Pb, set, g.tw);
+    else k_band_inv_y<M, 1><<<b, NT, 0, g.s>>>(in, o0, o1, o2, x0, g.n, g.Pb, set, g.tw);
+  }
+  static void fwd_y(const Grid &g, const float2 *in, float2 *out, int x0, int planes) {
+    k_band_fwd_y<M><<<col_grid<M>(g, planes), NT, 0, g.s>>>(in, out, x0, g.n, g.Pb, g.tw);
+  }
+  static void fwd_x(const Grid &g, const float2 *in, float2 *out, float scale, const float *amp) {
+    k_band_fwd_x<M><<<col_grid<M>(g, g.n), NT, 0, g.s>>>(in, out, g.n, g.Pb, scale, g.tw, amp);
+  }
+  static void to_band(const Grid &g, const float *x, float2 *out, int64_t rows_n) {
+    k_rows_to_band<L><<<row_grid<M>(rows_n), 256, 0, g.s>>>(x, out, rows_n, g.n / 2, g.Pb, g.tw);
+  }
+  static void to_rows(const Grid &g, const float2 *in, float *x, int64_t rows_n, int kp) {
+    k_band_to_rows<L><<<row_grid<M>(rows_n), 256, 0, g.s>>>(in, x, rows_n, g.n / 2, g.Pb, kp, g.tw);
+  }
+  static void source2(const Grid &g, const float2 *f, size_t field, float2 *out, int64_t rows_n) {
+    const unsigned b = (unsigned)((rows_n + SourceShape<L>::R - 1) / SourceShape<L>::R);
+    k_rows_source2<L><<<b, 192, 0, g.s>>>(f, field, out, rows_n, g.n / 2, g.Pb, g.tw);
+  }
+  static void particles(const Grid &g, const float2 *sx, const float2 *sy, const float2 *sz, bool rot,
+                        float *pos, int32_t *cell, float *vel, float vfac, int sets) {
+    const dim3 b(row_grid<M>((int64_t)M * M), sets);
+    k_rows_particles<L><<<b, 256, 0, g.s>>>(sx, sy, sz, rot, g.Pb, (size_t)g.n * g.n * g.Pb, g.tw, pos, cell,
+                                            vel, vfac);
+  }
+  static Passes table() { return {inv_x, inv_y, fwd_y, fwd_x, to_band, to_rows, source2, particles}; }
+};
+
+Passes passes_of(int m) {
+  switch (m) {
+    case 8: return Launch<8>::table();
+    case 16: return Launch<16>::table();
+    case 32: return Launch<32>::table();
+    case 64: return Launch<64>::table();
+    case 128: return Launch<128>::table();
+    case 256: return Launch<256>::table();
+    case 512: return Launch<512>::table();
+    default: return Launch<1024>::table();
+  }
+}
+
+// Device scratch of a call, one allocation carved up. A call takes the context's (which then
+// has none) and gives it back for the next one if it is at most kKeep; a larger one is
+// released before the call returns. (Twelve allocations and releases took two thirds of a
+// 128^3 call.)
+constexpr size_t kKeep = (size_t)2 << 30;
+
+struct Scratch {
+  pm_ctx *ctx;
+  IcScratch *buf = nullptr;
+  size_t used = 0;
+  bool idle = false;  // the work that reads it is known to have ended
+  template <class T>
+  T *take(size_t count) {  // before open(): adds up the sizes
+    T *p = buf ? reinterpret_cast<T *>((char *)buf->p + used) : nullptr;
+    used += (count * sizeof(T) + 255) / 256 * 256;
+    return p;
+  }
+  bool open() {
+    buf = __atomic_exchange_n(&ctx->ic, (IcScratch *)nullptr, __ATOMIC_ACQ_REL);
+    if (buf && buf->bytes < used) {
+      ic_scratch_free(buf);
+      buf = nullptr;
+    }
+    if (!buf) {
+      void *p = nullptr;
+      if (hipMalloc(&p, used) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+      }
+      buf = new IcScratch{p, used};
+    }
+    used = 0;
+    return true;
+  }
+  ~Scratch() {
+    if (!buf) return;
+    if (!idle) (void)hipDeviceSynchronize();  // an early error return: queued work may read it
+    IcScratch *none = nullptr;
+    if (buf->bytes > kKeep ||
+        !__atomic_compare_exchange_n(&ctx->ic, &none, buf, false, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED))
+      ic_scratch_free(buf);
   }
 };
 
 }  // namespace
+
+void ic_scratch_free(IcScratch *b) {
+  if (!b) return;
+  (void)hipFree(b->p);
+  delete b;
+}
 
 extern "C" {
 
@@ -226,129 +674,146 @@ int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab, co
                                       "with dealiasing)");
   const hipStream_t s = (hipStream_t)stream;
   const int64_t N = (int64_t)n * n * n, M = (int64_t)m * m * m;
-  IcScratch sc;
-  double *d_tab = nullptr;
-  float2 *spec_n = nullptr, *spec_d = nullptr, *spec_m = nullptr;
-  float2 *src_sp[6] = {};
-  float *fn_real = nullptr, *tmp_m = nullptr;
-  float *h1[6] = {}, *h2[6] = {};
-  float2 *tw_n = nullptr, *tw_m = nullptr;
-  float *tab_n = nullptr, *tab_m = nullptr;
-  const size_t en = fft_spec_elems(n), em = fft_spec_elems(m);
+  const int Pb = (n / 2 + 15) / 16 * 16;
+  const size_t band = (size_t)n * n * Pb, half = (size_t)m * n * Pb, plane = (size_t)m * Pb;
+  // planes of the product grid at a time: their six half-transformed fields stay cached
+  // (at most 128 MiB), a multiple of the lines a workgroup takes together
+  int chunk = m;
+  while (chunk > 8 && 6 * plane * chunk * sizeof(float2) > ((size_t)128 << 20)) chunk /= 2;
+  const int namp = 3 * (n / 2) * (n / 2);  // |m|^2 <= 3 (n/2 - 1)^2
   const int nsrc = order == 1 ? 0 : (order == 2 ? 1 : 6);
-  bool ok = sc.alloc((void **)&d_tab, sizeof(double) * 2 * ntab) == hipSuccess &&
-            sc.alloc((void **)&spec_n, sizeof(float2) * en) == hipSuccess &&
-            sc.alloc((void **)&spec_d, sizeof(float2) * en) == hipSuccess &&
-            sc.alloc((void **)&fn_real, sizeof(float) * N) == hipSuccess &&
-            sc.alloc((void **)&tw_n, sizeof(float2) * n) == hipSuccess &&
-            sc.alloc((void **)&tab_n, sizeof(float) * 3 * n) == hipSuccess;
-  if (ok && order >= 2) {
-    ok = sc.alloc((void **)&spec_m, sizeof(float2) * em) == hipSuccess &&
-         sc.alloc((void **)&tmp_m, sizeof(float) * M) == hipSuccess &&
-         sc.alloc((void **)&tw_m, sizeof(float2) * m) == hipSuccess &&
-         sc.alloc((void **)&tab_m, sizeof(float) * 3 * m) == hipSuccess;
-    for (int i = 0; ok && i < 6; ++i) ok = sc.alloc((void **)&h1[i], sizeof(float) * M) == hipSuccess;
-    for (int i = 0; ok && i < nsrc; ++i)
-      ok = sc.alloc((void **)&src_sp[i], sizeof(float2) * en) == hipSuccess;
-    for (int i = 0; ok && order == 3 && i < 6; ++i)
-      ok = sc.alloc((void **)&h2[i], sizeof(float) * M) == hipSuccess;
+  Scratch sc{ctx};
+  double *d_tab = nullptr;
+  float2 *tw_n = nullptr, *tw_m = nullptr, *delta = nullptr, *src_sp[6] = {}, *nx[2] = {}, *ny[3] = {};
+  float2 *mx[3] = {}, *my[6] = {}, *back = nullptr, *vec[3] = {};
+  float *tab_n = nullptr, *tab_m = nullptr, *amp = nullptr, *h1[6] = {}, *h2[6] = {}, *tmp = nullptr;
+  for (int pass = 0; pass < 2; ++pass) {
+    if (pass == 1 && !sc.open())
+      return pm_fail(ctx, PM_ERR_NOMEM, "initial-condition scratch allocation failed");
+    d_tab = sc.take<double>(2 * (size_t)ntab);
+    tw_n = sc.take<float2>(n);
+    tab_n = sc.take<float>(3 * n);
+    delta = sc.take<float2>(band);
+    amp = sc.take<float>(namp);
+    for (int i = 0; i < 3; ++i) {
+      if (i < 2) nx[i] = sc.take<float2>(2 * band);  // the n grid's passes: two [n][n][Pb]
+      ny[i] = sc.take<float2>(2 * band);
+    }
+    for (int i = 0; i < nsrc; ++i) src_sp[i] = sc.take<float2>(band);
+    if (order >= 2) {
+      tw_m = sc.take<float2>(m);
+      tab_m = sc.take<float>(3 * m);
+      for (int i = 0; i < 3; ++i) mx[i] = sc.take<float2>(half);
+      my[0] = sc.take<float2>(6 * plane * chunk);
+      for (int i = 1; i < 6 && pass; ++i) my[i] = my[0] + i * plane * chunk;
+      back = sc.take<float2>(half);
+    }
+    if (order == 3) {
+      for (int i = 0; i < 6; ++i) {
+        h1[i] = sc.take<float>(M);
+        h2[i] = sc.take<float>(M);
+      }
+      tmp = sc.take<float>(M);
+      for (int i = 0; i < 3; ++i) vec[i] = sc.take<float2>(band);
+    }
   }
-  if (!ok) return pm_fail(ctx, PM_ERR_NOMEM, "initial-condition scratch allocation failed");
   PM_HIP(ctx, hipMemcpyAsync(d_tab, lt.data(), sizeof(double) * 2 * ntab, hipMemcpyHostToDevice, s));
   const double *lk = d_tab, *lp = d_tab + ntab;
-  FftBufs bn{spec_n, nullptr, tw_n, tab_n}, bm{spec_m, nullptr, tw_m, tab_m};
-  PM_HIP(ctx, fft_tables(bn, n, 0, 0, s));
-  if (order >= 2) PM_HIP(ctx, fft_tables(bm, m, 0, 0, s));
-  const int Pn = fft_pitch(n), Pm = fft_pitch(m);
-  const unsigned gn = blocks_for((int64_t)n * n * (n / 2 + 1), kT);
-  const unsigned gm = blocks_for((int64_t)m * m * (m / 2 + 1), kT);
-  auto op_n = [&](const float2 *src, int gs, int Ps, SpecOp op) {  // into spec_n
-    k_spec_op<<<gn, kT, 0, s>>>(src, gs, Ps, spec_n, n, Pn, n, op, lk, lp, ntab);
-  };
-  auto op_m = [&](const float2 *src, int gs, int Ps, SpecOp op) {  // into spec_m
-    k_spec_op<<<gm, kT, 0, s>>>(src, gs, Ps, spec_m, m, Pm, n, op, lk, lp, ntab);
-  };
+  PM_HIP(ctx, fft_tables(FftBufs{nullptr, nullptr, tw_n, tab_n}, n, 0, 0, s));
+  if (order >= 2) PM_HIP(ctx, fft_tables(FftBufs{nullptr, nullptr, tw_m, tab_m}, m, 0, 0, s));
+  const Grid gn{n, Pb, tw_n, s}, gm{n, Pb, tw_m, s};
+  const Passes pn = passes_of(n), pm = passes_of(m);
   const float invN = (float)(1.0 / (double)N);
   const float trunc = (float)((double)N / (double)M);  // DFT on the m grid -> n-grid units
   // linear density at a = 1: DFT[delta] = sqrt(N) sqrt(P) DFT[w]
-  PM_HIP(ctx, fft_forward(bn, n, noise, nullptr, s));
-  k_spec_op<<<gn, kT, 0, s>>>(spec_n, n, Pn, spec_d, n, Pn, n,
-                              SpecOp{(float)std::sqrt((double)N), -1, -1, 0, 0, 1, 0}, lk, lp, ntab);
+  pn.to_band(gn, noise, nx[0], (int64_t)n * n);
+  pn.fwd_y(gn, nx[0], ny[0], 0, n);
+  k_amplitude<<<blocks_for(namp, kT), kT, 0, s>>>(lk, lp, ntab, (float)std::sqrt((double)N), namp, amp);
+  pn.fwd_x(gn, ny[0], delta, 1.0f, amp);
   PM_HIP(ctx, hipGetLastError());
-  PM_HIP(ctx, launch_fill(pos, 0.0f, 3 * N, s));
-  PM_HIP(ctx, launch_fill(vel, 0.0f, 3 * N, s));
-  const double ra = std::sqrt(a0);
-  // add sum_d grad-like fields: spectrum op into spec_n, inverse, then disp += cd f, vel += cv f
-  auto add_field = [&](int comp, double cd, double cv) -> hipError_t {
-    hipError_t e = fft_inverse(bn, n, fn_real, 1, 0, s);
-    if (e != hipSuccess) return e;
-    k_lpt_add<<<blocks_for(N, kT), kT, 0, s>>>(fn_real, comp, (float)cd, (float)cv, N, pos, vel);
-    return hipGetLastError();
+  // k_i k_j F / k^2 / N = m_i m_j F / m^2 / N of the band spectrum F, along i for all planes
+  auto hessian_x = [&](const float2 *f) {
+    pm.inv_x(gm, Combo{{f}, {{invN}}, 1}, mx[0], mx[1], mx[2], true, 1);
   };
-  // first order: Psi(1)_d = IDFT[i k_d delta / k^2] / N
-  for (int d = 0; d < 3; ++d) {
-    op_n(spec_d, n, Pn, SpecOp{invN, d, -1, 1, 1, 0, 0});
-    PM_HIP(ctx, add_field(d, a0, ra * a0));
-  }
+  // ... and along j for planes x0 .. : xx, yy, zz, xy, xz, yz before their powers of m_z
+  auto hessian_y = [&](int x0) {
+    pm.inv_y(gm, mx[2], my[0], nullptr, nullptr, x0, chunk, 1);  // m_x^2
+    pm.inv_y(gm, mx[1], my[4], my[3], nullptr, x0, chunk, 1);    // m_x, m_x m_y
+    pm.inv_y(gm, mx[0], my[2], my[5], my[1], x0, chunk, 1);      // 1, m_y, m_y^2
+  };
+  static const int kz_power[6] = {0, 0, 2, 0, 1, 1};
+  const int64_t crow = (int64_t)chunk * m;
   if (order >= 2) {
-    static const int hi[6] = {0, 1, 2, 0, 0, 1}, hj[6] = {0, 1, 2, 1, 2, 2};
-    // phi(1)_ij = IDFT[k_i k_j delta / k^2] / N on the product grid
-    for (int c = 0; c < 6; ++c) {
-      op_m(spec_d, n, Pn, SpecOp{invN, hi[c], hj[c], 1, 0, 0, 0});
-      PM_HIP(ctx, fft_inverse(bm, m, h1[c], 1, 0, s));
+    // second-order source from phi(1)_ij = IDFT[k_i k_j delta / k^2] / N, a chunk of planes
+    // at a time
+    hessian_x(delta);
+    for (int x0 = 0; x0 < m; x0 += chunk) {
+      hessian_y(x0);
+      if (order == 3)
+        for (int c = 0; c < 6; ++c)
+          pm.to_rows(gm, my[c], h1[c] + (int64_t)x0 * m * m, crow, kz_power[c]);
+      pm.source2(gm, my[0], plane * chunk, my[0], crow);
+      pm.fwd_y(gm, my[0], back, x0, chunk);
     }
-    Hess A{{h1[0], h1[1], h1[2], h1[3], h1[4], h1[5]}};
-    Hess B{{h2[0], h2[1], h2[2], h2[3], h2[4], h2[5]}};
-    // a source on the product grid -> its spectrum truncated to the n band (n-grid units)
-    auto source = [&](int which, float2 *dst) -> hipError_t {
-      k_lpt_source<<<blocks_for(M, kT), kT, 0, s>>>(A, B, which, M, tmp_m);
-      hipError_t e = fft_forward(bm, m, tmp_m, nullptr, s);
-      if (e != hipSuccess) return e;
-      k_spec_op<<<gn, kT, 0, s>>>(spec_m, m, Pm, dst, n, Pn, n, SpecOp{trunc, -1, -1, 0, 0, 0, 0},
-                                  lk, lp, ntab);
-      return hipGetLastError();
-    };
-    PM_HIP(ctx, source(kSrcS2, src_sp[0]));
-    // phi(2) = -lap^-1 S2: Psi(2)_d = IDFT[i k_d phi2] / N = IDFT[-i k_d S2 / k^2] / N
-    const double d2 = -3.0 / 7.0 * a0 * a0;
-    for (int d = 0; d < 3; ++d) {
-      op_n(src_sp[0], n, Pn, SpecOp{-invN, d, -1, 1, 1, 0, 0});
-      PM_HIP(ctx, add_field(d, d2, ra * 2.0 * d2));
+    pm.fwd_x(gm, back, src_sp[0], trunc, nullptr);
+    PM_HIP(ctx, hipGetLastError());
+  }
+  if (order == 3) {
+    // phi(2)_ij = IDFT[k_i k_j S2 / k^2] / N, then the five third-order sources
+    hessian_x(src_sp[0]);
+    for (int x0 = 0; x0 < m; x0 += chunk) {
+      hessian_y(x0);
+      for (int c = 0; c < 6; ++c) pm.to_rows(gm, my[c], h2[c] + (int64_t)x0 * m * m, crow, kz_power[c]);
     }
-    if (order == 3) {
-      // phi(2)_ij = IDFT[-k_i k_j phi2] = IDFT[k_i k_j S2 / k^2] / N on the product grid
-      for (int c = 0; c < 6; ++c) {
-        op_m(src_sp[0], n, Pn, SpecOp{invN, hi[c], hj[c], 1, 0, 0, 0});
-        PM_HIP(ctx, fft_inverse(bm, m, h2[c], 1, 0, s));
+    const Hess A{{h1[0], h1[1], h1[2], h1[3], h1[4], h1[5]}};
+    const Hess B{{h2[0], h2[1], h2[2], h2[3], h2[4], h2[5]}};
+    for (int w = kSrcDet; w <= kSrcRz; ++w) {
+      k_lpt_source<<<blocks_for(M, kT), kT, 0, s>>>(A, B, w, M, tmp);
+      for (int x0 = 0; x0 < m; x0 += chunk) {
+        pm.to_band(gm, tmp + (int64_t)x0 * m * m, my[0], crow);
+        pm.fwd_y(gm, my[0], back, x0, chunk);
       }
-      PM_HIP(ctx, source(kSrcDet, src_sp[1]));
-      PM_HIP(ctx, source(kSrcS3b, src_sp[2]));
-      PM_HIP(ctx, source(kSrcRx, src_sp[3]));
-      PM_HIP(ctx, source(kSrcRy, src_sp[4]));
-      PM_HIP(ctx, source(kSrcRz, src_sp[5]));
-      const double d3a = -1.0 / 3.0 * a0 * a0 * a0, d3b = 10.0 / 21.0 * a0 * a0 * a0;
-      const double d3c = -1.0 / 7.0 * a0 * a0 * a0;
-      // Psi(3a), Psi(3b) = grad lap^-1 S: IDFT[-i k_d S / k^2] / N
+      pm.fwd_x(gm, back, src_sp[w], trunc, nullptr);
+    }
+    PM_HIP(ctx, hipGetLastError());
+  }
+  // Psi(1)_d = IDFT[i k_d delta / k^2] / N, Psi(2)_d = IDFT[-i k_d S2 / k^2] / N, the same
+  // for 3a and 3b, and Psi(3c)_d = IDFT[-i (k x R)_d / k^2] / N: displacements and
+  // velocities weigh the orders differently (k_d / k^2 = m_d / (2 pi m^2))
+  const double ra = std::sqrt(a0), w = 1.0 / (kTwoPi * (double)N);
+  const double d2 = -3.0 / 7.0 * a0 * a0, d3a = -1.0 / 3.0 * a0 * a0 * a0, d3b = 10.0 / 21.0 * a0 * a0 * a0;
+  const double d3c = -1.0 / 7.0 * a0 * a0 * a0;
+  Combo pot{{delta, src_sp[0], src_sp[1], src_sp[2]}, {}, order == 3 ? 4 : order};
+  for (int v = 0; v < 2; ++v) {  // displacements, velocities
+    const double f = v ? ra : 1.0;
+    pot.c[v][0] = (float)(f * a0 * w);
+    pot.c[v][1] = (float)(-(v ? 2.0 : 1.0) * f * d2 * w);
+    pot.c[v][2] = (float)(-(v ? 3.0 : 1.0) * f * d3a * w);
+    pot.c[v][3] = (float)(-(v ? 3.0 : 1.0) * f * d3b * w);
+  }
+  if (order < 3) {
+    // (at first order one is a multiple of the other)
+    pn.inv_x(gn, pot, nx[0], nx[1], nullptr, true, order);
+    pn.inv_y(gn, nx[1], ny[0], nullptr, nullptr, 0, n, order);  // m_x phi
+    pn.inv_y(gn, nx[0], ny[2], ny[1], nullptr, 0, n, order);    // phi, m_y phi
+    pn.particles(gn, ny[0], ny[1], ny[2], true, pos, cell, vel, order == 1 ? (float)ra : 1.0f, order);
+  } else {
+    for (int v = 0; v < 2; ++v) {
+      const float c = (float)(-(v ? 3.0 * ra : 1.0) * d3c * w);
+      for (int j = 0; j < 4; ++j) pot.c[0][j] = pot.c[v][j];
+      k_vector_spectrum<<<blocks_for((int64_t)band, kT), kT, 0, s>>>(
+          pot, src_sp[3], src_sp[4], src_sp[5], c, n, Pb, vec[0], vec[1], vec[2]);
       for (int d = 0; d < 3; ++d) {
-        op_n(src_sp[1], n, Pn, SpecOp{-invN, d, -1, 1, 1, 0, 0});
-        PM_HIP(ctx, add_field(d, d3a, ra * 3.0 * d3a));
-        op_n(src_sp[2], n, Pn, SpecOp{-invN, d, -1, 1, 1, 0, 0});
-        PM_HIP(ctx, add_field(d, d3b, ra * 3.0 * d3b));
+        pn.inv_x(gn, Combo{{vec[d]}, {{1.0f}}, 1}, nx[0], nullptr, nullptr, false, 1);
+        pn.inv_y(gn, nx[0], ny[d], nullptr, nullptr, 0, n, 1);
       }
-      // Psi(3c) = curl A, A = -lap^-1 R: (curl A)_d = i (k_e A_f - k_f A_e) for the cyclic
-      // (d, e, f), i.e. IDFT[-i (k_e R_f - k_f R_e) / k^2] / N
-      for (int d = 0; d < 3; ++d) {
-        const int e = (d + 1) % 3, f = (d + 2) % 3;
-        op_n(src_sp[3 + f], n, Pn, SpecOp{-invN, e, -1, 1, 1, 0, 0});
-        op_n(src_sp[3 + e], n, Pn, SpecOp{invN, f, -1, 1, 1, 0, 1});
-        PM_HIP(ctx, add_field(d, d3c, ra * 3.0 * d3c));
-      }
+      pn.particles(gn, ny[0], ny[1], ny[2], false, v ? nullptr : pos, cell, v ? vel : nullptr, 1.0f, 1);
     }
   }
-  k_lpt_finish<<<blocks_for(N, kT), kT, 0, s>>>(pos, cell, n, N);
   PM_HIP(ctx, hipGetLastError());
-  // the scratch is released when the call returns: wait for the work that reads it
+  // (the table's host copy and a scratch above the kept size end with the call)
   PM_HIP(ctx, hipStreamSynchronize(s));
+  sc.idle = true;
   return PM_OK;
 }
 

@@ -35,6 +35,19 @@ struct pm_fr_level {
   double *alt; // second iterate buffer of the streaming sweeps (levels of >= 256 cells)
 };
 
+// two floats of a caller's array, which is only known to be aligned to one
+typedef float Pair4 __attribute__((ext_vector_type(2), aligned(4)));
+__device__ __forceinline__ float2 load_pair(const float *p) {
+  const Pair4 v = *reinterpret_cast<const Pair4 *>(p);
+  return make_float2(v.x, v.y);
+}
+
+struct IcScratch {        // device scratch of the initial conditions (ics.hip)
+  void *p;
+  size_t bytes;
+};
+void ic_scratch_free(IcScratch *b);
+
 struct pm_ctx {
   int n;
   int64_t np_max;
@@ -59,6 +72,7 @@ struct pm_ctx {
   void *spec2;           // two more spectra of the Fourier-space force (lazy)
   float2 *twiddle;       // [n] e^{-2 pi i m / n}, m = 0 .. n-1
   float *fft_tab;        // [3n] per-axis tables: k^2 part, window part, k_d
+  IcScratch *ic;         // initial conditions: the scratch kept between calls (or NULL)
   // counting sort (lazy)
   int32_t *cell_count;   // [n^3 + 1] counts -> starts -> ends (end of c = start of c + 1)
   int32_t *perm;         // [np_max] particle indices bucketed by cell
@@ -268,13 +282,8 @@ int fft_mean_blocks(int n);  // at most RED_BLOCKS
 // the context's spectrum, twiddles and tables (once), for the solvers and the estimator
 hipError_t fft_alloc(pm_ctx *ctx);
 int spectrum_pitch(int n);   // spectrum.hip: row pitch of the estimator's half spectrum
-// separate passes over one grid: the twiddles and tables of b for an n^3 grid; the
-// forward transform of the real grid x (mean subtracted when given) into b.spec (full
-// half spectrum, unnormalised); the inverse of b.spec (consumed) into out[(p * stride) +
-// comp] (unnormalised: no 1 / n^3)
+// the twiddles and tables of b for an n^3 grid
 hipError_t fft_tables(const FftBufs &b, int n, int deconv, int kind, hipStream_t s);
-hipError_t fft_forward(const FftBufs &b, int n, const float *x, const float *mean, hipStream_t s);
-hipError_t fft_inverse(const FftBufs &b, int n, float *out, int stride, int comp, hipStream_t s);
 // mean: the device mean of rho when known (the sorted deposit's), else computed here
 int pm_fft_solve(pm_ctx *ctx, const float *rho, float coef, int deconv, float *phi,
                  hipStream_t s, const float *mean = nullptr);

@@ -34,7 +34,7 @@
 
 #include <hip/hip_runtime.h>
 
-#include "../../include/hippm.h"
+#include "internal.h"
 
 namespace pm_tile {
 
@@ -114,8 +114,8 @@ __device__ __forceinline__ void load(const Level &a, const Pair<S> &p, int i0, C
 #pragma unroll
   for (int i = 0; i < S::NI; ++i) {
     const size_t at = (size_t)q * nn + p.col;
-    f[i] = *reinterpret_cast<const float2 *>(a.f + at);
-    if (a.uin) u[i] = *reinterpret_cast<const float2 *>(a.uin + at);
+    f[i] = load_pair(a.f + at);
+    if (a.uin) u[i] = load_pair(a.uin + at);
     q = q + 1 == a.n ? 0 : q + 1;
   }
 #pragma unroll
@@ -203,8 +203,7 @@ __device__ __forceinline__ void store(const Level &a, const Pair<S> &p, int i0, 
   for (int i = 0; i < S::TI; ++i)
     if (i0 + i < a.n) {
       const float x = c.uE[S::H + i], y = c.uO[S::H + i];
-      *reinterpret_cast<float2 *>(a.uout + (size_t)(i0 + i) * nn + p.col) =
-          p.swp ? make_float2(y, x) : make_float2(x, y);
+      *reinterpret_cast<Pair4 *>(a.uout + (size_t)(i0 + i) * nn + p.col) = p.swp ? Pair4{y, x} : Pair4{x, y};
     }
 }
 
