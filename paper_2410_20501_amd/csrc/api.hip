@@ -568,8 +568,9 @@ int pm_create(pm_ctx **out, int n, int64_t np_max, int flags) {
       hipMalloc(&ctx->red_partial, 3 * sizeof(double) * RED_PARTIAL_CAP) != hipSuccess ||
       hipMalloc(&ctx->red_result, 4 * sizeof(double)) != hipSuccess ||
       hipMalloc(&ctx->mean_f, 4 * sizeof(float)) != hipSuccess ||
-      hipHostMalloc(&ctx->host_result, 4 * sizeof(double), hipHostMallocDefault) != hipSuccess)
+      hipHostMalloc(&ctx->host_result, 8 * sizeof(double), hipHostMallocDefault) != hipSuccess)
     st = PM_ERR_NOMEM;
+  if (st == PM_OK) std::memset(ctx->host_result, 0, 8 * sizeof(double));  // (no report)
   if (st == PM_OK) st = pm_mg_setup(ctx);
   for (int i = 0; st == PM_OK && i < 8; ++i)
     if (hipEventCreate(&ctx->ev[i]) != hipSuccess) st = PM_ERR_HIP;

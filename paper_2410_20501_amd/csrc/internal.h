@@ -63,7 +63,8 @@ struct pm_ctx {
   // reductions
   double *red_partial;   // [RED_MAX_BLOCKS * 2]
   double *red_result;    // [4] device: {sum0, sum1, mean, spare}
-  double *host_result;   // pinned [4]
+  double *host_result;   // pinned [8]: [4 .. 6] the multigrid norms' report
+  unsigned long long norm_seq;  // of the last such report
   float *mean_f;         // [4] device: [0] FP32 mean of the current source grid,
                          // [1] mean of the solve's final iterate (gauge), [2] mean of the
                          // FFT solve's input

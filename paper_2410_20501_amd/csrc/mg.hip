@@ -12,6 +12,8 @@
 // source term.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
+#include <functional>
 
 #include "coarse_solve.h"
 #include "mg_tile.h"
@@ -282,30 +284,58 @@ __global__ __launch_bounds__(kThreads) void k_scale(float *__restrict__ u, int64
   u[c] *= s;
 }
 
-// Totals of the three per-block sums of the norm-summing smoother pass.
-__global__ __launch_bounds__(RED_THREADS) void k_triple_final(const double *__restrict__ partial,
-                                                              int nblocks,
-                                                              double *__restrict__ result,
-                                                              int64_t count,
-                                                              float *__restrict__ mean) {
-  double v[3] = {0.0, 0.0, 0.0};
-  for (int b = threadIdx.x; b < nblocks; b += RED_THREADS)
+// Totals of the three per-block sums of the norm-summing pass, taken by one workgroup:
+// to result and mean on the device and, as three words, to the host's pinned memory while
+// the stream goes on. The words arrive in any order: the third is a function of the other
+// two and of seq, so that the host knows a whole report (wait_norms).
+struct Report {
+  const double *partial;
+  int nblocks;
+  int64_t count;
+  double *result;
+  float *mean;
+  unsigned long long *host;  // NULL: nothing to report
+  unsigned long long seq;
+};
+
+__host__ __device__ inline unsigned long long report_check(unsigned long long a, unsigned long long b,
+                                                           unsigned long long seq) {
+  return a ^ (b << 21 | b >> 43) ^ seq * 0x9E3779B97F4A7C15ull;
+}
+
+// lds: 3 RED_THREADS / 64 doubles
+__device__ __forceinline__ void report_norms(const Report &r, double *lds) {
+  const int T = blockDim.x < RED_THREADS ? (int)blockDim.x : RED_THREADS, waves = T / 64;
+  if ((int)threadIdx.x < T) {
+    double v[3] = {0.0, 0.0, 0.0};
+    for (int b = threadIdx.x; b < r.nblocks; b += T)
 #pragma unroll
-    for (int i = 0; i < 3; ++i) v[i] += partial[3 * b + i];
-  __shared__ double l[3][RED_THREADS / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+      for (int i = 0; i < 3; ++i) v[i] += r.partial[3 * b + i];
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    v[i] = wave_sum(v[i]);
-    if (lane == 0) l[i][wave] = v[i];
+    for (int i = 0; i < 3; ++i) {
+      v[i] = wave_sum(v[i]);
+      if ((threadIdx.x & 63) == 0) lds[i * waves + (threadIdx.x >> 6)] = v[i];
+    }
   }
   __syncthreads();
-  if (threadIdx.x < 3) {
-    double a = 0.0;
-    for (int w = 0; w < RED_THREADS / 64; ++w) a += l[threadIdx.x][w];
-    result[threadIdx.x] = a;
-    if (threadIdx.x == 2) *mean = (float)(a / (double)count);  // mean of the input
+  if (threadIdx.x != 0) return;
+  double t[3] = {0.0, 0.0, 0.0};
+  for (int i = 0; i < 3; ++i)
+    for (int w = 0; w < waves; ++w) t[i] += lds[i * waves + w];
+  const unsigned long long a = (unsigned long long)__double_as_longlong(t[0]);
+  const unsigned long long b = (unsigned long long)__double_as_longlong(t[1]);
+  const unsigned long long word[3] = {a, b, report_check(a, b, r.seq)};
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    __hip_atomic_store(r.host + i, word[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    r.result[i] = t[i];
   }
+  *r.mean = (float)(t[2] / (double)r.count);  // mean of the input
+}
+
+__global__ __launch_bounds__(RED_THREADS) void k_report(Report r) {
+  __shared__ double lds[3 * RED_THREADS / 64];
+  report_norms(r, lds);
 }
 
 // Truncation-error estimate of the paper's alternative stopping rule (Sect. 3.7.1,
@@ -406,20 +436,25 @@ __global__ __launch_bounds__(kThreads) void k_finish_phi4(const float4 *__restri
                        fmaf(scale, v.w, -m));
 }
 
-// Coarsest level: one workgroup (coarse_solve.h).
+// Coarsest level: one workgroup (coarse_solve.h), and one for a report.
 template <int N>
 __global__ __launch_bounds__(pm_coarse::kThreads) void k_coarse_solve(
     float *__restrict__ ug, const float *__restrict__ fg, float scale,
-    const float *__restrict__ mean, float h2) {
-  __shared__ float2 spec[N * N * (N / 2 + 1)];
+    const float *__restrict__ mean, float h2, Report report) {
+  __shared__ __align__(8) float2 spec[N * N * (N / 2 + 1)];
+  if (blockIdx.x) {
+    report_norms(report, reinterpret_cast<double *>(spec));
+    return;
+  }
   pm_coarse::solve<N>(ug, fg, scale, src_mean(mean), h2, spec);
 }
 
 // the block's tile of an n^3 level in TI x TJ x TK tiles (XCD-aware: neighbours along k,
 // then j, share an L2 and each other's halos)
 template <class S>
-__device__ __forceinline__ void block_tile(int n, int &i0, int &j0, int &k0) {
-  const unsigned b = xcd_block(blockIdx.x, gridDim.x);
+__device__ __forceinline__ void block_tile(unsigned block, unsigned blocks, int n, int &i0, int &j0,
+                                           int &k0) {
+  const unsigned b = xcd_block(block, blocks);
   const unsigned tk = (unsigned)pm_tile::tiles_of(n, S::TK), tj = (unsigned)pm_tile::tiles_of(n, S::TJ);
   const unsigned q = b / tk;
   k0 = (int)(b - q * tk) * S::TK;
@@ -428,16 +463,22 @@ __device__ __forceinline__ void block_tile(int n, int &i0, int &j0, int &k0) {
 }
 
 // The tile kernels (mg_tile.h). down: pre-smoothing, residual and restriction of a level,
-// with NORM also the three sums of the convergence test (three doubles per block); up:
-// prolongation and post-smoothing.
+// with NORM also the three sums of the convergence test (three doubles per block), or, in
+// the pass after that one, their totals by a workgroup more (the first); up: prolongation
+// and post-smoothing.
 template <int TI, int TJ, int TK, int KIND, bool OM1, bool NORM>
 __global__ __launch_bounds__((pm_tile::Down<TI, TJ, TK>::NT)) void k_tile_down(
     pm_tile::Level a, const float *__restrict__ mean, int hs, float *__restrict__ fc,
-    double *__restrict__ partial) {
+    double *__restrict__ partial, Report report) {
   using S = pm_tile::Down<TI, TJ, TK>;
   __shared__ __align__(16) float lds[S::LDS];
+  const unsigned extra = !NORM && report.host ? 1 : 0;
+  if (blockIdx.x < extra) {
+    report_norms(report, reinterpret_cast<double *>(lds));
+    return;
+  }
   int i0, j0, k0;
-  block_tile<S>(a.n, i0, j0, k0);
+  block_tile<S>(blockIdx.x - extra, gridDim.x - extra, a.n, i0, j0, k0);
   a.mean = src_mean(mean);
   double sum[3];
   pm_tile::tile_down<TI, TJ, TK, KIND, OM1, NORM>(a, i0, j0, k0, hs, fc, lds, sum);
@@ -464,7 +505,7 @@ __global__ __launch_bounds__((pm_tile::Up<TI, TJ, TK>::NT)) void k_tile_up(
   __shared__ __align__(16) float lds[S::LDS];
   __shared__ float raw[S::RAW];
   int i0, j0, k0;
-  block_tile<S>(a.n, i0, j0, k0);
+  block_tile<S>(blockIdx.x, gridDim.x, a.n, i0, j0, k0);
   a.mean = src_mean(mean);
   pm_tile::tile_up<TI, TJ, TK, OM1>(a, ec, i0, j0, k0, hs, lds, raw);
 }
@@ -515,6 +556,7 @@ inline unsigned norm_blocks(int n) {
 // cycle that reduced it by less than kFloorGain ends the solve with PM_WARN_FLOOR.
 constexpr double kFloorBelow = 1e-4;
 constexpr double kFloorGain = 1.5;
+constexpr int kTestIn = 2;
 
 struct Src {
   const float *f;
@@ -534,6 +576,10 @@ struct Solver {
   Src src0;
   float *cur[PM_MAX_LEVELS];
   float *alt[PM_MAX_LEVELS];
+  Report report{};                     // of the norm pass, for the next launch to take
+  int test_in = 0;                     // launches until the test (0: none is due)
+  bool stop = false;
+  std::function<hipError_t()> test;
 
   Src src(int l) const { return l == 0 ? src0 : Src{ctx->lev[l].f, 1.0f, nullptr}; }
   float h2(int l) const {
@@ -559,11 +605,14 @@ struct Solver {
   hipError_t tile_down(int l, int left, bool restricts, bool from_guess = false, float uscale = 1.0f,
                        double *partial = nullptr) {
     do {
+      if (stop) return hipSuccess;
       const int now = std::min(left, 2);
       left -= now;
       launch_tile_down(tile_level(l, from_guess, uscale), src(l).mean, 2 * now,
                        left == 0 && restricts ? ctx->lev[l + 1].f : nullptr, partial);
       std::swap(cur[l], alt[l]);
+      const hipError_t e = launched();
+      if (e != hipSuccess) return e;
       from_guess = false;
       uscale = 1.0f;
       partial = nullptr;
@@ -576,10 +625,13 @@ struct Solver {
     int left = p->post;
     const float *ec = cur[l + 1];
     do {
+      if (stop) return hipSuccess;
       const int now = std::min(left, 2);
       left -= now;
       launch_tile_up(tile_level(l, false, 1.0f), src(l).mean, ec, 2 * now);
       std::swap(cur[l], alt[l]);
+      const hipError_t e = launched();
+      if (e != hipSuccess) return e;
       ec = nullptr;
     } while (left > 0);
     return hipGetLastError();
@@ -588,10 +640,12 @@ struct Solver {
   template <int TI, int TJ, int TK>
   void launch_tile_down_shape(const pm_tile::Level &a, const float *mean, int hs, float *fc,
                               double *partial) {
-    const unsigned nb = tile_blocks(a.n, TI, TJ, TK);
-    constexpr int NT = pm_tile::Down<TI, TJ, TK>::NT;
     const bool om1 = a.omega == 1.0f, norm = partial != nullptr;
-#define PM_TILE_DOWN(K_, O_, N_) k_tile_down<TI, TJ, TK, K_, O_, N_><<<nb, NT, 0, s>>>(a, mean, hs, fc, partial)
+    const Report r = norm ? Report{} : take_report();
+    const unsigned nb = tile_blocks(a.n, TI, TJ, TK) + (r.host ? 1 : 0);
+    constexpr int NT = pm_tile::Down<TI, TJ, TK>::NT;
+#define PM_TILE_DOWN(K_, O_, N_) \
+  k_tile_down<TI, TJ, TK, K_, O_, N_><<<nb, NT, 0, s>>>(a, mean, hs, fc, partial, r)
 #define PM_TILE_DOWN_KIND(K_)                                                        \
   do {                                                                               \
     if (om1) { if (norm) PM_TILE_DOWN(K_, true, true); else PM_TILE_DOWN(K_, true, false); } \
@@ -705,12 +759,14 @@ struct Solver {
   }
 
   hipError_t coarse(int l) {
+    if (stop) return hipSuccess;
     const Src sr = src(l);
     const int n = ctx->lev[l].n;
+    const Report r = take_report();
 #define PM_COARSE(N_)                                                                      \
   case N_:                                                                                 \
-    k_coarse_solve<N_><<<1, (N_ * N_ + 63) / 64 * 64, 0, s>>>(cur[l], sr.f, sr.scale,      \
-                                                              sr.mean, h2(l));             \
+    k_coarse_solve<N_><<<r.host ? 2 : 1, (N_ * N_ + 63) / 64 * 64, 0, s>>>(                \
+        cur[l], sr.f, sr.scale, sr.mean, h2(l), r);                                        \
     break
     switch (n) {
       PM_COARSE(8);
@@ -722,7 +778,56 @@ struct Solver {
       default: return hipErrorInvalidValue;  // (pm_mg_setup ends at one of these)
     }
 #undef PM_COARSE
-    return hipGetLastError();
+    return launched();
+  }
+
+  // The next launch takes the pending report, if there is one.
+  Report take_report() {
+    const Report r = report;
+    report = Report{};
+    return r;
+  }
+
+  // After a launch below the finest level's norm pass: `test` is called when `test_in`
+  // launches are queued behind that pass. It waits for the report and decides (stop:
+  // nothing more is launched).
+  hipError_t launched() {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || test_in == 0 || --test_in > 0) return e;
+    return test();
+  }
+
+  // Report of the norm pass over nblocks workgroups just launched.
+  Report norm_report(int nblocks) {
+    const int64_t n = ctx->lev[0].n;
+    return Report{ctx->red_partial, nblocks, n * n * n, ctx->red_result, ctx->mean_f + 1,
+                  reinterpret_cast<unsigned long long *>(ctx->host_result + 4), ++ctx->norm_seq};
+  }
+
+  // The two sums of the last report. The host reads them while the stream goes on: against
+  // a launch for the totals, a copy and a synchronisation, a cycle of a tiled finest level
+  // takes 14 (32^3: 36 -> 22 us) to 17 us (128^3) less, of a streaming one 5 us. Ends when
+  // the report has arrived, or the stream has run out of work or failed.
+  hipError_t wait_norms(double (&sum)[2]) {
+    const volatile unsigned long long *w =
+        reinterpret_cast<const volatile unsigned long long *>(ctx->host_result + 4);
+    bool idle = false;
+    for (unsigned spins = 1;; ++spins) {
+      const unsigned long long a = w[0], b = w[1], c = w[2];
+      if (c == report_check(a, b, ctx->norm_seq)) {
+        std::memcpy(&sum[0], &a, sizeof(double));
+        std::memcpy(&sum[1], &b, sizeof(double));
+        return hipSuccess;
+      }
+      if (idle) return hipErrorUnknown;  // the work has ended without a report
+      if (spins % 4096 == 0) {
+        const hipError_t e = hipStreamQuery(s);
+        if (e == hipErrorNotReady) (void)hipGetLastError();
+        else if (e != hipSuccess) return e;
+        idle = e == hipSuccess;
+      }
+      __builtin_ia32_pause();
+    }
   }
 
   // One cycle from level l (shape p->cycle unless given); when pre_done, the
@@ -850,6 +955,41 @@ int pm_mg_solve(pm_ctx *ctx, const float *rho, float coef, float *phi, const pm_
   } else {
     double rel[64];
     double fnorm = 0.0;
+    double sum[2] = {0.0, 0.0};
+    bool zero = false;
+    // the test of the iterate whose norms were taken last: sv.stop and status
+    auto decide = [&]() -> hipError_t {
+      if (cycles == 0) fnorm = sqrt(sum[1]);
+      if (fnorm == 0.0) {
+        zero = sv.stop = true;
+        return hipSuccess;
+      }
+      rel[cycles] = sqrt(sum[0]) / fnorm;
+      bool converged = rel[cycles] < p->tol;
+      if (p->alpha > 0.0f) {
+        // the paper's rule: residual below alpha times the truncation-error estimate of
+        // the same iterate (the input of the norm pass, read rescaled in the first one)
+        double tnorm = 0.0;
+        const hipError_t e = sv.tau_norm(fused_norm ? sv.alt[0] : sv.cur[0],
+                                         fused_norm && cycles == 0 ? uscale : 1.0f, &tnorm);
+        if (e != hipSuccess) return e;
+        converged = sqrt(sum[0]) < (double)p->alpha * tnorm;
+      }
+      if (converged) {
+        status = PM_OK;
+      } else if (cycles > 0 && rel[cycles] < kFloorBelow &&
+                 rel[cycles - 1] < kFloorGain * rel[cycles]) {
+        // a V-cycle removes most of the algebraic residual (about 6 to 10 times, App. C);
+        // a cycle that gained less than kFloorGain met the FP32 rounding floor
+        status = PM_WARN_FLOOR;
+      }
+      sv.stop = status != PM_WARN_NOT_CONVERGED || cycles == p->max_cycles;
+      return hipSuccess;
+    };
+    sv.test = [&]() -> hipError_t {
+      const hipError_t e = sv.wait_norms(sum);
+      return e == hipSuccess ? decide() : e;
+    };
     status = PM_WARN_NOT_CONVERGED;
     for (;;) {
       // residual norm of the current iterate: fused into the next pre-smoothing
@@ -860,54 +1000,49 @@ int pm_mg_solve(pm_ctx *ctx, const float *rho, float coef, float *phi, const pm_
         if (tiled) PM_HIP(ctx, sv.tile_down(0, std::min(p->pre, 2), restrict_now,
                                             from_guess && cycles == 0, us, ctx->red_partial));
         else PM_HIP(ctx, sv.stream_sweeps(0, 0, std::min(p->pre, 2), ctx->red_partial, us));
-        k_triple_final<<<1, RED_THREADS, 0, s>>>(ctx->red_partial, (int)nb, ctx->red_result,
-                                                  count, ctx->mean_f + 1);
+        sv.report = sv.norm_report((int)nb);
       } else {
         sv.norms();
+        PM_HIP(ctx, hipMemcpyAsync(ctx->host_result, ctx->red_result, 2 * sizeof(double),
+                                   hipMemcpyDeviceToHost, s));
+        PM_HIP(ctx, hipStreamSynchronize(s));
+        std::memcpy(sum, ctx->host_result, sizeof(sum));
+        PM_HIP(ctx, decide());
       }
-      PM_HIP(ctx, hipMemcpyAsync(ctx->host_result, ctx->red_result, 2 * sizeof(double),
-                                 hipMemcpyDeviceToHost, s));
-      PM_HIP(ctx, hipStreamSynchronize(s));
-      if (cycles == 0) fnorm = sqrt(ctx->host_result[1]);
-      if (fnorm == 0.0) {
-        if (fused_norm) std::swap(sv.cur[0], sv.alt[0]);  // drop the speculative pass
-        PM_HIP(ctx, launch_fill(phi, 0.0f, count, s));
-        if (stats) {
-          stats->cycles = 0;
-          stats->status = PM_OK;
-          stats->relres[0] = 0.0;
+      // On a tiled finest level the cycle goes on while the host waits: the totals are
+      // taken beside its next launch and the test is made once kTestIn of them are queued,
+      // which cover the time that the report and the next launches take (6 to 8 us). After
+      // a stop those launches were in vain, but harmless: they leave the tested iterate as
+      // it is. A streaming level's next pass takes longer than the wait: test at once.
+      float *const tested = sv.cur[0];
+      const bool ahead = tiled && restrict_now && cycles < p->max_cycles;
+      if (ahead) {
+        sv.test_in = kTestIn;
+        PM_HIP(ctx, sv.vcycle(0, true));
+      } else if (fused_norm) {
+        k_report<<<1, RED_THREADS, 0, s>>>(sv.take_report());
+        PM_HIP(ctx, hipGetLastError());
+        PM_HIP(ctx, sv.test());
+      }
+      if (sv.stop) {
+        if (sv.cur[0] != tested) std::swap(sv.cur[0], sv.alt[0]);
+        if (zero) {
+          if (fused_norm) std::swap(sv.cur[0], sv.alt[0]);  // drop the speculative pass
+          PM_HIP(ctx, launch_fill(phi, 0.0f, count, s));
+          if (stats) {
+            stats->cycles = 0;
+            stats->status = PM_OK;
+            stats->relres[0] = 0.0;
+          }
+          return PM_OK;
         }
-        return PM_OK;
-      }
-      rel[cycles] = sqrt(ctx->host_result[0]) / fnorm;
-      bool converged = rel[cycles] < p->tol;
-      if (p->alpha > 0.0f) {
-        // the paper's rule: residual below alpha times the truncation-error estimate of
-        // the same iterate (the input of the norm pass, read rescaled in the first one)
-        const double dnorm = sqrt(ctx->host_result[0]);
-        double tnorm = 0.0;
-        PM_HIP(ctx, sv.tau_norm(fused_norm ? sv.alt[0] : sv.cur[0],
-                                fused_norm && cycles == 0 ? uscale : 1.0f, &tnorm));
-        converged = dnorm < (double)p->alpha * tnorm;
-      }
-      if (converged) {
-        status = PM_OK;
-      } else if (cycles > 0 && rel[cycles] < kFloorBelow &&
-                 rel[cycles - 1] < kFloorGain * rel[cycles]) {
-        // a V-cycle removes most of the algebraic residual (about 6 to 10 times, App. C);
-        // a cycle that gained less than kFloorGain met the FP32 rounding floor
-        status = PM_WARN_FLOOR;
-      }
-      if (status != PM_WARN_NOT_CONVERGED || cycles == p->max_cycles) {
-        if (fused_norm) {
-          // the speculative pass smoothed the tested iterate twice more: keep its output
-          // (smoothing does not raise the error); its mean is taken as the tested
-          // iterate's (the pass changes it by far less than the solve's error)
-          have_sum = true;
-        }
+        // the norm pass smoothed the tested iterate twice more: keep its output (smoothing
+        // does not raise the error); its mean is taken as the tested iterate's (the pass
+        // changes it by far less than the solve's error)
+        have_sum = fused_norm;
         break;
       }
-      if (fused_norm) {
+      if (fused_norm && !ahead) {
         // finish the cycle whose pre-smoothing already ran (remaining pre sweeps first)
         if (tiled) {
           if (!restrict_now) PM_HIP(ctx, sv.tile_down(0, std::max(p->pre - 2, 0), true));
@@ -915,7 +1050,7 @@ int pm_mg_solve(pm_ctx *ctx, const float *rho, float coef, float *phi, const pm_
           PM_HIP(ctx, sv.stream_sweeps(0, 0, p->pre - 2, nullptr));
         }
         PM_HIP(ctx, sv.vcycle(0, true));
-      } else {
+      } else if (!fused_norm) {
         PM_HIP(ctx, sv.vcycle(0));
       }
       ++cycles;
