@@ -12,8 +12,8 @@
 // Full approximation storage (Sect. 3.7.2): after pre-smoothing, the residual
 // d = s - N_h(u) and u are restricted (full weighting), the coarse right-hand side is
 // N_H(R u) + R d, the coarse problem starts from R u, and u += P(u_H - R u) (trilinear).
-// The coarsest grid gets a fixed number of sweeps (one workgroup in LDS when it is
-// small).
+// The coarsest grid gets a fixed number of sweeps. Grids of up to 16^3 cells, down to the
+// coarsest, are one launch and one workgroup (k_fr_small).
 #include <cmath>
 
 #include "internal.h"
@@ -21,8 +21,9 @@
 namespace {
 
 constexpr int kFrThreads = 256;
-constexpr int kFrCoarseThreads = 512;
-constexpr int kFrCoarseMax = 2048;   // coarsest cells held in LDS (two FP64 arrays)
+constexpr int kFrSmallThreads = 512;
+constexpr int kFrSmallMax = 4096;  // cells of the largest grid that k_fr_small takes
+constexpr int kFrSmallOps = 64;    // steps of its program at most
 
 __host__ __device__ inline int wrapn(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
@@ -51,6 +52,13 @@ __device__ __forceinline__ void cell_ijk(unsigned c, int n, int &i, int &j, int 
     i = (int)(q / un);
     j = (int)(q - (unsigned)i * un);
   }
+}
+
+// keeps the compiler from moving one lane's LDS accesses over another's of the same wave
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ __forceinline__ unsigned fr_thread() {
@@ -171,6 +179,29 @@ __device__ double root4(double p, double q) {
   const double S = 0.5 * sqrt(w / 3.0);
   const double arg = p > 0.0 ? -4.0 * S * S + p / S : -4.0 * S * S - p / S;
   return (p > 0.0 ? -S : S) + 0.5 * sqrt(fmax(arg, 0.0));
+}
+
+// The positive root of u^(NE+2) + p u + q = 0 (q < 0) from the value it had before, where
+// that is close enough: the polynomial is convex for u > 0 and f' >= 2 r^2 (3 r^3) at its one
+// positive root r, so a Newton step takes a relative error e to at most 2 e^2. A first
+// correction of at most 2e-3 u0 with f'(u0) >= u0^2 (u0^3) proves that r lies within 4e-3 of
+// u0; three steps then reach 1e-16 (the hardware reciprocal's 1e-7 costs a factor only).
+// About 150 cycles of latency against 400 or more of the closed forms, which are what bounds
+// a half-sweep of a few waves; otherwise the closed forms.
+template <int NE>
+__device__ __forceinline__ double root_near(double u0, double p, double q) {
+  double u = u0;
+  bool near = u0 > 0.0;
+#pragma unroll
+  for (int it = 0; it < 3; ++it) {
+    const double u2 = u * u, up = NE == 1 ? u2 : u2 * u;
+    const double f = fma(NE == 1 ? u2 + p : up + p, u, q), fp = fma(NE + 2.0, up, p);
+    const double step = f * __builtin_amdgcn_rcp(fp);
+    if (it == 0) near = near && fp >= up && fabs(step) <= 2e-3 * u0;
+    u -= step;
+  }
+  if (near) return u;
+  return NE == 1 ? root3(p, q) : root4(p, q);
 }
 
 struct FrLevel {
@@ -723,53 +754,174 @@ __global__ __launch_bounds__(kFrThreads) void k_fr_prolong(const double *uin, do
   }
 }
 
-// the coarsest grid (n^3 <= kFrCoarseMax, n even): `sweeps` red-black sweeps in LDS
+// The part of a cycle that a grid of at most kFrSmallMax cells and the grids below it take,
+// in one workgroup and LDS. A launch per step is bound by latency there, not by work: 2.2 to
+// 5 us for each of the 11 steps of an 8^3 grid's visit, whose half-sweeps take 0.25 us here.
+// The steps are a program that the host writes: visits of every shape and any number of
+// levels run in one loop, and each step's code is there once.
+// Measured, V visits with 32 coarsest sweeps: 8^3 63 -> 25 us; 16^3 96 -> 54 us (its own
+// steps take as long on one compute unit as in launches of their own, 30 us; grids of 8^3
+// as the largest: a 256^3 F cycle 1237 against 1219 us; 1024 threads spill: 1264).
+enum { kFrOpPre, kFrOpPost, kFrOpDown, kFrOpUp, kFrOpCoarse };
+struct FrProgram {
+  int nops, nlev, pre, post, coarse_sweeps;
+  FrLevel lev[3];                  // 16, 8, 4 cells a side at most
+  unsigned char op[kFrSmallOps];   // operation * 4 + level
+};
+
+// one cell of a level and its neighbours in LDS, decoded once for many sweeps
+struct FrSite {
+  int c, nb[6];
+  __device__ __forceinline__ FrSite(int t, int n, int colour) {
+    int i, j, k2;
+    if ((n & (n - 1)) == 0) {
+      const int lg = __builtin_ctz((unsigned)n);
+      k2 = t & ((n >> 1) - 1);
+      j = (t >> (lg - 1)) & (n - 1);
+      i = t >> (2 * lg - 1);
+    } else {
+      const int hn = n >> 1, q = t / hn;
+      k2 = t - q * hn;
+      i = q / n;
+      j = q - i * n;
+    }
+    const int k = 2 * k2 + ((i + j + colour) & 1), ri = i * n * n, rj = j * n;
+    c = ri + rj + k;
+    nb[0] = wrapn(i - 1, n) * n * n + rj + k;
+    nb[1] = wrapn(i + 1, n) * n * n + rj + k;
+    nb[2] = ri + wrapn(j - 1, n) * n + k;
+    nb[3] = ri + wrapn(j + 1, n) * n + k;
+    nb[4] = ri + rj + wrapn(k - 1, n);
+    nb[5] = ri + rj + wrapn(k + 1, n);
+  }
+};
+
 template <int NE>
-__global__ __launch_bounds__(kFrCoarseThreads) void k_fr_coarse(double *__restrict__ u,
-                                                                const double *__restrict__ s,
-                                                                FrLevel L, int sweeps) {
-  constexpr int kCC = kFrCoarseMax / kFrCoarseThreads;  // cells per thread at most
-  __shared__ double su[kFrCoarseMax];
-  __shared__ double ss[kFrCoarseMax];
-  const int n = L.n, cells = n * n * n;
-  // a thread's cells, their colours and neighbours' places, decoded once for all sweeps
-  int cell[kCC], colour_of[kCC], nbr[kCC][6];
-#pragma unroll
-  for (int m = 0; m < kCC; ++m) {
-    const int c = (int)threadIdx.x + m * kFrCoarseThreads;
-    cell[m] = c < cells ? c : -1;
-    const int cv = c < cells ? c : 0;
-    const int i = cv / (n * n), j = (cv / n) % n, k = cv % n;
-    colour_of[m] = (i + j + k) & 1;
-    const int ri = i * n * n, rj = j * n;
-    nbr[m][0] = wrapn(i - 1, n) * n * n + rj + k;
-    nbr[m][1] = wrapn(i + 1, n) * n * n + rj + k;
-    nbr[m][2] = ri + wrapn(j - 1, n) * n + k;
-    nbr[m][3] = ri + wrapn(j + 1, n) * n + k;
-    nbr[m][4] = ri + rj + wrapn(k - 1, n);
-    nbr[m][5] = ri + rj + wrapn(k + 1, n);
-    if (c < cells) {
-      su[c] = u[c];
-      ss[c] = s[c];
+__device__ __forceinline__ void fr_relax(const FrSite &x, double *u, const double *sv, const FrLevel &L) {
+  const double nb = nb6<NE>(u[x.nb[0]], u[x.nb[1]], u[x.nb[2]], u[x.nb[3]], u[x.nb[4]], u[x.nb[5]]);
+  const double p = fma(nb, -1.0 / 6.0, L.ps * sv[x.c]);
+  u[x.c] = root_near<NE>(u[x.c], p, L.q);
+}
+
+// N_h(u) at cell c
+__device__ __forceinline__ double fr_operator(const double *u, const FrLevel &L, double K, int ne, int c) {
+  int i, j, k;
+  cell_ijk((unsigned)c, L.n, i, j, k);
+  const double uc = u[c];
+  return L.a_op * (nb_sum(u, L.n, i, j, k, ne) - 6.0 * pow_n1(uc, ne)) - K / uc;
+}
+
+template <int NE>
+__global__ __launch_bounds__(kFrSmallThreads) void k_fr_small(double *__restrict__ ug,
+                                                              const double *__restrict__ sg,
+                                                              FrProgram P, double K) {
+  // per level u and s, below the top one also u0, and d of the finer grid of a restriction
+  constexpr int kNext = kFrSmallMax / 8, kLast = kFrSmallMax / 64;
+  __shared__ double lds[3 * kFrSmallMax + 3 * kNext + 3 * kLast];
+  double *const d = lds + 2 * kFrSmallMax;
+  auto u_of = [&](int l) { return lds + (l == 0 ? 0 : (l == 1 ? 3 * kFrSmallMax : 3 * kFrSmallMax + 3 * kNext)); };
+  const int tid = threadIdx.x;
+  const auto cells_of = [&](int l) { return P.lev[l].n * P.lev[l].n * P.lev[l].n; };
+  {
+    const int cells = cells_of(0);
+    double *u = u_of(0), *sv = u + kFrSmallMax;
+    for (int c = tid; c < cells; c += kFrSmallThreads) {
+      u[c] = ug[c];
+      sv[c] = sg[c];
     }
   }
   __syncthreads();
-  for (int it = 0; it < sweeps; ++it)
-    for (int colour = 0; colour < 2; ++colour) {
+  for (int pc = 0; pc < P.nops; ++pc) {
+    const int op = P.op[pc] >> 2, l = P.op[pc] & 3;
+    const FrLevel L = P.lev[l];
+    const int cells = cells_of(l), room = l == 0 ? kFrSmallMax : (l == 1 ? kNext : kLast);
+    double *u = u_of(l), *sv = u + room;
+    if (op == kFrOpDown) {
+      // d = s - N(u), then u0 = u = R u and s = R d + N(R u) of the coarse grid
+      for (int c = tid; c < cells; c += kFrSmallThreads) d[c] = sv[c] - fr_operator(u, L, K, NE, c);
+      __syncthreads();
+      const FrLevel C = P.lev[l + 1];
+      const int n = L.n, cc = cells_of(l + 1), croom = l == 0 ? kNext : kLast;
+      double *uc = u_of(l + 1), *sc = uc + croom, *u0 = sc + croom;
+      for (int t = tid; t < 2 * cc; t += kFrSmallThreads) {
+        const bool resid = t >= cc;
+        const double *src = resid ? d : u;
+        const int c = resid ? t - cc : t;
+        int I, J, Kc;
+        cell_ijk((unsigned)c, C.n, I, J, Kc);
+        constexpr double w[4] = {0.125, 0.375, 0.375, 0.125};
+        double sum = 0.0;
 #pragma unroll
-      for (int m = 0; m < kCC; ++m) {
-        const int c = cell[m];
-        if (c < 0 || colour_of[m] != colour) continue;
-        const double nb = nb6<NE>(su[nbr[m][0]], su[nbr[m][1]], su[nbr[m][2]], su[nbr[m][3]],
-                                  su[nbr[m][4]], su[nbr[m][5]]);
-        const double p = fma(nb, -1.0 / 6.0, L.ps * ss[c]);
-        su[c] = NE == 1 ? root3(p, L.q) : root4(p, L.q);
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const double *r = src + (wrapn(2 * I - 1 + a, n) * n + wrapn(2 * J - 1 + b, n)) * n;
+            double tr = 0.0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tr += w[e] * r[wrapn(2 * Kc - 1 + e, n)];
+            sum += w[a] * w[b] * tr;
+          }
+        if (resid) {
+          sc[c] = sum;
+        } else {
+          u0[c] = sum;
+          uc[c] = sum;
+        }
       }
       __syncthreads();
-    }
+      for (int c = tid; c < cc; c += kFrSmallThreads) sc[c] += fr_operator(u0, C, K, NE, c);
+      __syncthreads();
+    } else if (op == kFrOpUp) {
+      // u += P(uH - u0): per axis 3/4 of the nearest coarse centre and 1/4 of the next one
+      const int N = P.lev[l + 1].n, n = L.n, cc = cells_of(l + 1), croom = l == 0 ? kNext : kLast;
+      double *uc = u_of(l + 1), *e = uc + 2 * croom;
+      for (int c = tid; c < cc; c += kFrSmallThreads) e[c] = uc[c] - e[c];
+      __syncthreads();
+      for (int c = tid; c < cells; c += kFrSmallThreads) {
+        int i, j, k;
+        cell_ijk((unsigned)c, n, i, j, k);
+        const int I[2] = {i >> 1, wrapn((i >> 1) + ((i & 1) ? 1 : -1), N)};
+        const int J[2] = {j >> 1, wrapn((j >> 1) + ((j & 1) ? 1 : -1), N)};
+        const int k0 = k >> 1, k1 = wrapn(k0 + ((k & 1) ? 1 : -1), N);
+        constexpr double w[2] = {0.75, 0.25};
+        double v = 0.0;
 #pragma unroll
-  for (int m = 0; m < kCC; ++m)
-    if (cell[m] >= 0) u[cell[m]] = su[cell[m]];
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            const double *r = e + (I[a] * N + J[b]) * N;
+            v += w[a] * w[b] * (w[0] * r[k0] + w[1] * r[k1]);
+          }
+        u[c] += v;
+      }
+      __syncthreads();
+    } else {
+      // red-black sweeps; the coarsest grid's and the pre-sweeps begin with colour 0
+      const int sweeps = op == kFrOpCoarse ? P.coarse_sweeps : (op == kFrOpPre ? P.pre : P.post);
+      const int first = op == kFrOpPost ? 1 : 0, half = cells / 2;
+      if (half <= 64) {
+        // one wave, whose LDS accesses are performed in order: no barrier between colours
+        if (tid < 64) {
+          const FrSite x0(min(tid, half - 1), L.n, first), x1(min(tid, half - 1), L.n, 1 - first);
+          for (int it = 0; it < sweeps; ++it) {
+            if (tid < half) fr_relax<NE>(x0, u, sv, L);
+            wave_order();
+            if (tid < half) fr_relax<NE>(x1, u, sv, L);
+            wave_order();
+          }
+        }
+        __syncthreads();
+      } else {
+        for (int it = 0; it < 2 * sweeps; ++it) {
+          for (int t = tid; t < half; t += kFrSmallThreads)
+            fr_relax<NE>(FrSite(t, L.n, (it & 1) ^ first), u, sv, L);
+          __syncthreads();
+        }
+      }
+    }
+  }
+  const int cells = cells_of(0);
+  for (int c = tid; c < cells; c += kFrSmallThreads) ug[c] = lds[c];
 }
 
 // s = -cA (rho - mean) - K
@@ -938,21 +1090,47 @@ struct FrRun {
     return hipGetLastError();
   }
 
+  // the coarsest grid where k_fr_small does not take it
   hipError_t coarsest(int l, double *u) {
-    const FrLevel L = level(l);
-    if ((int64_t)L.n * L.n * L.n <= kFrCoarseMax) {
-      if (ne == 1)
-        k_fr_coarse<1><<<1, kFrCoarseThreads, 0, s>>>(u, ctx->fr_lev[l].s, L, p->fr_coarse_sweeps);
-      else
-        k_fr_coarse<2><<<1, kFrCoarseThreads, 0, s>>>(u, ctx->fr_lev[l].s, L, p->fr_coarse_sweeps);
-      return hipGetLastError();
-    }
     for (int it = 0; it < p->fr_coarse_sweeps; ++it)
       if (hipError_t e = sweep(l, u, 0)) return e;
     return hipSuccess;
   }
 
+  // The steps of `cycle` from level l of the program down (top: the level it starts at).
+  void write_program(FrProgram &P, int top, int l, int kind) const {
+    const auto put = [&](int op) { P.op[P.nops++] = (unsigned char)(op * 4 + l - top); };
+    if (l == ctx->fr_nlev - 1) {
+      put(kFrOpCoarse);
+      return;
+    }
+    put(kFrOpPre);
+    put(kFrOpDown);
+    write_program(P, top, l + 1, kind);
+    if (kind != PM_CYCLE_V) write_program(P, top, l + 1, kind == PM_CYCLE_W ? PM_CYCLE_W : PM_CYCLE_V);
+    put(kFrOpUp);
+    put(kFrOpPost);
+  }
+  // grids of at most kFrSmallMax cells below the finest one, whose sweeps are timed as such
+  bool small(int l) const {
+    const int64_t n = ctx->fr_lev[l].n;
+    return l > 0 && n * n * n <= kFrSmallMax && ctx->fr_nlev - l <= 3;
+  }
+  hipError_t small_cycle(int l, double *u, int kind) {
+    FrProgram P{};
+    P.nlev = ctx->fr_nlev - l;
+    P.pre = p->fr_pre;
+    P.post = p->fr_post;
+    P.coarse_sweeps = p->fr_coarse_sweeps;
+    for (int m = 0; m < P.nlev; ++m) P.lev[m] = level(l + m);
+    write_program(P, l, l, kind);  // (at most 2 + 4 visits' four steps and 4 coarsest solves)
+    if (ne == 1) k_fr_small<1><<<1, kFrSmallThreads, 0, s>>>(u, ctx->fr_lev[l].s, P, K);
+    else k_fr_small<2><<<1, kFrSmallThreads, 0, s>>>(u, ctx->fr_lev[l].s, P, K);
+    return hipGetLastError();
+  }
+
   hipError_t cycle(int l, double *u, int kind) {
+    if (small(l)) return small_cycle(l, u, kind);
     if (l == ctx->fr_nlev - 1) return coarsest(l, u);
     const FrLevel L = level(l);
     const int64_t cells = (int64_t)L.n * L.n * L.n;
