@@ -44,11 +44,11 @@ MEASURED_TRAFFIC = {
                628408.0, 524301.0, 2.0, 1.0),
     # deposit: the particle-owned tile kernel plus the gather pass over the tile boxes
     "deposit": ("paper_2410_20501_amd/csrc/particles.hip",
-                "308bad8e89e30c243fa67ca6bd23dd537a0c1b315361ebdd5cbdcc4194bf4b0d",
+                "c7c6d1d599da8a112a4782295f0ea8ec6a17c29bca8f964dd1a057e626e6182b",
                 2005610.0, 1549791.0, 2.0, 1.0),
     # interpolation with the fused gradient, kicks and drift of a chained step
     "interp": ("paper_2410_20501_amd/csrc/particles.hip",
-               "308bad8e89e30c243fa67ca6bd23dd537a0c1b315361ebdd5cbdcc4194bf4b0d",
+               "c7c6d1d599da8a112a4782295f0ea8ec6a17c29bca8f964dd1a057e626e6182b",
                2749282.0, 5320506.0, 2.0, 1.0),
 }
 

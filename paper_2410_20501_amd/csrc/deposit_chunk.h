@@ -13,8 +13,11 @@
 //   3. each touched cell of the box is added to the grid with one FP32 global
 //      atomic (so the last bits may differ between runs), or, for a 64-bit
 //      fixed-point grid, one integer global atomic (exact: the same in every run).
-// Chunks whose box exceeds the LDS table fall back to one global atomic per
-// weight. Which particles form a chunk is the caller's choice (an Index object
+// A chunk whose box exceeds the LDS table is taken as parts of one slot per thread, and
+// such a part as its four waves' slots, each with a box of its own; a wave whose box exceeds
+// it still falls back to one global atomic per weight. (Rows of a lattice displaced by 0.3 cells rms: at 128^3 every chunk exceeds the
+// table and a part seldom, 969 -> 157 us; at 256^3 every part does and a wave seldom, 7990 ->
+// 1778; 256^3 in tile-major order 1864 -> 579.) Which particles form a chunk is the caller's choice (an Index object
 // maps the chunk's slots to particle rows, -1 for an empty slot): runs of
 // consecutive rows after a tile-major reorder, or lattice blocks of particles
 // that started on a lattice.
@@ -232,7 +235,8 @@ struct LatticeIndex {
 // integer global atomics instead of FP32 ones, so the grid is exact and the same for
 // every order of the particles and chunks (rho and mass are then unused); each
 // (particle, cell) weight becomes the same integer on the LDS path and the fallback.
-template <int MAS, int PK, class Index, bool FIXED = false>
+// PPT: slots per thread of the chunk.
+template <int MAS, int PK, class Index, bool FIXED = false, int PPT = kGPPT>
 __device__ void deposit_chunk(const float *__restrict__ pos, const int32_t *__restrict__ cell,
                               const Index idx, int n, float mass, float *__restrict__ rho,
                               unsigned long long *__restrict__ fixg = nullptr) {
@@ -244,12 +248,12 @@ __device__ void deposit_chunk(const float *__restrict__ pos, const int32_t *__re
     particle_cell<PK>(pos, cell, idx.ref(), n, ref, o);
   }
   // 1. cells relative to the reference particle, and their bounding box
-  int lc[kGPPT][3];
-  float lo_f[kGPPT][3];
-  bool ok[kGPPT];
+  int lc[PPT][3];
+  float lo_f[PPT][3];
+  bool ok[PPT];
   int lo[3] = {n, n, n}, hi[3] = {-n, -n, -n};
 #pragma unroll
-  for (int m = 0; m < kGPPT; ++m) {
+  for (int m = 0; m < PPT; ++m) {
     const int64_t p = idx(threadIdx.x + m * kGThreads);
     ok[m] = p >= 0;
     int c[3] = {0, 0, 0};
@@ -267,98 +271,137 @@ __device__ void deposit_chunk(const float *__restrict__ pos, const int32_t *__re
     }
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int g[3];  // the box: extent, lo its first cell
+  // (an empty box has its first cell above its last; a wide one ends the product early)
+  auto volume = [&]() {
+    if (g[0] < 3) return 0;
+    return g[0] * g[1] > kGTable ? kGTable + 1 : g[0] * g[1] * g[2];
+  };
+  auto box = [&]() {  // of the block's lo, hi (in place)
+    __syncthreads();
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const int l = wave_min_i(lo[a]), h = wave_max_i(hi[a]);
-    if (lane == 0) {
-      red[a][wave] = l;
-      red[3 + a][wave] = h;
+    for (int a = 0; a < 3; ++a) {
+      const int l = wave_min_i(lo[a]), h = wave_max_i(hi[a]);
+      if (lane == 0) {
+        red[a][wave] = l;
+        red[3 + a][wave] = h;
+      }
     }
-  }
-  __syncthreads();
-  int g[3];
+    __syncthreads();
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    int l = red[a][0], h = red[3 + a][0];
-    for (int w = 1; w < kGThreads / 64; ++w) {
-      l = min(l, red[a][w]);
-      h = max(h, red[3 + a][w]);
+    for (int a = 0; a < 3; ++a) {
+      int l = red[a][0], h = red[3 + a][0];
+      for (int w = 1; w < kGThreads / 64; ++w) {
+        l = min(l, red[a][w]);
+        h = max(h, red[3 + a][w]);
+      }
+      lo[a] = l;
+      g[a] = h - l + 3;  // grown by the window's reach of one cell per side
     }
-    lo[a] = l;
-    g[a] = h - l + 3;  // grown by the window's reach of one cell per side
-  }
-  const int gvol = g[0] * g[1] * g[2];
-  if (gvol > kGTable) {
-    // fallback: global atomics per weight
+    return volume();
+  };
+  int gvol = box();
+  const int step = PPT > 1 && gvol > kGTable ? 1 : PPT;  // slots per thread taken together
+  const float kFix = 1073741824.0f;                      // 2^30
 #pragma unroll 1
-    for (int m = 0; m < kGPPT; ++m) {
-      const int64_t p = idx(threadIdx.x + m * kGThreads);
-      if (p < 0) continue;
-      int f[3];
-      float w[3][MAS];
-      particle_support<MAS, PK>(pos, cell, p, n, f, w);
-      for (int a = 0; a < MAS; ++a) {
-        const size_t ia = (size_t)wrap_index(f[0] + a, n) * n;
-        for (int b = 0; b < MAS; ++b) {
-          const size_t row = (ia + wrap_index(f[1] + b, n)) * n;
-          if constexpr (FIXED) {
-            const float wab = w[0][a] * w[1][b] * 1073741824.0f;  // 2^30, as below
+  for (int m0 = 0; m0 < PPT; m0 += step) {
+    if (step < PPT) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        lo[a] = n;
+        hi[a] = -n;
+#pragma unroll
+        for (int m = 0; m < PPT; ++m)
+          if (m == m0 && ok[m]) lo[a] = hi[a] = lc[m][a];
+      }
+      gvol = box();
+    }
+    const bool split = gvol > kGTable;  // (red still holds the waves' extents)
+#pragma unroll 1
+    for (int w0 = 0; w0 < (split ? kGThreads / 64 : 1); ++w0) {
+      if (split) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          lo[a] = red[a][w0];
+          g[a] = red[3 + a][w0] - lo[a] + 3;
+        }
+        gvol = volume();
+      }
+      const bool mine = !split || wave == w0;
+      if (gvol == 0) continue;
+      if (gvol > kGTable) {
+        // fallback: global atomics per weight
+#pragma unroll 1
+        for (int m = m0; m < m0 + step; ++m) {
+          const int64_t p = idx(threadIdx.x + m * kGThreads);
+          if (p < 0 || !mine) continue;
+          int f[3];
+          float w[3][MAS];
+          particle_support<MAS, PK>(pos, cell, p, n, f, w);
+          for (int a = 0; a < MAS; ++a) {
+            const size_t ia = (size_t)wrap_index(f[0] + a, n) * n;
+            for (int b = 0; b < MAS; ++b) {
+              const size_t row = (ia + wrap_index(f[1] + b, n)) * n;
+              if constexpr (FIXED) {
+                const float wab = w[0][a] * w[1][b] * kFix;
+                for (int c = 0; c < MAS; ++c)
+                  atomicAdd(&fixg[row + wrap_index(f[2] + c, n)],
+                            (unsigned long long)(unsigned)rintf(wab * w[2][c]));
+              } else {
+                const float wab = mass * w[0][a] * w[1][b];
+                for (int c = 0; c < MAS; ++c)
+                  unsafeAtomicAdd(&rho[row + wrap_index(f[2] + c, n)], wab * w[2][c]);
+              }
+            }
+          }
+        }
+        continue;
+      }
+      // 2. scatter the window weights into the LDS box (integer atomics: exact sums)
+      if (w0 > 0) __syncthreads();  // the last wave's box has been read
+      for (int i = threadIdx.x; i < gvol; i += kGThreads) acc[i] = 0ull;
+      __syncthreads();
+#pragma unroll 2
+      for (int m = 0; m < PPT; ++m) {
+        if (!ok[m] || !mine || m < m0 || m >= m0 + step) continue;
+        int f[3];
+        float w[3][MAS];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          // local index of the particle's cell is lc - lo + 1; the window's first cell
+          // is one below it (TSC), or at or one below it (CIC)
+          f[a] = axis_off<MAS>(lc[m][a] - lo[a] + 1, lo_f[m][a], w[a]);
+        }
+#pragma unroll
+        for (int a = 0; a < MAS; ++a) {
+#pragma unroll
+          for (int b = 0; b < MAS; ++b) {
+            const int row = ((f[0] + a) * g[1] + (f[1] + b)) * g[2] + f[2];
+            const float wab = w[0][a] * w[1][b] * kFix;
+#pragma unroll
             for (int c = 0; c < MAS; ++c)
-              atomicAdd(&fixg[row + wrap_index(f[2] + c, n)],
-                        (unsigned long long)(unsigned)rintf(wab * w[2][c]));
-          } else {
-            const float wab = mass * w[0][a] * w[1][b];
-            for (int c = 0; c < MAS; ++c)
-              unsafeAtomicAdd(&rho[row + wrap_index(f[2] + c, n)], wab * w[2][c]);
+              atomicAdd(&acc[row + c], (unsigned long long)(unsigned)rintf(wab * w[2][c]));
           }
         }
       }
-    }
-    return;
-  }
-  // 2. scatter the window weights into the LDS box (integer atomics: exact sums)
-  for (int i = threadIdx.x; i < gvol; i += kGThreads) acc[i] = 0ull;
-  __syncthreads();
-  const float kFix = 1073741824.0f;  // 2^30
-#pragma unroll 2
-  for (int m = 0; m < kGPPT; ++m) {
-    if (!ok[m]) continue;
-    int f[3];
-    float w[3][MAS];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      // local index of the particle's cell is lc - lo + 1; the window's first cell
-      // is one below it (TSC), or at or one below it (CIC)
-      f[a] = axis_off<MAS>(lc[m][a] - lo[a] + 1, lo_f[m][a], w[a]);
-    }
-#pragma unroll
-    for (int a = 0; a < MAS; ++a) {
-#pragma unroll
-      for (int b = 0; b < MAS; ++b) {
-        const int row = ((f[0] + a) * g[1] + (f[1] + b)) * g[2] + f[2];
-        const float wab = w[0][a] * w[1][b] * kFix;
-#pragma unroll
-        for (int c = 0; c < MAS; ++c)
-          atomicAdd(&acc[row + c], (unsigned long long)(unsigned)rintf(wab * w[2][c]));
+      __syncthreads();
+      // 3. one global atomic per touched cell
+      const float scale = mass * (1.0f / kFix);
+      const int g12 = g[1] * g[2];
+      for (int t = threadIdx.x; t < gvol; t += kGThreads) {
+        const unsigned long long v = acc[t];
+        if (v == 0ull) continue;
+        const int x = t / g12, r = t - x * g12;
+        const int y = r / g[2], z = r - y * g[2];
+        const int gi = wrap_any(ref[0] + lo[0] - 1 + x, n);
+        const int gj = wrap_any(ref[1] + lo[1] - 1 + y, n);
+        const int gk = wrap_any(ref[2] + lo[2] - 1 + z, n);
+        if constexpr (FIXED)
+          atomicAdd(&fixg[((size_t)gi * n + gj) * n + gk], v);
+        else
+          unsafeAtomicAdd(&rho[((size_t)gi * n + gj) * n + gk], (float)v * scale);
       }
     }
-  }
-  __syncthreads();
-  // 3. one global atomic per touched cell
-  const float scale = mass * (1.0f / kFix);
-  const int g12 = g[1] * g[2];
-  for (int t = threadIdx.x; t < gvol; t += kGThreads) {
-    const unsigned long long v = acc[t];
-    if (v == 0ull) continue;
-    const int x = t / g12, r = t - x * g12;
-    const int y = r / g[2], z = r - y * g[2];
-    const int gi = wrap_any(ref[0] + lo[0] - 1 + x, n);
-    const int gj = wrap_any(ref[1] + lo[1] - 1 + y, n);
-    const int gk = wrap_any(ref[2] + lo[2] - 1 + z, n);
-    if constexpr (FIXED)
-      atomicAdd(&fixg[((size_t)gi * n + gj) * n + gk], v);
-    else
-      unsafeAtomicAdd(&rho[((size_t)gi * n + gj) * n + gk], (float)v * scale);
   }
 }
 

@@ -236,8 +236,46 @@ hipError_t launch_gradient(const float *phi, int n, int points, float *g, hipStr
   return hipGetLastError();
 }
 
+// Both in one launch for a grid of up to kMomentsOne cells (32^3: 7.2 -> 4.4 us).
+constexpr int64_t kMomentsOne = 65536;
+constexpr int kMomentsThreads = 1024;
+__global__ __launch_bounds__(kMomentsThreads) void k_moments_one(const float *__restrict__ x, int count,
+                                                                 double *__restrict__ result,
+                                                                 float *__restrict__ mean_out) {
+  double s1 = 0.0, s2 = 0.0;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < count; i += kMomentsThreads) {
+    const double d = x[i];
+    s1 += d;
+    s2 += d * d;
+  }
+  __shared__ double l1[kMomentsThreads / 64], l2[kMomentsThreads / 64];
+  s1 = wave_sum(s1);
+  s2 = wave_sum(s2);
+  if ((threadIdx.x & 63) == 0) {
+    l1[threadIdx.x >> 6] = s1;
+    l2[threadIdx.x >> 6] = s2;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double a = 0.0, b = 0.0;
+    for (int w = 0; w < kMomentsThreads / 64; ++w) {
+      a += l1[w];
+      b += l2[w];
+    }
+    result[0] = a;
+    result[1] = b;
+    result[2] = count > 0 ? a / (double)count : 0.0;
+    if (mean_out) mean_out[0] = (float)result[2];
+  }
+}
+
 hipError_t launch_sum_moments(const float *x, int64_t count, double *partial, double *result,
                               float *mean_out, hipStream_t s) {
+  if (count <= kMomentsOne) {
+    k_moments_one<<<1, kMomentsThreads, 0, s>>>(x, (int)count, result, mean_out);
+    return hipGetLastError();
+  }
   int nb = (int)std::min<int64_t>(RED_BLOCKS, (count + RED_THREADS - 1) / RED_THREADS);
   if (nb < 1) nb = 1;
   if ((reinterpret_cast<uintptr_t>(x) & 15) == 0)

@@ -10,8 +10,6 @@ namespace {
 
 using pm_chunk::axis_box;
 using pm_chunk::axis_off;
-using pm_chunk::kGChunk;
-using pm_chunk::kGPPT;
 using pm_chunk::kGThreads;
 using pm_chunk::min_image;
 using pm_chunk::particle_cell;
@@ -305,13 +303,15 @@ __global__ __launch_bounds__(kThreads) void k_gather_perm(const T *__restrict__ 
 
 // ------------------------------------------------------------------ chunked gather deposit
 
-template <int MAS, int PK>
-__global__ __launch_bounds__(kGThreads) void k_deposit_chunk(const float *__restrict__ pos,
+constexpr int64_t kChunkWide = 4000000, kChunkNarrow = 200000;  // (launch_deposit_atomic)
+template <int MAS, int PK, int PPT>
+__global__ __launch_bounds__(kGThreads, 3) void k_deposit_chunk(const float *__restrict__ pos,
                                                              const int32_t *__restrict__ cell,
                                                              int64_t np, int n, float mass,
                                                              float *__restrict__ rho) {
-  const int64_t base = (int64_t)blockIdx.x * kGChunk;
-  pm_chunk::deposit_chunk<MAS, PK>(pos, cell, pm_chunk::RangeIndex{base, np}, n, mass, rho);
+  const int64_t base = (int64_t)blockIdx.x * (kGThreads * PPT);
+  pm_chunk::deposit_chunk<MAS, PK, pm_chunk::RangeIndex, false, PPT>(
+      pos, cell, pm_chunk::RangeIndex{base, np}, n, mass, rho);
 }
 
 // Scatter of the counting sort: every particle takes the next place of its key's
@@ -1335,23 +1335,30 @@ __global__ __launch_bounds__(kIThreads) void k_interp_tile_phi(float *__restrict
 hipError_t launch_deposit_atomic(const float *pos, const int32_t *cell, int64_t np, int poskind,
                                  int mas, int n, float mass, float *rho, hipStream_t s) {
   if (np == 0) return hipSuccess;
-  const unsigned nb = blocks_for(np, kGChunk);
-  if (mas == PM_TSC) {
-    if (poskind == PM_POS_BOX)
-      k_deposit_chunk<3, PM_POS_BOX><<<nb, kGThreads, 0, s>>>(pos, cell, np, n, mass, rho);
-    else
-      k_deposit_chunk<3, PM_POS_CELLOFF><<<nb, kGThreads, 0, s>>>(pos, cell, np, n, mass, rho);
-  } else if (mas == PM_NGP) {
-    if (poskind == PM_POS_BOX)
-      k_deposit_chunk<1, PM_POS_BOX><<<nb, kGThreads, 0, s>>>(pos, cell, np, n, mass, rho);
-    else
-      k_deposit_chunk<1, PM_POS_CELLOFF><<<nb, kGThreads, 0, s>>>(pos, cell, np, n, mass, rho);
-  } else {
-    if (poskind == PM_POS_BOX)
-      k_deposit_chunk<2, PM_POS_BOX><<<nb, kGThreads, 0, s>>>(pos, cell, np, n, mass, rho);
-    else
-      k_deposit_chunk<2, PM_POS_CELLOFF><<<nb, kGThreads, 0, s>>>(pos, cell, np, n, mass, rho);
-  }
+  // Particles per thread: a chunk of 8 a thread adds the fewest cells to the grid, but its
+  // serial chain is 50 us, so fewer where the chunks would leave most of the chip idle. Us
+  // with 8 | 2 | 1 a thread, lattice rows displaced by 0.3 cells rms: 32^3 52 | 23 | 11, 48^3
+  // 58 | 14 | 12, 64^3 69 | 16 | 19, 96^3 84 | 48 | 59, 128^3 153 | 147 | 128; particles in
+  // tile-major order: 64^3 61 | 16 | 21, 128^3 103 | 85 | 97, 256^3 578 | 634 | 662.
+#define PM_CHUNK(M, K, N_) \
+  k_deposit_chunk<M, K, N_><<<blocks_for(np, kGThreads * N_), kGThreads, 0, s>>>(pos, cell, np, n, mass, rho)
+#define PM_CHUNK_BY_COUNT(M, K)                              \
+  do {                                                       \
+    if (np > kChunkWide) PM_CHUNK(M, K, 8);                  \
+    else if (np > kChunkNarrow) PM_CHUNK(M, K, 2);           \
+    else PM_CHUNK(M, K, 1);                                  \
+  } while (0)
+#define PM_CHUNK_KIND(M)                                     \
+  do {                                                       \
+    if (poskind == PM_POS_BOX) PM_CHUNK_BY_COUNT(M, PM_POS_BOX); \
+    else PM_CHUNK_BY_COUNT(M, PM_POS_CELLOFF);               \
+  } while (0)
+  if (mas == PM_TSC) PM_CHUNK_KIND(3);
+  else if (mas == PM_NGP) PM_CHUNK_KIND(1);
+  else PM_CHUNK_KIND(2);
+#undef PM_CHUNK_KIND
+#undef PM_CHUNK_BY_COUNT
+#undef PM_CHUNK
   return hipGetLastError();
 }
 
