@@ -15,9 +15,10 @@
 //      fixed-point grid, one integer global atomic (exact: the same in every run).
 // A chunk whose box exceeds the LDS table is taken as parts of one slot per thread, and
 // such a part as its four waves' slots, each with a box of its own; a wave whose box exceeds
-// it still falls back to one global atomic per weight. (Rows of a lattice displaced by 0.3 cells rms: at 128^3 every chunk exceeds the
-// table and a part seldom, 969 -> 157 us; at 256^3 every part does and a wave seldom, 7990 ->
-// 1778; 256^3 in tile-major order 1864 -> 579.) Which particles form a chunk is the caller's choice (an Index object
+// it still falls back to one global atomic per weight. (Rows of a lattice displaced by 0.3
+// cells rms: at 128^3 every chunk exceeds the table and a part seldom, 969 -> 157 us; at
+// 256^3 every part does and a wave seldom, 7990 -> 1778; 256^3 in tile-major order 1864 ->
+// 579.) Which particles form a chunk is the caller's choice (an Index object
 // maps the chunk's slots to particle rows, -1 for an empty slot): runs of
 // consecutive rows after a tile-major reorder, or lattice blocks of particles
 // that started on a lattice.
