@@ -110,7 +110,7 @@ enum pm_guess {
 /* pm_create flags */
 enum pm_create_flags {
   /* Run every multigrid level with the plain one-kernel-per-half-sweep kernels
-   * instead of the fused streaming kernels (a reference for testing; slower). */
+   * instead of the fused streaming and tile kernels (a reference for testing; slower). */
   PM_CREATE_REFERENCE_KERNELS = 1,
   /* pm_accel, pm_kdk and pm_kdk_chain first count the non-finite values of the
    * positions (and velocities) they are given, one pass over those arrays and a host
@@ -288,7 +288,7 @@ int pm_solve_fft_kernel(pm_ctx *ctx, const float *rho, float coef, int kernel, i
 /* pm_solve_fft without a context and without allocating, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc). The spectrum, tables and the mean's partial sums live in a
- * statically sized device array of the library (about 12.6 MiB, held on each GPU the
+ * statically sized device array of the library (about 10 MiB, held on each GPU the
  * library runs on until the process ends); n must be a power of two, 8 .. 128
  * (PM_ERR_SHAPE otherwise). Same kernels and result as pm_solve_fft with the same n,
  * coef and deconv (0 .. 3). rho and phi: device arrays [n][n][n] owned by the caller.
