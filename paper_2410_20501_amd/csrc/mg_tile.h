@@ -227,8 +227,11 @@ __device__ __forceinline__ void tile_down(const Level &a, int i0, int j0, int k0
       float rE, rO;
       residual<S>(i, a, p, c, LE, LO, rE, rO);
       if (p.inside && i0 + i - S::H < a.n) {
-        sum[0] += (double)fmaf(rE, rE, rO * rO);
-        sum[1] += (double)fmaf(c.fE[i], c.fE[i], c.fO[i] * c.fO[i]);
+        // (squared in FP64: a source of any size, a cotangent among them, keeps its norm; a
+        // solve takes as long as with FP32 squares, 128^3 658 against 657 us)
+        const double a64 = rE, b64 = rO, f64 = c.fE[i], g64 = c.fO[i];
+        sum[0] = fma(a64, a64, fma(b64, b64, sum[0]));
+        sum[1] = fma(f64, f64, fma(g64, g64, sum[1]));
         sum[2] += (double)(c.uE[i] + c.uO[i]);
       }
     }
