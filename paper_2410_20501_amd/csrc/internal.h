@@ -233,8 +233,8 @@ int pm_mg_setup(pm_ctx *ctx);
 
 // mg_stream.hip
 int64_t smooth_stream_blocks(int n);
-// partial != NULL: the pass also sums ||f - L u||^2, ||f||^2 and sum u of its input,
-// three doubles per block; uscale multiplies the input as it is read; ec != NULL (not
+// partial != NULL: the pass also sums ||f - L u||^2 and ||f||^2 of its input and sum u of
+// its output, three doubles per block; uscale multiplies the input as it is read; ec != NULL (not
 // with partial): the input is uin + P ec, the trilinear prolongation of the coarse
 // correction ec ((n/2)^3) added as each plane is read
 hipError_t launch_smooth_stream(const float *uin, float *uout, const float *f, float fscale,

@@ -330,7 +330,7 @@ __device__ __forceinline__ void report_norms(const Report &r, double *lds) {
     __hip_atomic_store(r.host + i, word[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     r.result[i] = t[i];
   }
-  *r.mean = (float)(t[2] / (double)r.count);  // mean of the input
+  *r.mean = (float)(t[2] / (double)r.count);  // mean of the pass's output
 }
 
 __global__ __launch_bounds__(RED_THREADS) void k_report(Report r) {
@@ -1037,8 +1037,7 @@ int pm_mg_solve(pm_ctx *ctx, const float *rho, float coef, float *phi, const pm_
           return PM_OK;
         }
         // the norm pass smoothed the tested iterate twice more: keep its output (smoothing
-        // does not raise the error); its mean is taken as the tested iterate's (the pass
-        // changes it by far less than the solve's error)
+        // does not raise the error), whose sum it has taken
         have_sum = fused_norm;
         break;
       }

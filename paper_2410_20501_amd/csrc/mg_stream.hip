@@ -132,7 +132,7 @@ struct SmoothState {
   float fE[S::RING][S::PP], fO[S::RING][S::PP];  // fscale (f - mean)
   static constexpr int PF = smooth_prefetch<H, NORM, PRO>();
   float2 pu[PF][S::PP], pf[PF][S::PP];            // planes in flight from HBM
-  double s_r, s_f, s_u;  // NORM: ||f - L u||^2, ||f||^2 and sum u of the input
+  double s_r, s_f, s_u;  // NORM: ||f - L u||^2 and ||f||^2 of the input, sum u of the output
   // PRO: u += P e as each plane enters (trilinear prolongation of the coarse correction)
   const float *ec;          // coarse grid, nc^3
   float *craw;              // LDS: one raw coarse plane
@@ -289,7 +289,6 @@ __device__ __forceinline__ void smooth_norm(SmoothState<H, true, OMEGA1, PRO> &c
   const float *PE = c.lds + lds_prev_slot1<R, H>() * Sh::SLOT, *PO = PE + Sh::ARR;
   // Squares in FP64: a source of any size keeps its norm (a solve at 512^3 takes 12.1 ms as
   // with FP32 squares, at 256^3 2.14 to 2.16 ms against 2.14).
-  float su = 0.f;  // this plane's few terms in FP32, their sum in FP64
 #pragma unroll
   for (int t = 0; t < PP; ++t) {
     if (!c.inside[t]) continue;
@@ -304,9 +303,7 @@ __device__ __forceinline__ void smooth_norm(SmoothState<H, true, OMEGA1, PRO> &c
     const double da = ra, db = rb, ga = fa, gb = fb;
     c.s_r = fma(da, da, fma(db, db, c.s_r));
     c.s_f = fma(ga, ga, fma(gb, gb, c.s_f));
-    su += a + b;
   }
-  c.s_u += su;
 }
 
 template <int R, int S, int H, bool NORM, bool OMEGA1, bool PRO>
@@ -403,6 +400,7 @@ __device__ __forceinline__ void smooth_step(SmoothState<H, NORM, OMEGA1, PRO> &c
     for (int t = 0; t < PP; ++t)
       if (c.inside[t]) {
         const float a = c.uE[cH][t], b = c.uO[cH][t];
+        if constexpr (NORM) c.s_u += (double)a + (double)b;
         *reinterpret_cast<float2 *>(c.uout + op + c.col[t]) =
             c.swp[t] ? make_float2(b, a) : make_float2(a, b);
       }

@@ -209,7 +209,7 @@ __device__ __forceinline__ void store(const Level &a, const Pair<S> &p, int i0, 
 
 // hs half-sweeps on the tile at (i0, j0, k0), red first, and the restriction of the
 // residual after them to fc (NULL: left out). NORM: sum[0..2] receive this thread's part
-// of ||f - L u||^2, ||f||^2 and sum u of the input over the tile's interior.
+// of ||f - L u||^2 and ||f||^2 of the input and of the output's sum over the tile's interior.
 template <int TI, int TJ, int TK, int KIND, bool OM1, bool NORM>
 __device__ __forceinline__ void tile_down(const Level &a, int i0, int j0, int k0, int hs,
                                           float *__restrict__ fc, float *lds, double (&sum)[3]) {
@@ -232,13 +232,17 @@ __device__ __forceinline__ void tile_down(const Level &a, int i0, int j0, int k0
         const double a64 = rE, b64 = rO, f64 = c.fE[i], g64 = c.fO[i];
         sum[0] = fma(a64, a64, fma(b64, b64, sum[0]));
         sum[1] = fma(f64, f64, fma(g64, g64, sum[1]));
-        sum[2] += (double)(c.uE[i] + c.uO[i]);
       }
     }
     __syncthreads();  // every read of the input's values precedes the first update
   }
   sweeps<S, 0, OM1>(hs, a, p, c, LE, LO);
   store<S>(a, p, i0, c);
+  if constexpr (NORM) {
+#pragma unroll
+    for (int i = S::H; i < S::H + S::TI; ++i)
+      if (p.inside && i0 + i - S::H < a.n) sum[2] += (double)c.uE[i] + (double)c.uO[i];
+  }
   if (!fc) return;
   // weights along i in registers: one value per coarse plane and column
   float cE[S::TI / 2], cO[S::TI / 2];
