@@ -20,9 +20,10 @@ struct pm_level {
 };
 
 #ifndef PM_STREAM_MIN_N
-#define PM_STREAM_MIN_N 256   // levels at least this large use the streaming kernels, smaller
-                             // ones the tile kernels (us per V(2,2) cycle: 128^3 105 against
-                             // 71, 192^3 274 against 174, 256^3 228 against 340)
+#define PM_STREAM_MIN_N 224   // levels at least this large use the streaming kernels, smaller
+                             // ones the tile kernels (us per V(2,2) cycle of a grid with
+                             // streaming | tile kernels on its finest level: 128^3 107 | 74,
+                             // 160^3 141 | 124, 192^3 178 | 176, 224^3 215 | 258, 256^3 235 | 340)
 #endif
 
 // one grid of the f(R) full-approximation-storage hierarchy (FP64)
