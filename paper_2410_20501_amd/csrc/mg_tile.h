@@ -230,8 +230,8 @@ __device__ __forceinline__ void tile_down(const Level &a, int i0, int j0, int k0
         // (squared in FP64: a source of any size, a cotangent among them, keeps its norm; a
         // solve takes as long as with FP32 squares, 128^3 658 against 657 us)
         const double a64 = rE, b64 = rO, f64 = c.fE[i], g64 = c.fO[i];
-        sum[0] = fma(a64, a64, fma(b64, b64, sum[0]));
-        sum[1] = fma(f64, f64, fma(g64, g64, sum[1]));
+        sum[0] += fma(a64, a64, b64 * b64);
+        sum[1] += fma(f64, f64, g64 * g64);
       }
     }
     __syncthreads();  // every read of the input's values precedes the first update
