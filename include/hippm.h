@@ -602,10 +602,12 @@ int pm_tune(pm_batch *batch, float *pos, float *phi, const pm_step_params *param
  *   PM_KERNEL_DEPOSIT  the deposit kernels of PM_DEPOSIT_SORTED (the tile
  *                      pass and the gather pass, or the cell gather);
  *                      algorithmic bytes 12 per particle + 4 per cell
- *   PM_KERNEL_SMOOTH   the streaming smoother on the finest grid (n >= 256);
- *                      algorithmic bytes 12 per cell per red-black sweep (a pass
- *                      fuses two sweeps: 24 per cell), + 0.5 per cell for the
- *                      post-smoothing pass that adds the prolongation
+ *   PM_KERNEL_SMOOTH   the smoothing passes on the finest grid (those of a context
+ *                      with a single level, n <= 18, and of a reference context
+ *                      apart); algorithmic bytes 12 per cell per red-black sweep
+ *                      (a pass fuses two sweeps: 24 per cell), + 0.5 per cell for a
+ *                      pass that adds the prolongation or, below 224 cells a
+ *                      side, restricts the residual
  *   PM_KERNEL_INTERP   interpolation (+ kick) in pm_accel/pm_kdk/pm_kdk_chain;
  *                      algorithmic bytes 48 per particle (+4 with cell indices)
  *                      + 12 per cell (force grid), or + 4 per cell with the

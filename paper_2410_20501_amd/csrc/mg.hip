@@ -599,6 +599,13 @@ struct Solver {
                           guess_factor(l), ctx->lev[l].n, hh, 1.0f / hh, p->omega};
   }
 
+  // algorithmic bytes of a tile pass of the finest level, counted as for a streaming one;
+  // coarse: it restricts or prolongs
+  double tile_bytes(int sweeps, bool coarse) const {
+    const double n = ctx->lev[0].n;
+    return (12.0 * sweeps + (coarse ? 0.5 : 0.0)) * n * n * n;
+  }
+
   // Down a tiled level: `left` sweeps in passes of at most two and, where `restricts`, in
   // the last pass the residual and its restriction. The first pass may start from the
   // Jacobi guess, scale its input, and sum the norms of it (partial).
@@ -608,8 +615,11 @@ struct Solver {
       if (stop) return hipSuccess;
       const int now = std::min(left, 2);
       left -= now;
+      const bool last = left == 0 && restricts;
+      if (l == 0) pm_kt_begin(ctx, PM_KERNEL_SMOOTH, s);
       launch_tile_down(tile_level(l, from_guess, uscale), src(l).mean, 2 * now,
-                       left == 0 && restricts ? ctx->lev[l + 1].f : nullptr, partial);
+                       last ? ctx->lev[l + 1].f : nullptr, partial);
+      if (l == 0) pm_kt_end(ctx, PM_KERNEL_SMOOTH, s, tile_bytes(now, last));
       std::swap(cur[l], alt[l]);
       const hipError_t e = launched();
       if (e != hipSuccess) return e;
@@ -628,7 +638,9 @@ struct Solver {
       if (stop) return hipSuccess;
       const int now = std::min(left, 2);
       left -= now;
+      if (l == 0) pm_kt_begin(ctx, PM_KERNEL_SMOOTH, s);
       launch_tile_up(tile_level(l, false, 1.0f), src(l).mean, ec, 2 * now);
+      if (l == 0) pm_kt_end(ctx, PM_KERNEL_SMOOTH, s, tile_bytes(now, ec != nullptr));
       std::swap(cur[l], alt[l]);
       const hipError_t e = launched();
       if (e != hipSuccess) return e;
