@@ -278,6 +278,12 @@ __device__ void deposit_chunk(const float *__restrict__ pos, const int32_t *__re
     if (g[0] < 3) return 0;
     return g[0] * g[1] > kGTable ? kGTable + 1 : g[0] * g[1] * g[2];
   };
+  // Cells of the largest box. A particle's one NGP weight costs an atomic either way, so a
+  // box pays only where it is small for its particles (8 cells a slot: half of them in clumps,
+  // in tile-major order, 256^3 315 -> 123 us against 4 cells a slot), and a search for smaller
+  // boxes does not pay (lattice rows by parts and waves: 256^3 1066 us, 128^3 80; so 291, 43).
+  constexpr bool kParts = MAS > 1;
+  constexpr int kRoom = kParts || 8 * PPT * kGThreads > kGTable ? kGTable : 8 * PPT * kGThreads;
   auto box = [&]() {  // of the block's lo, hi (in place)
     __syncthreads();
 #pragma unroll
@@ -302,7 +308,7 @@ __device__ void deposit_chunk(const float *__restrict__ pos, const int32_t *__re
     return volume();
   };
   int gvol = box();
-  const int step = PPT > 1 && gvol > kGTable ? 1 : PPT;  // slots per thread taken together
+  const int step = kParts && PPT > 1 && gvol > kRoom ? 1 : PPT;  // slots per thread taken together
   const float kFix = 1073741824.0f;                      // 2^30
 #pragma unroll 1
   for (int m0 = 0; m0 < PPT; m0 += step) {
@@ -317,7 +323,7 @@ __device__ void deposit_chunk(const float *__restrict__ pos, const int32_t *__re
       }
       gvol = box();
     }
-    const bool split = gvol > kGTable;  // (red still holds the waves' extents)
+    const bool split = kParts && gvol > kRoom;  // (red still holds the waves' extents)
 #pragma unroll 1
     for (int w0 = 0; w0 < (split ? kGThreads / 64 : 1); ++w0) {
       if (split) {
@@ -330,7 +336,7 @@ __device__ void deposit_chunk(const float *__restrict__ pos, const int32_t *__re
       }
       const bool mine = !split || wave == w0;
       if (gvol == 0) continue;
-      if (gvol > kGTable) {
+      if (gvol > kRoom) {
         // fallback: global atomics per weight
 #pragma unroll 1
         for (int m = m0; m < m0 + step; ++m) {
