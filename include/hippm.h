@@ -615,7 +615,9 @@ int pm_tune(pm_batch *batch, float *pos, float *phi, const pm_step_params *param
  *                      52 per particle (+8 with cell indices) + 4 per cell
  *   PM_KERNEL_FR_SWEEP the f(R) non-linear Gauss-Seidel sweep on the finest grid
  *                      (both colours, FP64): algorithmic bytes 32 per cell (u read
- *                      by each colour's pass, s read and u written once)
+ *                      by each colour's pass, s read and u written once); grids of
+ *                      10^3 and 14^3 cells, which have no coarser one, record a
+ *                      cycle's sweeps as one launch
  * pm_kernel_timer_read synchronises on the recorded events and returns the
  * summed elapsed time, the number of launches and the summed algorithmic
  * bytes; PM_WARN_NOT_CONVERGED if launches exceeded the pool. */

@@ -1111,10 +1111,12 @@ struct FrRun {
     put(kFrOpUp);
     put(kFrOpPost);
   }
-  // grids of at most kFrSmallMax cells below the finest one, whose sweeps are timed as such
+  // grids of at most kFrSmallMax cells below the finest one, whose sweeps are timed as such,
+  // and a finest grid that is the coarsest too (32 sweeps in one launch: 10^3 234 -> 60 us,
+  // 14^3 240 -> 151), which are timed as one launch a cycle
   bool small(int l) const {
     const int64_t n = ctx->fr_lev[l].n;
-    return l > 0 && n * n * n <= kFrSmallMax && ctx->fr_nlev - l <= 3;
+    return (l > 0 || ctx->fr_nlev == 1) && n * n * n <= kFrSmallMax && ctx->fr_nlev - l <= 3;
   }
   hipError_t small_cycle(int l, double *u, int kind) {
     FrProgram P{};
@@ -1124,8 +1126,11 @@ struct FrRun {
     P.coarse_sweeps = p->fr_coarse_sweeps;
     for (int m = 0; m < P.nlev; ++m) P.lev[m] = level(l + m);
     write_program(P, l, l, kind);  // (at most 2 + 4 visits' four steps and 4 coarsest solves)
+    if (l == 0) pm_kt_begin(ctx, PM_KERNEL_FR_SWEEP, s);
     if (ne == 1) k_fr_small<1><<<1, kFrSmallThreads, 0, s>>>(u, ctx->fr_lev[l].s, P, K);
     else k_fr_small<2><<<1, kFrSmallThreads, 0, s>>>(u, ctx->fr_lev[l].s, P, K);
+    const double n = ctx->n;
+    if (l == 0) pm_kt_end(ctx, PM_KERNEL_FR_SWEEP, s, 32.0 * p->fr_coarse_sweeps * n * n * n);
     return hipGetLastError();
   }
 
