@@ -504,11 +504,18 @@ extern "C" int pm_power_spectrum(pm_ctx *ctx, const float *rho, int deconv, int 
   // FP64 mean in red_result[2], FP32 mean (subtracted before the transform: a large mean
   // would set the scale of every mode's rounding) in mean_f[2]
   PM_HIP(ctx, launch_sum_moments(rho, N, ctx->red_partial, ctx->red_result, ctx->mean_f + 2, s));
-  // the reduction scratch (3 x RED_PARTIAL_CAP doubles): window table, totals, block sums
+  // the reduction scratch (3 x RED_PARTIAL_CAP doubles): window table, totals, and the block
+  // sums where it holds those of all the workgroups; else (125 of them with 512 shells, half
+  // a chip) they lie in the force grid, 3 n^3 floats of scratch. 512^3 with 256 shells 2708
+  // -> 2072 us, 1024^3 with 512 35.2 -> 18.8 ms.
   double *win = ctx->red_partial, *total = win + 1024, *partial = total + 3 * kPkMaxBins;
-  const int64_t room = 3 * (int64_t)RED_PARTIAL_CAP - 1024 - 3 * kPkMaxBins;
-  const int work = ((n / 2) / T + 1) * n;
-  const int nb = (int)std::min<int64_t>(std::min(work, 512), room / (3 * nbins));
+  const int blocks = std::min(((n / 2) / T + 1) * n, 512);
+  int64_t room = 3 * (int64_t)RED_PARTIAL_CAP - 1024 - 3 * kPkMaxBins;
+  if (room < (int64_t)3 * nbins * blocks && 3 * N / 2 > room) {
+    partial = reinterpret_cast<double *>(ctx->g);
+    room = 3 * N / 2;
+  }
+  const int nb = (int)std::min<int64_t>(blocks, room / (3 * nbins));
   k_spectrum_tables<<<(n + 255) / 256, 256, 0, s>>>(tw, win, n, deconv);
   const unsigned rows = (unsigned)(((int64_t)n * n + TL / (n / 2) - 1) / (TL / (n / 2)));
   const dim3 cols(P / T, n);
