@@ -32,8 +32,9 @@ constexpr double turn(int m, int n, bool sine) {
 }
 
 // In-place DFT of N values (natural order in and out), e^{-2 pi i/N} forward, its
-// conjugate inverse (INV), unnormalised: even lengths split into the even and odd
-// elements, odd lengths summed directly.
+// conjugate inverse (INV), unnormalised: lengths that are multiples of four split into the
+// four subsequences m, m + 4, .. (one layer of twiddles for two halvings: fewer roundings),
+// other even ones into the even and odd elements, odd lengths summed directly.
 template <int N, bool INV>
 struct Dft {
   static __device__ __forceinline__ void run(float2 (&x)[N]) {
@@ -41,6 +42,16 @@ struct Dft {
       const float2 a = x[0], b = x[1];
       x[0] = make_float2(a.x + b.x, a.y + b.y);
       x[1] = make_float2(a.x - b.x, a.y - b.y);
+    } else if constexpr (N % 4 == 0) {
+      float2 q[4][N / 4];
+#pragma unroll
+      for (int m = 0; m < N / 4; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) q[r][m] = x[4 * m + r];
+      if constexpr (N > 4)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Dft<N / 4, INV>::run(q[r]);
+      combine4<0>(x, q);
     } else if constexpr (N % 2 == 0) {
       float2 e[N / 2], o[N / 2];
 #pragma unroll
@@ -53,6 +64,47 @@ struct Dft {
       combine<0>(x, e, o);
     } else {
       direct(x);
+    }
+  }
+  // v e^{-+ 2 pi i K / N}. The constants carry the remainder that FP32 leaves of them: the
+  // first roots of unity all round to a modulus 2.5e-8 too small, and a transform that
+  // multiplies by them again and again loses amplitude by it. With radix-2 splits and rounded
+  // constants the potential of a 512^3 solve was 2.37e-7 off (seven-point kernel), 256^3
+  // 2.25e-7; so 1.78e-7 and 1.83e-7. Time: 256^3 solves 150 -> 151 us, dealiased
+  // second-order initial conditions, bound by vector instructions, 256^3 2984 -> 3037 us.
+  template <int K>
+  static __device__ __forceinline__ float2 turned(float2 v) {
+    if constexpr (4 * K == N) {
+      return INV ? make_float2(-v.y, v.x) : make_float2(v.y, -v.x);
+    } else if constexpr (2 * K == N) {
+      return make_float2(-v.x, -v.y);
+    } else if constexpr (K > 0) {
+      constexpr double cd = turn(K, N, false), sd = (INV ? 1.0 : -1.0) * turn(K, N, true);
+      constexpr float c = (float)cd, s = (float)sd, cl = (float)(cd - (double)c), sl = (float)(sd - (double)s);
+      if constexpr (8 * K % N == 0) {  // +-1 +-i over the root of 2
+        constexpr bool same = (cd > 0.0) == (sd > 0.0);
+        const float p = same ? v.x - v.y : v.x + v.y, q = same ? v.x + v.y : v.y - v.x;
+        return make_float2(fmaf(p, c, p * cl), fmaf(q, c, q * cl));
+      } else {
+        const float x = fmaf(-v.y, s, fmaf(v.x, cl, -(v.y * sl))), y = fmaf(v.y, c, fmaf(v.x, sl, v.y * cl));
+        return make_float2(fmaf(v.x, c, x), fmaf(v.x, s, y));
+      }
+    } else {
+      return v;
+    }
+  }
+  template <int K>
+  static __device__ __forceinline__ void combine4(float2 (&x)[N], const float2 (&q)[4][N / 4]) {
+    if constexpr (K < N / 4) {
+      const float2 a = q[0][K], b = turned<K>(q[1][K]), c = turned<2 * K>(q[2][K]), d = turned<3 * K>(q[3][K]);
+      const float2 s = make_float2(a.x + c.x, a.y + c.y), t = make_float2(a.x - c.x, a.y - c.y);
+      const float2 u = make_float2(b.x + d.x, b.y + d.y), v = make_float2(b.x - d.x, b.y - d.y);
+      const float2 w = INV ? make_float2(-v.y, v.x) : make_float2(v.y, -v.x);  // (-+ i) v
+      x[K] = make_float2(s.x + u.x, s.y + u.y);
+      x[K + N / 4] = make_float2(t.x + w.x, t.y + w.y);
+      x[K + N / 2] = make_float2(s.x - u.x, s.y - u.y);
+      x[K + 3 * N / 4] = make_float2(t.x - w.x, t.y - w.y);
+      combine4<K + 1>(x, q);
     }
   }
   template <int K>
