@@ -95,9 +95,16 @@ __device__ __forceinline__ float power(float k, int p) { return p == 0 ? 1.0f : 
 // sums of c[set][j] f[j] over the band spectra given
 struct Combo {
   const float2 *f[4];
-  float c[2][4];
+  double c[2][4];
   int count;
 };
+
+// 1 / m2 for an integer m2 > 0 (a Newton step on FP32's reciprocal), 0 for 0
+__device__ __forceinline__ double inverse_of(int m2) {
+  if (m2 == 0) return 0.0;
+  const double r = (double)__builtin_amdgcn_rcpf((float)m2);
+  return r * fma(-(double)m2, r, 2.0);
+}
 
 // sqrt(N P(k)) of every |m|^2 = t that the band holds (0 at 0): 3 (n/2)^2 logarithms and
 // exponentials in FP64 instead of n^3 / 2 (128^3: the pass that applies them 28.6 -> 9.7 us and this one 4.7)
@@ -108,8 +115,9 @@ __global__ __launch_bounds__(kT) void k_amplitude(const double *__restrict__ lk,
   if (t < count) amp[t] = t ? (float)(scale * table_sqrt_p(kTwoPi * sqrt((double)t), lk, lp, nt)) : 0.0f;
 }
 
-// The k factors are formed from the integers m = k / (2 pi), exact in FP32, so that a factor
-// m_i m_j / m^2 costs three roundings; the powers of 2 pi left over go into the weights.
+// The k factors are formed from the integers m = k / (2 pi); the powers of 2 pi left over go
+// into the weights. The factor c m_x^o / m^2 of a spectrum is formed in FP64 and rounded once;
+// powers of m_y and m_z multiply later, one rounding each.
 
 // Inverse along i: U = (sum of the spectra) (/ m^2 with DIV), then for o = 0 .. NOUT - 1
 // out_o[i][ky][kz] = the transform of m_x^o U. With a grid of two in y, a second sum goes
@@ -125,6 +133,8 @@ __global__ __launch_bounds__(ColShape<M>::NT) void k_band_inv_x(Combo in, float2
   const int my = p.outer < n / 2 ? p.outer : p.outer - n;
   const bool live = p.kz < n / 2 && p.outer != n / 2;
   const int yz = my * my + p.kz * p.kz;
+  // U / c[0] (the other spectra by the ratio of their weights to the first's)
+  const double c0 = in.c[blockIdx.y][0];
   float2 u[S::N1];
 #pragma unroll
   for (int m = 0; m < S::N1; ++m) {
@@ -132,14 +142,11 @@ __global__ __launch_bounds__(ColShape<M>::NT) void k_band_inv_x(Combo in, float2
     float2 v = make_float2(0.f, 0.f);
     if (live && sx >= 0) {
       const int64_t at = ((int64_t)sx * n + p.outer) * Pb + p.kz;
-      for (int j = 0; j < in.count; ++j) {
+      v = in.f[0][at];
+      for (int j = 1; j < in.count; ++j) {
         const float2 f = in.f[j][at];
-        v = make_float2(fmaf(in.c[blockIdx.y][j], f.x, v.x), fmaf(in.c[blockIdx.y][j], f.y, v.y));
-      }
-      if (DIV) {
-        const int m2 = mx * mx + yz;
-        const float r = m2 > 0 ? 1.0f / (float)m2 : 0.0f;
-        v = make_float2(v.x * r, v.y * r);
+        const float c = (float)(in.c[blockIdx.y][j] / c0);
+        v = make_float2(fmaf(c, f.x, v.x), fmaf(c, f.y, v.y));
       }
     }
     u[m] = v;
@@ -150,7 +157,9 @@ __global__ __launch_bounds__(ColShape<M>::NT) void k_band_inv_x(Combo in, float2
     float2 x[S::N1];
 #pragma unroll
     for (int m = 0; m < S::N1; ++m) {
-      const float f = power((float)signed_of<M>(p.t + S::N2 * m), o);
+      const int mx = signed_of<M>(p.t + S::N2 * m);
+      const double w = DIV ? c0 * inverse_of(mx * mx + yz) : c0;
+      const float f = (float)(w * (o == 0 ? 1 : (o == 1 ? mx : mx * mx)));
       x[m] = make_float2(f * u[m].x, f * u[m].y);
     }
     cols<M, true>(x, lds, p.base, p.t, tw);
@@ -416,11 +425,12 @@ __global__ __launch_bounds__(kT) void k_vector_spectrum(Combo pot, const float2 
   if (kzi >= n / 2 || ix == n / 2 || iy == n / 2) return;
   const float kx = (float)mx, ky = (float)my, kz = (float)kzi;
   const int m2 = mx * mx + my * my + kzi * kzi;
-  const float r = m2 > 0 ? 1.0f / (float)m2 : 0.0f;
+  const float r = (float)inverse_of(m2);
   float2 s = make_float2(0.f, 0.f);
   for (int j = 0; j < pot.count; ++j) {
     const float2 f = pot.f[j][at];
-    s = make_float2(fmaf(pot.c[0][j], f.x, s.x), fmaf(pot.c[0][j], f.y, s.y));
+    const float w = (float)pot.c[0][j];
+    s = make_float2(fmaf(w, f.x, s.x), fmaf(w, f.y, s.y));
   }
   const float2 X = rx[at], Y = ry[at], Z = rz[at];
   auto put = [&](float2 *o, float k, float2 a, float ka, float2 b, float kb) {
@@ -723,7 +733,7 @@ int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab, co
   if (order >= 2) PM_HIP(ctx, fft_tables(FftBufs{nullptr, nullptr, tw_m, tab_m}, m, 0, 0, s));
   const Grid gn{n, Pb, tw_n, s}, gm{n, Pb, tw_m, s};
   const Passes pn = passes_of(n), pm = passes_of(m);
-  const float invN = (float)(1.0 / (double)N);
+  const double invN = 1.0 / (double)N;
   const float trunc = (float)((double)N / (double)M);  // DFT on the m grid -> n-grid units
   // linear density at a = 1: DFT[delta] = sqrt(N) sqrt(P) DFT[w]
   pn.to_band(gn, noise, nx[0], (int64_t)n * n);
@@ -786,10 +796,10 @@ int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab, co
   Combo pot{{delta, src_sp[0], src_sp[1], src_sp[2]}, {}, order == 3 ? 4 : order};
   for (int v = 0; v < 2; ++v) {  // displacements, velocities
     const double f = v ? ra : 1.0;
-    pot.c[v][0] = (float)(f * a0 * w);
-    pot.c[v][1] = (float)(-(v ? 2.0 : 1.0) * f * d2 * w);
-    pot.c[v][2] = (float)(-(v ? 3.0 : 1.0) * f * d3a * w);
-    pot.c[v][3] = (float)(-(v ? 3.0 : 1.0) * f * d3b * w);
+    pot.c[v][0] = f * a0 * w;
+    pot.c[v][1] = -(v ? 2.0 : 1.0) * f * d2 * w;
+    pot.c[v][2] = -(v ? 3.0 : 1.0) * f * d3a * w;
+    pot.c[v][3] = -(v ? 3.0 : 1.0) * f * d3b * w;
   }
   if (order < 3) {
     // (at first order one is a multiple of the other)
@@ -804,7 +814,7 @@ int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab, co
       k_vector_spectrum<<<blocks_for((int64_t)band, kT), kT, 0, s>>>(
           pot, src_sp[3], src_sp[4], src_sp[5], c, n, Pb, vec[0], vec[1], vec[2]);
       for (int d = 0; d < 3; ++d) {
-        pn.inv_x(gn, Combo{{vec[d]}, {{1.0f}}, 1}, nx[0], nullptr, nullptr, false, 1);
+        pn.inv_x(gn, Combo{{vec[d]}, {{1.0}}, 1}, nx[0], nullptr, nullptr, false, 1);
         pn.inv_y(gn, nx[0], ny[d], nullptr, nullptr, 0, n, 1);
       }
       pn.particles(gn, ny[0], ny[1], ny[2], false, v ? nullptr : pos, cell, v ? vel : nullptr, 1.0f, 1);
