@@ -515,8 +515,9 @@ int pm_ic_vjp(pm_ctx *ctx, const float *pos_bar, const float *vel_bar, int64_t n
  *     truncated back (free of aliasing for the quadratic and cubic terms; the paper uses
  *     Orszag's 3/2 rule, which this equals for the quadratic ones); 0: on the n grid;
  *   pos [np][3]: box units (cell == NULL) or in-cell offsets with cell [np]; vel [np][3].
- * n must be a power of two (2n <= 1024 with dealiasing). The working fields (up to 13 grids
- * of (2n)^3 floats at third order) are allocated by the call; up to 2 GiB of them stay with
+ * n must be a power of two (2n <= 1024 with dealiasing). The working fields (12 bytes per
+ * cell at first order, 24 at second, 92 at third, with dealiasing 40 and 444, and up to 128
+ * MiB at orders 2 and 3) are allocated by the call; up to 2 GiB of them stay with
  * the context for its next call, more are released before the call returns. It synchronises
  * the stream before it returns. Errors: PM_ERR_ARG, PM_ERR_SHAPE,
  * PM_ERR_NOMEM, PM_ERR_HIP. */

@@ -171,8 +171,11 @@ __global__ __launch_bounds__(ColShape<M>::NT) void k_band_inv_x(Combo in, float2
 }
 
 // Inverse along j of the planes i = x0 .. : out_o[i - x0][j][kz] = the transform of m_y^o in.
+// (On the n grid this pass and the three others along i and j have their columns in the same
+// places before and after: a block reads its own whole before it writes, so an output may be
+// the input.)
 template <int M, int NOUT>
-__global__ __launch_bounds__(ColShape<M>::NT) void k_band_inv_y(const float2 *__restrict__ in, float2 *o0,
+__global__ __launch_bounds__(ColShape<M>::NT) void k_band_inv_y(const float2 *in, float2 *o0,
                                                                 float2 *o1, float2 *o2, int x0, int n,
                                                                 int Pb, size_t set, const float2 *__restrict__ tw) {
   using S = Split<M>;
@@ -205,8 +208,7 @@ __global__ __launch_bounds__(ColShape<M>::NT) void k_band_inv_y(const float2 *__
 
 // Forward along j of the planes x0 .. : the band of the transform to out[i][ky][kz].
 template <int M>
-__global__ __launch_bounds__(ColShape<M>::NT) void k_band_fwd_y(const float2 *__restrict__ in,
-                                                                float2 *__restrict__ out, int x0, int n,
+__global__ __launch_bounds__(ColShape<M>::NT) void k_band_fwd_y(const float2 *in, float2 *out, int x0, int n,
                                                                 int Pb, const float2 *__restrict__ tw) {
   using S = Split<M>;
   __shared__ __align__(16) float lds[ColShape<M>::LDS];
@@ -227,8 +229,7 @@ __global__ __launch_bounds__(ColShape<M>::NT) void k_band_fwd_y(const float2 *__
 // Forward along i: the band of the transform times scale or, with a table of them,
 // the amplitude at |m|^2.
 template <int M>
-__global__ __launch_bounds__(ColShape<M>::NT) void k_band_fwd_x(const float2 *__restrict__ in,
-                                                                float2 *__restrict__ out, int n, int Pb,
+__global__ __launch_bounds__(ColShape<M>::NT) void k_band_fwd_x(const float2 *in, float2 *out, int n, int Pb,
                                                                 float scale,
                                                                 const float2 *__restrict__ tw,
                                                                 const float *__restrict__ amp) {
@@ -382,11 +383,11 @@ struct Hess {
 enum { kSrcS2 = 0, kSrcDet = 1, kSrcS3b = 2, kSrcRx = 3, kSrcRy = 4, kSrcRz = 5 };
 
 // The pointwise sources of the higher orders (paper Sect. 3.3, explicit forms), from the
-// second derivatives of phi(1) (A) and of phi(2) (B).
-__global__ __launch_bounds__(kT) void k_lpt_source(Hess A, Hess B, int which, int64_t count,
+// second derivatives of phi(1) (A) and of phi(2) (B), for the cells from first on.
+__global__ __launch_bounds__(kT) void k_lpt_source(Hess A, Hess B, int which, int64_t first, int64_t count,
                                                    float *__restrict__ out) {
-  const int64_t p = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (p >= count) return;
+  const int64_t o = (int64_t)blockIdx.x * kT + threadIdx.x, p = first + o;
+  if (o >= count) return;
   const float axx = A.a[0][p], ayy = A.a[1][p], azz = A.a[2][p];
   const float axy = A.a[3][p], axz = A.a[4][p], ayz = A.a[5][p];
   float v = 0.0f;
@@ -408,7 +409,7 @@ __global__ __launch_bounds__(kT) void k_lpt_source(Hess A, Hess B, int which, in
     else
       v = bxz * ayz - byz * axz + axy * (bxx - byy) - bxy * (axx - ayy);
   }
-  out[p] = v;
+  out[o] = v;
 }
 
 // Third order: the vector spectrum i m_d (sum of the potentials' sources) / m^2 plus
@@ -691,41 +692,67 @@ int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab, co
   int chunk = m;
   while (chunk > 8 && 6 * plane * chunk * sizeof(float2) > ((size_t)128 << 20)) chunk /= 2;
   const int namp = 3 * (n / 2) * (n / 2);  // |m|^2 <= 3 (n/2 - 1)^2
-  const int nsrc = order == 1 ? 0 : (order == 2 ? 1 : 6);
+  const size_t fields = 6 * plane * chunk;  // (complex values of the six half-transformed ones)
   Scratch sc{ctx};
   double *d_tab = nullptr;
   float2 *tw_n = nullptr, *tw_m = nullptr, *delta = nullptr, *src_sp[6] = {}, *nx[2] = {}, *ny[3] = {};
-  float2 *mx[3] = {}, *my[6] = {}, *back = nullptr, *vec[3] = {};
+  float2 *mx[3] = {}, *my[6] = {}, *my2 = nullptr, *my3 = nullptr, *back = nullptr, *vec[3] = {};
   float *tab_n = nullptr, *tab_m = nullptr, *amp = nullptr, *h1[6] = {}, *h2[6] = {}, *tmp = nullptr;
+  // Fields lie where others are no longer, or not yet, needed (bytes per cell of the n grid
+  // without | with dealiasing on large grids: order 1 12, order 2 24 | 40, order 3 92 | 444,
+  // and at most 128 MiB of half-transformed fields).
   for (int pass = 0; pass < 2; ++pass) {
     if (pass == 1 && !sc.open())
       return pm_fail(ctx, PM_ERR_NOMEM, "initial-condition scratch allocation failed");
     d_tab = sc.take<double>(2 * (size_t)ntab);
     tw_n = sc.take<float2>(n);
     tab_n = sc.take<float>(3 * n);
-    delta = sc.take<float2>(band);
     amp = sc.take<float>(namp);
-    for (int i = 0; i < 3; ++i) {
-      if (i < 2) nx[i] = sc.take<float2>(2 * band);  // the n grid's passes: two [n][n][Pb]
-      ny[i] = sc.take<float2>(2 * band);
+    delta = sc.take<float2>(order == 2 ? 2 * band : band);
+    if (order == 1) {
+      // the potential's passes in delta's place
+      nx[0] = ny[2] = delta;
+      nx[1] = ny[0] = sc.take<float2>(band);
+      ny[1] = sc.take<float2>(band);
+      continue;
     }
-    for (int i = 0; i < nsrc; ++i) src_sp[i] = sc.take<float2>(band);
-    if (order >= 2) {
-      tw_m = sc.take<float2>(m);
-      tab_m = sc.take<float>(3 * m);
-      for (int i = 0; i < 3; ++i) mx[i] = sc.take<float2>(half);
-      my[0] = sc.take<float2>(6 * plane * chunk);
-      for (int i = 1; i < 6 && pass; ++i) my[i] = my[0] + i * plane * chunk;
-      back = sc.take<float2>(half);
-    }
-    if (order == 3) {
+    tw_m = sc.take<float2>(m);
+    tab_m = sc.take<float>(3 * m);
+    float2 *const x3 = sc.take<float2>(order == 2 ? 4 * half : 3 * half);
+    float2 *const sp = order == 2 ? nullptr : sc.take<float2>(6 * band + half);
+    float *const h = order == 2 ? nullptr : sc.take<float>(12 * (size_t)M);
+    size_t extra = order == 2 ? fields * sizeof(float2) : 0;  // bytes of what fits nowhere
+    // first Hessian: over the second one; second: over the sources and the band returned to,
+    // which come after it; sources: over the Hessian's first transforms
+    const size_t source = plane * chunk * sizeof(float2) + (size_t)chunk * m * m * sizeof(float);
+    const bool fit1 = fields * sizeof(float2) <= 6 * (size_t)M * sizeof(float);
+    const bool fit2 = fields <= 5 * band + half, fit3 = source <= 3 * half * sizeof(float2);
+    if (order == 3 && (!fit1 || !fit2)) extra = fields * sizeof(float2);
+    if (order == 3 && !fit3) extra = std::max(extra, source);
+    float2 *const rest = reinterpret_cast<float2 *>(sc.take<char>(extra));
+    if (pass == 0) continue;
+    for (int i = 0; i < 3; ++i) mx[i] = x3 + i * half;
+    if (order == 2) {
+      src_sp[0] = delta + band;
+      back = x3 + 3 * half;
+      my[0] = rest;
+      nx[0] = ny[2] = x3;  // (two sets of each)
+      nx[1] = ny[0] = x3 + 2 * band;
+      ny[1] = delta;
+    } else {
       for (int i = 0; i < 6; ++i) {
-        h1[i] = sc.take<float>(M);
-        h2[i] = sc.take<float>(M);
+        src_sp[i] = sp + i * band;
+        h1[i] = h + i * M;
+        h2[i] = h + (6 + i) * M;
       }
-      tmp = sc.take<float>(M);
-      for (int i = 0; i < 3; ++i) vec[i] = sc.take<float2>(band);
+      back = sp + 6 * band;
+      my[0] = fit1 ? reinterpret_cast<float2 *>(h2[0]) : rest;
+      my2 = fit2 ? src_sp[1] : rest;
+      my3 = fit3 ? x3 : rest;
+      tmp = reinterpret_cast<float *>(my3 + plane * chunk);
+      for (int i = 0; i < 3; ++i) vec[i] = reinterpret_cast<float2 *>(h) + i * band;
     }
+    for (int i = 1; i < 6; ++i) my[i] = my[0] + i * plane * chunk;
   }
   PM_HIP(ctx, hipMemcpyAsync(d_tab, lt.data(), sizeof(double) * 2 * ntab, hipMemcpyHostToDevice, s));
   const double *lk = d_tab, *lp = d_tab + ntab;
@@ -736,10 +763,10 @@ int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab, co
   const double invN = 1.0 / (double)N;
   const float trunc = (float)((double)N / (double)M);  // DFT on the m grid -> n-grid units
   // linear density at a = 1: DFT[delta] = sqrt(N) sqrt(P) DFT[w]
-  pn.to_band(gn, noise, nx[0], (int64_t)n * n);
-  pn.fwd_y(gn, nx[0], ny[0], 0, n);
+  pn.to_band(gn, noise, delta, (int64_t)n * n);
+  pn.fwd_y(gn, delta, delta, 0, n);
   k_amplitude<<<blocks_for(namp, kT), kT, 0, s>>>(lk, lp, ntab, (float)std::sqrt((double)N), namp, amp);
-  pn.fwd_x(gn, ny[0], delta, 1.0f, amp);
+  pn.fwd_x(gn, delta, delta, 1.0f, amp);
   PM_HIP(ctx, hipGetLastError());
   // k_i k_j F / k^2 / N = m_i m_j F / m^2 / N of the band spectrum F, along i for all planes
   auto hessian_x = [&](const float2 *f) {
@@ -771,6 +798,7 @@ int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab, co
   if (order == 3) {
     // phi(2)_ij = IDFT[k_i k_j S2 / k^2] / N, then the five third-order sources
     hessian_x(src_sp[0]);
+    for (int i = 0; i < 6; ++i) my[i] = my2 + i * plane * chunk;
     for (int x0 = 0; x0 < m; x0 += chunk) {
       hessian_y(x0);
       for (int c = 0; c < 6; ++c) pm.to_rows(gm, my[c], h2[c] + (int64_t)x0 * m * m, crow, kz_power[c]);
@@ -778,10 +806,10 @@ int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab, co
     const Hess A{{h1[0], h1[1], h1[2], h1[3], h1[4], h1[5]}};
     const Hess B{{h2[0], h2[1], h2[2], h2[3], h2[4], h2[5]}};
     for (int w = kSrcDet; w <= kSrcRz; ++w) {
-      k_lpt_source<<<blocks_for(M, kT), kT, 0, s>>>(A, B, w, M, tmp);
       for (int x0 = 0; x0 < m; x0 += chunk) {
-        pm.to_band(gm, tmp + (int64_t)x0 * m * m, my[0], crow);
-        pm.fwd_y(gm, my[0], back, x0, chunk);
+        k_lpt_source<<<blocks_for(crow * m, kT), kT, 0, s>>>(A, B, w, (int64_t)x0 * m * m, crow * m, tmp);
+        pm.to_band(gm, tmp, my3, crow);
+        pm.fwd_y(gm, my3, back, x0, chunk);
       }
       pm.fwd_x(gm, back, src_sp[w], trunc, nullptr);
     }
@@ -814,10 +842,10 @@ int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab, co
       k_vector_spectrum<<<blocks_for((int64_t)band, kT), kT, 0, s>>>(
           pot, src_sp[3], src_sp[4], src_sp[5], c, n, Pb, vec[0], vec[1], vec[2]);
       for (int d = 0; d < 3; ++d) {
-        pn.inv_x(gn, Combo{{vec[d]}, {{1.0}}, 1}, nx[0], nullptr, nullptr, false, 1);
-        pn.inv_y(gn, nx[0], ny[d], nullptr, nullptr, 0, n, 1);
+        pn.inv_x(gn, Combo{{vec[d]}, {{1.0}}, 1}, vec[d], nullptr, nullptr, false, 1);
+        pn.inv_y(gn, vec[d], vec[d], nullptr, nullptr, 0, n, 1);
       }
-      pn.particles(gn, ny[0], ny[1], ny[2], false, v ? nullptr : pos, cell, v ? vel : nullptr, 1.0f, 1);
+      pn.particles(gn, vec[0], vec[1], vec[2], false, v ? nullptr : pos, cell, v ? vel : nullptr, 1.0f, 1);
     }
   }
   PM_HIP(ctx, hipGetLastError());
