@@ -518,12 +518,15 @@ int pm_ic_vjp(pm_ctx *ctx, const float *pos_bar, const float *vel_bar, int64_t n
  * n must be a power of two (2n <= 1024 with dealiasing). The working fields (12 bytes per
  * cell at first order, 24 at second, 92 at third, with dealiasing 40 and 444, and up to 128
  * MiB at orders 2 and 3) are allocated by the call; up to 2 GiB of them stay with
- * the context for its next call, more are released before the call returns. It synchronises
- * the stream before it returns. Errors: PM_ERR_ARG, PM_ERR_SHAPE,
- * PM_ERR_NOMEM, PM_ERR_HIP. */
+ * the context for its next call (until pm_ic_release or pm_destroy), more are released before
+ * the call returns. It synchronises the stream before it returns. Errors: PM_ERR_ARG,
+ * PM_ERR_SHAPE, PM_ERR_NOMEM, PM_ERR_HIP. */
 int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab,
               const double *p_tab, int order, int dealias, double a0, float *pos,
               int32_t *cell, float *vel, pm_stream stream);
+/* Gives back the working fields that pm_ic_lpt has left with the context, if any (a run that
+ * needs the memory calls it between its initial conditions and its steps). */
+int pm_ic_release(pm_ctx *ctx);
 
 /* Power spectrum of a density grid (the estimator behind the paper's Sect. 4 results):
  * delta = rho / mean(rho) - 1, delta_k = DFT[delta] / n^3 divided by the window

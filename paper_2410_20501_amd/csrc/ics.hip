@@ -31,6 +31,7 @@
 // dealiasing, kernels of a call: 128^3 1236 -> 370 us, 256^3 2970 us; a 128^3 call 4840 -> 394
 // us (two thirds of it were allocations, now kept: Scratch).
 #include <cmath>
+#include <new>
 #include <vector>
 
 #include "fft_line.h"
@@ -636,7 +637,11 @@ struct Scratch {
         (void)hipGetLastError();
         return false;
       }
-      buf = new IcScratch{p, used};
+      buf = new (std::nothrow) IcScratch{p, used};
+      if (!buf) {
+        (void)hipFree(p);
+        return false;
+      }
     }
     used = 0;
     return true;
@@ -660,6 +665,12 @@ void ic_scratch_free(IcScratch *b) {
 }
 
 extern "C" {
+
+int pm_ic_release(pm_ctx *ctx) {
+  if (!ctx) return PM_ERR_ARG;
+  ic_scratch_free(__atomic_exchange_n(&ctx->ic, (IcScratch *)nullptr, __ATOMIC_ACQ_REL));
+  return PM_OK;
+}
 
 int pm_ic_lpt(pm_ctx *ctx, const float *noise, int ntab, const double *k_tab, const double *p_tab,
               int order, int dealias, double a0, float *pos, int32_t *cell, float *vel,

@@ -125,6 +125,7 @@ def _load():
         "pm_ic_vjp": (c_int, [P, P, P, c_int64, c_double, P, P]),
         "pm_ic_lpt": (c_int, [P, P, c_int, POINTER(c_double), POINTER(c_double), c_int, c_int,
                               c_double, P, P, P, P]),
+        "pm_ic_release": (c_int, [P]),
         "pm_power_spectrum": (c_int, [P, P, c_int, c_int, POINTER(c_double), POINTER(c_double),
                                       POINTER(c_int64), P]),
         "pm_batch_create": (c_int, [POINTER(c_void_p), c_int, POINTER(c_int), POINTER(c_int64),
@@ -516,6 +517,11 @@ def pm_ic_lpt(ctx: Context, noise, k_tab, p_tab, a0, pos, vel, cell=None, order=
                         _ptr(pos, shape=(np_, 3), name="pos"), _ptr(cell, torch.int32, (np_,), "cell"),
                         _ptr(vel, shape=(np_, 3), name="vel"), _stream())
     return ctx._check(st, "pm_ic_lpt")
+
+
+def pm_ic_release(ctx: Context):
+    """Gives back the working fields that pm_ic_lpt keeps with the context."""
+    return ctx._check(_lib.pm_ic_release(ctx.handle), "pm_ic_release")
 
 
 def pm_power_spectrum(ctx: Context, rho, deconv=3, nbins=None):

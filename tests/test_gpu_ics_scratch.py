@@ -58,3 +58,21 @@ def test_shared_places_do_not_show(n):
                 x, v = _call(lib, ctx, w, *c)
                 assert torch.equal(x, fresh[c][0]) and torch.equal(v, fresh[c][1]), (a, b, c)
     ctx.close()
+
+
+def test_release():
+    import paper_2410_20501_amd as lib
+    n = 128
+    w = torch.randn((n, n, n), device="cuda")
+    ctx = lib.Context(n, n ** 3)
+    lib.pm_ic_release(ctx)  # (nothing kept)
+    x, v = _call(lib, ctx, w, 2, True)
+    kept = torch.cuda.mem_get_info()[0]
+    lib.pm_ic_release(ctx)
+    back = torch.cuda.mem_get_info()[0] - kept
+    print(f"[case] released {back >> 20} MiB", flush=True)
+    assert back >= 40 * n ** 3
+    lib.pm_ic_release(ctx)
+    y, u = _call(lib, ctx, w, 2, True)
+    assert torch.equal(x, y) and torch.equal(v, u)
+    ctx.close()
