@@ -998,10 +998,11 @@ int pm_mg_solve(pm_ctx *ctx, const float *rho, float coef, float *phi, const pm_
       sv.stop = status != PM_WARN_NOT_CONVERGED || cycles == p->max_cycles;
       return hipSuccess;
     };
-    sv.test = [&]() -> hipError_t {
+    auto test = [&]() -> hipError_t {
       const hipError_t e = sv.wait_norms(sum);
       return e == hipSuccess ? decide() : e;
     };
+    sv.test = std::ref(test);  // (a reference: no allocation, which could throw)
     status = PM_WARN_NOT_CONVERGED;
     for (;;) {
       // residual norm of the current iterate: fused into the next pre-smoothing
