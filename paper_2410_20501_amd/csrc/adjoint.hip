@@ -284,7 +284,8 @@ __global__ __launch_bounds__(kVThreads) void k_interp_vjp_chunk(
 // instructions; the conversion of a float to 64 bits is a dozen), and by the atomics at the
 // end, 64 neighbouring floats each instead of 64 of one component: 128^3, one particle a
 // cell, 227 -> 97 us; 32^3 31 -> 16. A particle whose window leaves the box (not possible for a
-// bucket that matches its positions), and every particle of a tile with a non-finite
+// bucket that matches its positions), one whose weights the fixed point does not hold (an
+// offset far outside its cell, or not finite), and every particle of a tile with a non-finite
 // cotangent, takes the per-weight global path.
 constexpr int kVTThreads = 512;  // (a tile of the lattice state in one pass: 117 -> 97 us at 128^3)
 constexpr int kVTT = 8, kVTH = kVTT + 2, kVTHalo = kVTH * kVTH * kVTH;
@@ -353,7 +354,9 @@ __global__ __launch_bounds__(kVTThreads) void k_interp_vjp_tile(
       lf += lf < -n / 2 ? n : 0;
       lf -= lf > n / 2 ? n : 0;
       b[d] = lf + 1;
-      inbox = inbox && b[d] >= 0 && b[d] <= kVTH - MAS && w[d][0] == w[d][0];
+      // (weights of an offset in [0, 1) are at most 1; up to 4 at either end, the middle one is
+      // at most 5 and a product far below fix_units' range; NaN compares false)
+      inbox = inbox && b[d] >= 0 && b[d] <= kVTH - MAS && w[d][0] <= 4.0f && w[d][MAS - 1] <= 4.0f;
     }
     const float l0 = lam[3 * (size_t)p], l1 = lam[3 * (size_t)p + 1], l2 = lam[3 * (size_t)p + 2];
     float gx = 0.f, gy = 0.f, gz = 0.f;
