@@ -236,8 +236,10 @@ hipError_t launch_gradient(const float *phi, int n, int points, float *g, hipStr
   return hipGetLastError();
 }
 
-// Both in one launch for a grid of up to kMomentsOne cells (32^3: 7.2 -> 4.4 us).
-constexpr int64_t kMomentsOne = 65536;
+// Both in one launch for a grid of up to kMomentsOne cells. A one-cycle solve, which takes
+// two of them, with one launch | two each, us back to back: 8^3 10.8 | 13.3, 24^3 23.7 | 24.0,
+// 32^3 25.3 | 25.8, 36^3 31.1 | 29.0, 40^3 40.7 | 36.9.
+constexpr int64_t kMomentsOne = 32768;
 constexpr int kMomentsThreads = 1024;
 __global__ __launch_bounds__(kMomentsThreads) void k_moments_one(const float *__restrict__ x, int count,
                                                                  double *__restrict__ result,
