@@ -63,7 +63,7 @@ __device__ __forceinline__ void line_pass(float2 *spec, int base, int stride) {
   float2 x[N];
 #pragma unroll
   for (int m = 0; m < N; ++m) x[m] = spec[base + m * stride];
-  Dft<N, INV>::run(x);
+  Dft<N, INV, false>::run(x);
 #pragma unroll
   for (int m = 0; m < N; ++m) spec[base + m * stride] = x[m];
 }
@@ -111,7 +111,7 @@ __device__ __forceinline__ void solve(float *__restrict__ ug, const float *__res
 #pragma unroll
     for (int m = 0; m < N / 2; ++m)
       z[m] = make_float2(scale * (z[m].x - mean), scale * (z[m].y - mean));
-    Dft<N / 2, false>::run(z);
+    Dft<N / 2, false, false>::run(z);
     split<N, 0>(z, X);
 #pragma unroll
     for (int k = 0; k < NH; ++k) spec[t * NH + k] = X[k];
@@ -125,9 +125,9 @@ __device__ __forceinline__ void solve(float *__restrict__ ug, const float *__res
     const int base = lo * NH + kz;
 #pragma unroll
     for (int m = 0; m < N; ++m) x[m] = spec[base + m * N * NH];
-    Dft<N, false>::run(x);
+    Dft<N, false, false>::run(x);
     divide<N, 0>(x, symbol<N>(lo) + symbol<N>(kz), h2 / (float)(N * N * N), lo == 0 && kz == 0);
-    Dft<N, true>::run(x);
+    Dft<N, true, false>::run(x);
 #pragma unroll
     for (int m = 0; m < N; ++m) spec[base + m * N * NH] = x[m];
   }
@@ -139,7 +139,7 @@ __device__ __forceinline__ void solve(float *__restrict__ ug, const float *__res
 #pragma unroll
     for (int k = 0; k < NH; ++k) X[k] = spec[t * NH + k];
     join<N, 0>(X, z);
-    Dft<N / 2, true>::run(z);
+    Dft<N / 2, true, false>::run(z);
     float2 *dst = reinterpret_cast<float2 *>(ug + (size_t)t * N);
 #pragma unroll
     for (int m = 0; m < N / 2; ++m) dst[m] = z[m];

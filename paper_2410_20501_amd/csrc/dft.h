@@ -35,7 +35,7 @@ constexpr double turn(int m, int n, bool sine) {
 // conjugate inverse (INV), unnormalised: lengths that are multiples of four split into the
 // four subsequences m, m + 4, .. (one layer of twiddles for two halvings: fewer roundings),
 // other even ones into the even and odd elements, odd lengths summed directly.
-template <int N, bool INV>
+template <int N, bool INV, bool EXACT = true>
 struct Dft {
   static __device__ __forceinline__ void run(float2 (&x)[N]) {
     if constexpr (N == 2) {
@@ -50,7 +50,7 @@ struct Dft {
         for (int r = 0; r < 4; ++r) q[r][m] = x[4 * m + r];
       if constexpr (N > 4)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) Dft<N / 4, INV>::run(q[r]);
+        for (int r = 0; r < 4; ++r) Dft<N / 4, INV, EXACT>::run(q[r]);
       combine4<0>(x, q);
     } else if constexpr (N % 2 == 0) {
       float2 e[N / 2], o[N / 2];
@@ -59,8 +59,8 @@ struct Dft {
         e[m] = x[2 * m];
         o[m] = x[2 * m + 1];
       }
-      Dft<N / 2, INV>::run(e);
-      Dft<N / 2, INV>::run(o);
+      Dft<N / 2, INV, EXACT>::run(e);
+      Dft<N / 2, INV, EXACT>::run(o);
       combine<0>(x, e, o);
     } else {
       direct(x);
@@ -72,6 +72,8 @@ struct Dft {
   // constants the potential of a 512^3 solve was 2.37e-7 off (seven-point kernel), 256^3
   // 2.25e-7; so 1.78e-7 and 1.83e-7. Time: 256^3 solves 150 -> 151 us, dealiased
   // second-order initial conditions, bound by vector instructions, 256^3 2984 -> 3037 us.
+  // Not EXACT: rounded constants, for the coarsest multigrid level, whose solution is a
+  // correction and whose time is one chain of these (16^3 5.84 -> 5.45 us).
   template <int K>
   static __device__ __forceinline__ float2 turned(float2 v) {
     if constexpr (4 * K == N) {
@@ -81,7 +83,9 @@ struct Dft {
     } else if constexpr (K > 0) {
       constexpr double cd = turn(K, N, false), sd = (INV ? 1.0 : -1.0) * turn(K, N, true);
       constexpr float c = (float)cd, s = (float)sd, cl = (float)(cd - (double)c), sl = (float)(sd - (double)s);
-      if constexpr (8 * K % N == 0) {  // +-1 +-i over the root of 2
+      if constexpr (!EXACT) {
+        return make_float2(v.x * c - v.y * s, v.x * s + v.y * c);
+      } else if constexpr (8 * K % N == 0) {  // +-1 +-i over the root of 2
         constexpr bool same = (cd > 0.0) == (sd > 0.0);
         const float p = same ? v.x - v.y : v.x + v.y, q = same ? v.x + v.y : v.y - v.x;
         return make_float2(fmaf(p, c, p * cl), fmaf(q, c, q * cl));
