@@ -40,16 +40,16 @@ MEASURED_TRAFFIC = {
     # and the post-smoothing pass (with the prolongation) weighted by their counts (45
     # and 39 dispatches)
     "smooth": ("paper_2410_20501_amd/csrc/mg_stream.hip",
-               "4ea35171df84f337cefdd3d1146566fb9eea23ffec47a4cdf832b17cc38d203f",
-               628408.0, 524301.0, 2.0, 1.0),
+               "53c420d6c53ac12bf233f8b833e1b7a0dd8fc43b7b5f32bee2d4609958aafcb2",
+               632144.7, 524301.1, 2.0, 1.0),
     # deposit: the particle-owned tile kernel plus the gather pass over the tile boxes
     "deposit": ("paper_2410_20501_amd/csrc/particles.hip",
                 "c7c6d1d599da8a112a4782295f0ea8ec6a17c29bca8f964dd1a057e626e6182b",
-                2005610.0, 1549791.0, 2.0, 1.0),
+                2005657.1, 1549783.0, 2.0, 1.0),
     # interpolation with the fused gradient, kicks and drift of a chained step
     "interp": ("paper_2410_20501_amd/csrc/particles.hip",
                "c7c6d1d599da8a112a4782295f0ea8ec6a17c29bca8f964dd1a057e626e6182b",
-               2749282.0, 5320506.0, 2.0, 1.0),
+               2747068.9, 5337194.9, 2.0, 1.0),
 }
 
 
@@ -288,10 +288,10 @@ def bench_batched(nboxes=96, steps=20, master_seed=2024):
 def bench_fft(n=256, reps=20):
     """FFT Poisson solve (Green's function with TSC deconvolution) and FFT_7pt on an n^3
     grid (the 256^3 ten-step workload's solver), timed with HIP events on the current
-    stream. Algorithmic bytes: the five LDS-staged passes each read and write the half
-    spectrum (n^2 (n/2+1) complex, about 4 B per cell each way), the first pass reads
-    the real density (4 B/cell) instead and the last writes the real potential: about
-    8 B per cell per pass, 40 B per cell per solve."""
+    stream. Algorithmic bytes: the five passes (lines in registers) each read and write
+    the half spectrum (n^2 (n/2+1) complex, about 4 B per cell each way), the first pass
+    reads the real density (4 B/cell) instead and the last writes the real potential:
+    about 8 B per cell per pass, 40 B per cell per solve (FULL_FFT 72)."""
     import numpy as np
     import torch
 

@@ -232,12 +232,16 @@ const char *pm_last_error(const pm_ctx *ctx);
  * with the CIC (8 cells) or TSC (27 cells) window, u = position in cell units,
  * and particle weight w = n^3 / np (mean density 1, the paper's normalisation
  * when np = n^3). rho is overwritten.
- * order PM_DEPOSIT_ATOMIC: chunks of 2048 consecutive particles are sorted by
- *   cell in on-chip memory, every cell of the chunk's box sums its weights in
- *   registers, and the box is added to rho with one FP32 atomic per cell (the
- *   sum order across chunks, hence the last bits, may differ between runs).
- *   Fast when neighbours in memory are neighbours in space (see pm_reorder);
- *   chunks spread over more than 4096 cells use one atomic per weight.
+ * order PM_DEPOSIT_ATOMIC: the weights of a chunk of consecutive particles (256
+ *   in calls of up to 200000, 512 up to 4 million, 2048 above) are summed in a
+ *   box of their cells on chip, in 2^-30 fixed point, and the box is added to rho
+ *   with one FP32 atomic per cell (the sum order across chunks, hence the last
+ *   bits, may differ between runs). Fast when neighbours in memory are
+ *   neighbours in space (see pm_reorder): a chunk whose box exceeds 5120 cells is
+ *   taken as parts of 256 particles, such a part as its four waves of 64, and
+ *   only a wave whose own box exceeds them uses one atomic per weight. With
+ *   PM_NGP a chunk has one box, of at most 8 cells a particle, or uses one atomic
+ *   per particle.
  * order PM_DEPOSIT_SORTED: particles are bucketed (a counting sort into context
  *   scratch; the caller's arrays are not reordered). With n % 8 == 0 the buckets
  *   are 8^3-cell tiles: each tile adds its particles' weights into a box of the
@@ -257,8 +261,12 @@ int pm_deposit(pm_ctx *ctx, const float *pos, const int32_t *cell, int64_t np,
  * phi: in = starting guess when params->guess == PM_GUESS_WARM; out = the
  * solution with its mean removed. V-cycles of red-black Gauss-Seidel
  * smoothing, restriction to a grid twice as coarse, recursion down to at most
- * 16 cells per side, trilinear prolongation-correction. Unless fixed_cycles is
- * set, the residual norm is checked after every cycle (one host sync each).
+ * 18 cells per side (solved exactly), trilinear prolongation-correction. Unless
+ * fixed_cycles is set, the residual norm is checked after every cycle: the host
+ * waits for it (on grids below 224 cells a side while the next cycle begins). It
+ * is that of the iterate before two more pre-smoothing sweeps, which are part of
+ * the result (grids of more than 18 cells a side). Norms are FP64: sources of any
+ * size that FP32 holds are solved alike.
  * Returns PM_OK, or a warning if tol was not reached; stats may be NULL. */
 int pm_solve_mg(pm_ctx *ctx, const float *rho, float coef, float *phi,
                 const pm_mg_params *params, pm_mg_stats *stats, pm_stream stream);
@@ -307,7 +315,9 @@ int pm_solve_fft_noalloc(const float *rho, int n, float coef, int deconv, float 
  *   K = a^4 R_bar / (3 c~^2),  s = -(Omega_m a / c~^2)(rho - mean rho) - K,
  * which for u given its neighbours is the depressed polynomial u^(n+2) + p u + q = 0
  * solved by the paper's closed forms (cubic for n = 1, quartic for n = 2) in FP64 (the
- * cubic's forms evaluated in FP32 and polished to FP64 rounding by two Newton steps).
+ * cubic's forms evaluated in FP32 and polished to FP64 rounding by two Newton steps; on
+ * grids of at most 16^3 cells below the finest, or on a finest grid without a coarser one,
+ * three Newton steps from the cell's last value where the first proves the root near).
  * Full-approximation-storage cycles (params->fr_cycle, fr_cycles of them) of red-black
  * non-linear Gauss-Seidel (fr_pre sweeps red first, fr_post sweeps black first),
  * full-weighting restriction of u and of the residual, coarse problem

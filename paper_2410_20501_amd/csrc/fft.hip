@@ -351,7 +351,7 @@ int fft_mean_blocks(int n) {
 //        n      32          64         128        256        512
 //   FFT       81 -> 27   84 -> 27   116 -> 42  243 -> 160  3291 -> 1489
 //   FULL_FFT 177 -> 30  187 -> 34   232 -> 65  599 -> 329  8181 -> 3398
-// (FULL_FFT moves 128 bytes a cell instead of 176.)
+// (FULL_FFT moves 72 bytes a cell instead of 96, counted as the 40 of FFT are.)
 hipError_t fft_run(const FftBufs &b, int n, const float *rho, const float *mean, double *partial,
                    float coef, int deconv, int kind, float *out, hipStream_t s) {
   const float scale = (float)((double)coef / ((double)n * n * n));

@@ -28,7 +28,7 @@
 // transform each of the summed orders, written as whole particles with the lattice added.
 //
 // Bound by vector instructions and, above 128^3, by memory. Measured at second order with
-// dealiasing, kernels of a call: 128^3 1236 -> 370 us, 256^3 2970 us; a 128^3 call 4840 -> 394
+// dealiasing, kernels of a call: 128^3 1236 -> 360 us, 256^3 3000 us; a 128^3 call 4911 -> 387
 // us (two thirds of it were allocations, now kept: Scratch).
 #include <cmath>
 #include <new>

@@ -1,4 +1,4 @@
-// Streaming multigrid kernels for the large levels (n >= 256).
+// Streaming multigrid kernels for the large levels (n >= PM_STREAM_MIN_N).
 //
 // A block owns an SJ x SK tile of (j, k) columns and a chunk of CI consecutive
 // i-planes, and walks through the planes once. Each thread keeps a fixed set of
@@ -13,7 +13,8 @@
 // result goes to a different buffer (out of place), because neighbouring blocks
 // still read the old values of the shared halo. Options:
 //   NORM     sums ||f - L u||^2 and ||f||^2 of the *input* field on the block's
-//            interior (the convergence test of the previous cycle, for free);
+//            interior (the convergence test of the previous cycle, for free), and
+//            the output's sum;
 // k_rr_stream: residual f - L u on the fine grid, restricted to the coarse grid
 // (full weighting (1,3,3,1)/8 per axis, or the 8-child average), in one pass.
 #include "internal.h"

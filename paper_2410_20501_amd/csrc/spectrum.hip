@@ -12,8 +12,8 @@
 //
 // Binning mode by mode (window by pow and sin in FP64, three LDS atomics a mode with most
 // lanes of a wave in one shell, then global atomics of every block into the same shells)
-// took 208 of 400 us at 256^3; now 252 us in all (127 at 128^3 against 254, 2720 at 512^3
-// against 3440), most of it the transform's passes.
+// took 208 of 400 us at 256^3; now 216 us in all (120 at 128^3 against 238, 2083 at 512^3
+// against 3311, 18.8 ms at 1024^3 against 32.8), most of it the transform's passes.
 #include <cmath>
 #include <vector>
 
